@@ -44,6 +44,7 @@ void free_plan(fdas_plan* p) {
   if (p->d_tscale) (void)hipFree(p->d_tscale);
   if (p->d_dtiles) (void)hipFree(p->d_dtiles);
   if (p->d_drows) (void)hipFree(p->d_drows);
+  if (p->d_dedge) (void)hipFree(p->d_dedge);
   for (auto& t : p->ols) {
     if (t.H) (void)hipFree(t.H);
     if (t.tw1) (void)hipFree(t.tw1);
@@ -299,13 +300,13 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
   p->direct = desc->method == FDAS_CONV_DIRECT_MFMA;
   std::vector<float> Bpk, tscale;
   std::vector<uint16_t> Bsp;
-  std::vector<int> dtiles, drows;
+  std::vector<int> dtiles, drows, dedge;
   if (p->direct && desc->precision != FDAS_PREC_FP32) {
     fdas::direct_pack_split(bank, desc->z_max, desc->precision == FDAS_PREC_SPLIT_BF16, Bsp, tscale, dtiles, drows,
                             &p->dP_max, &p->dP8_max);
     p->dtiles = (int)dtiles.size() / 4;
   } else if (p->direct) {
-    fdas::direct_pack(bank, desc->z_max, Bpk, dtiles, drows, &p->dP_max, &p->dP8_max);
+    fdas::direct_pack(bank, desc->z_max, Bpk, dtiles, drows, dedge, p->dgroups, &p->dP_max);
     p->dtiles = (int)dtiles.size() / 4;
   }
   p->h_ta.resize((size_t)desc->n_harm * p->rows);
@@ -325,7 +326,8 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
   } else if (p->direct) {
     if ((e = upload(&p->d_Bpk, Bpk.data(), Bpk.size() * sizeof(float))) != hipSuccess ||
         (e = upload(&p->d_dtiles, dtiles.data(), dtiles.size() * sizeof(int))) != hipSuccess ||
-        (e = upload(&p->d_drows, drows.data(), drows.size() * sizeof(int))) != hipSuccess) {
+        (e = upload(&p->d_drows, drows.data(), drows.size() * sizeof(int))) != hipSuccess ||
+        (e = upload(&p->d_dedge, dedge.data(), dedge.size() * sizeof(int))) != hipSuccess) {
       free_plan(p);
       return hip_fail(e, "uploading the direct-method template operand");
     }
@@ -381,10 +383,10 @@ fdas_status fdas_convolve(fdas_plan* p, const void* d_spectrum, int64_t n, float
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   hipError_t e;
   if (p->direct) {
-    const fdas::DirectTables t{p->d_Bpk, p->d_dtiles, p->d_drows, p->dtiles, p->dP_max, p->dP8_max,
-                               p->d_Bsp, p->d_tscale};
+    const fdas::DirectTables t{p->d_Bpk,  p->d_dtiles, p->d_drows, p->d_dedge, p->dgroups.data(), (int)p->dgroups.size(),
+                               p->dtiles, p->dP_max,   p->dP8_max, p->d_Bsp,   p->d_tscale};
     if (p->desc.precision == FDAS_PREC_FP32)
-      e = fdas::launch_direct_conv(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t,
+      e = fdas::launch_direct_conv(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t, p->cus,
                                    static_cast<hipStream_t>(stream));
     else
       e = fdas::launch_direct_conv_split(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t,

@@ -20,13 +20,23 @@ void ols_spectra(const std::vector<std::vector<std::complex<double>>>& bank, int
                  std::vector<float>& out);
 double erlang_threshold(int k, double p_fa);
 
-// Packed template operand of the direct (matrix-core) correlation: templates
-// ordered by |z| (0, -1, 1, -2, 2, ...) in tiles of 8; tile g covers taps
-// [-P_g, P_g - 1] in P_g pairs of 64 lane-ordered floats (zero-padded to a
-// multiple of 8 pairs).  tiles[g] = {P_g, first pair, members, padded pairs};
-// rows[8 g + t] = FOP row of member t.
+// Packed template operand of the direct FP32 (matrix-core) correlation: slots
+// of |z| = z_max, ..., 0 in tiles of 8, column 2 t the real and 2 t + 1 the
+// imaginary part of slot t's taps at distances d >= 0 (the taps are symmetric
+// in d and conjugate in z).  tiles[4 g] = {steps of 4 distances, 0, 0, 0};
+// rows[16 g + col] = FOP row of column col (even: +z, odd: -z, -1: none);
+// edge[8 g + t] = L/2 of slot t.  Consecutive tiles form groups that one
+// launch works on together (at most 6 tiles and 64 KiB of operand).  A
+// group's entries of 64 lane-ordered floats are step-major: step p of every
+// tile with more than p steps, then two steps per tile holding the unpaired
+// taps at d = -edge.
+struct DirectGroup {
+  int first, tiles;   // tile range
+  int offset, count;  // operand entries
+};
 void direct_pack(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, std::vector<float>& Bpk,
-                 std::vector<int>& tiles, std::vector<int>& rows, int* P_max, int* P8_max);
+                 std::vector<int>& tiles, std::vector<int>& rows, std::vector<int>& edge,
+                 std::vector<DirectGroup>& groups, int* P_max);
 
 // ---- overlap-save geometry -------------------------------------------------
 constexpr int kOlsC = 4096;      // default FFT length of one chunk
@@ -85,30 +95,34 @@ struct ConvTrial {
 hipError_t launch_ols_conv_batch(const ConvTrial* trials, int ntrials, int64_t item_begin, int64_t item_end,
                                  const OlsTables& t, int rows, int tmax, int slots, hipStream_t s);
 
-// Split 16-bit form of the packed operand: templates ordered and tiled as in
-// direct_pack; tile g covers 2 P8 taps in P8/8 groups of 16, each group 64
+// Split 16-bit operand: templates ordered by |z| (0, -1, 1, -2, 2, ...) in
+// tiles of 8, tiles[4 g] = {P, first 16-tap group, members, P rounded up to 8}
+// and rows[8 g + t] the FOP row of member t; tile g covers 2 P8 taps in P8/8 groups of 16, each group 64
 // lanes x 8 hi values then 64 x 8 lo values (16-bit patterns, lane group
 // kg = lane/16 holding taps 4kg..4kg+3 as (Re, Im) pairs).  Tile values are
 // scaled by 2^eh (largest magnitude brought to about 2^14); tscale[g] = 2^-eh.
-// tiles[4g + 1] counts 16-tap groups.  bf16 selects bfloat16, else FP16.
+// bf16 selects bfloat16, else FP16.
 void direct_pack_split(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, bool bf16,
                        std::vector<uint16_t>& Bsp, std::vector<float>& tscale, std::vector<int>& tiles,
                        std::vector<int>& rows, int* P_max, int* P8_max);
 
 struct DirectTables {
-  const float* Bpk;    // packed template operand
-  const int4* tiles;   // per tile {P, first pair, members, padded pairs}
-  const int* rows;     // [ntiles][8] FOP rows
+  const float* Bpk;    // packed template operand (FP32)
+  const int4* tiles;   // per tile, as direct_pack / direct_pack_split describe
+  const int* rows;     // FOP rows of the tiles' columns
+  const int* edge;     // [ntiles][8] L/2 of every slot (FP32)
+  const DirectGroup* groups;  // host memory (FP32)
+  int ngroups;
   int ntiles;
-  int P_max;    // largest P over the tiles
-  int P8_max;   // largest padded pair count
+  int P_max;      // widest template, L/2
+  int P8_max;     // largest padded pair count (split precisions)
   const uint4* Bsp = nullptr;     // split 16-bit operand (split precisions)
   const float* tscale = nullptr;  // per-tile 2^-eh (split precisions)
 };
 int direct_block_bins();
 int direct_max_half_taps();
 size_t direct_lds_bytes(int P_max, int P8_max);
-hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
+hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t, int cus,
                               hipStream_t s);
 hipError_t launch_direct_conv_split(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
                                     bool bf16, hipStream_t s);

@@ -170,6 +170,67 @@ void ols_spectra(const std::vector<std::vector<cd>>& bank, int C, int P, std::ve
 }
 
 void direct_pack(const std::vector<std::vector<cd>>& bank, int z_max, std::vector<float>& Bpk,
+                 std::vector<int>& tiles, std::vector<int>& rows, std::vector<int>& edge,
+                 std::vector<DirectGroup>& groups, int* P_max) {
+  // slots hold |z| = z_max, z_max - 1, ..., 0, eight to a tile
+  const int T = (z_max + 8) / 8;
+  tiles.assign((size_t)T * 4, 0);
+  rows.assign((size_t)T * 16, -1);
+  edge.assign((size_t)T * 8, 0);
+  Bpk.clear();
+  *P_max = tap_count(z_max) / 2;
+  for (int g = 0; g < T; ++g) {
+    tiles[4 * g] = (tap_count(z_max - 8 * g) / 2 + 3) / 4;  // distances 0 .. P - 1 of the widest member, in fours
+    for (int t = 0; t < 8 && z_max - 8 * g - t >= 0; ++t) {
+      const int az = z_max - 8 * g - t;
+      rows[16 * g + 2 * t] = z_max + az;
+      if (az > 0) rows[16 * g + 2 * t + 1] = z_max - az;
+      edge[8 * g + t] = tap_count(az) / 2;
+    }
+  }
+  // the fewest equal groups whose operands fit in 64 KiB each
+  for (int ng = (T + 5) / 6; ng <= T; ++ng) {
+    groups.clear();
+    int most = 0;
+    for (int q = 0, offset = 0; q < ng; ++q) {
+      DirectGroup gr{q * T / ng, (q + 1) * T / ng - q * T / ng, offset, 0};
+      for (int g = gr.first; g < gr.first + gr.tiles; ++g) gr.count += tiles[4 * g] + 2;
+      offset += gr.count;
+      most = std::max(most, gr.count);
+      groups.push_back(gr);
+    }
+    if (most * 256 <= 65536) break;
+  }
+  auto entry = [&](int g, int step) {  // step < steps: distances 4 step ..; else edge step (step - steps)
+    const int steps = tiles[4 * g];
+    for (int lane = 0; lane < 64; ++lane) {
+      const int col = lane & 15, kk = lane >> 4, slot = col >> 1;
+      const int az = z_max - 8 * g - slot;
+      cd h(0.0, 0.0);
+      if (az >= 0) {
+        const std::vector<cd>& hz = bank[z_max + az];
+        const int half = (int)hz.size() / 2;
+        if (step < steps) {
+          const int d = 4 * step + kk;
+          if (d < half) h = d == 0 ? 0.5 * hz[half] : hz[half + d];
+        } else if (4 * (step - steps) + kk == slot) {
+          h = hz[0];  // d = -L/2
+        }
+      }
+      Bpk.push_back((float)((col & 1) ? h.imag() : h.real()));
+    }
+  };
+  for (const DirectGroup& gr : groups) {
+    for (int p = 0; p < tiles[4 * gr.first]; ++p)
+      for (int g = gr.first; g < gr.first + gr.tiles && tiles[4 * g] > p; ++g) entry(g, p);
+    for (int g = gr.first; g < gr.first + gr.tiles; ++g)
+      for (int e = 0; e < 2; ++e) entry(g, tiles[4 * g] + e);
+  }
+}
+
+// Operand of the split kernel in FP32 and lane order: tap pairs
+// (d, d + 1) of tiles of 8 templates, against (Re X, Im X) of each tap.
+static void pack_pairs(const std::vector<std::vector<cd>>& bank, int z_max, std::vector<float>& Bpk,
                  std::vector<int>& tiles, std::vector<int>& rows, int* P_max, int* P8_max) {
   // member order by |z|: 0, -1, 1, -2, 2, ...
   std::vector<int> order;
@@ -239,7 +300,7 @@ void direct_pack_split(const std::vector<std::vector<cd>>& bank, int z_max, bool
                        std::vector<float>& tscale, std::vector<int>& tiles, std::vector<int>& rows, int* P_max,
                        int* P8_max) {
   std::vector<float> Bpk;
-  direct_pack(bank, z_max, Bpk, tiles, rows, P_max, P8_max);  // same order, tiles and supports
+  pack_pairs(bank, z_max, Bpk, tiles, rows, P_max, P8_max);  // same order, tiles and supports
   const int T = (int)tiles.size() / 4;
   tscale.assign(T, 1.0f);
   Bsp.clear();

@@ -17,9 +17,11 @@ struct fdas_plan {
   fdas::OlsTables ols[3];  // overlap-save tables per chunk length 2048, 4096, 8192 (built on demand)
   int ols_idx = 1;         // chunk length of the single-spectrum calls (the descriptor's)
   bool direct = false;      // FDAS_CONV_DIRECT_MFMA: matrix-core correlation instead of overlap-save
-  float* d_Bpk = nullptr;   // direct: packed template operand
-  int4* d_dtiles = nullptr; // direct: per-tile {P, first pair, members, 0}
-  int* d_drows = nullptr;   // direct: [tiles][8] FOP rows
+  float* d_Bpk = nullptr;   // direct, FP32: packed template operand
+  int4* d_dtiles = nullptr; // direct: tile table
+  int* d_drows = nullptr;   // direct: FOP rows of the tiles' columns
+  int* d_dedge = nullptr;   // direct, FP32: L/2 of every slot
+  std::vector<fdas::DirectGroup> dgroups;  // direct, FP32: tiles of every launch
   int dtiles = 0, dP_max = 0, dP8_max = 0;
   uint4* d_Bsp = nullptr;   // direct, split precisions: hi/lo 16-bit operand
   float* d_tscale = nullptr;  // direct, split precisions: per-tile 2^-eh
