@@ -45,6 +45,7 @@ void free_plan(fdas_plan* p) {
   if (p->d_dtiles) (void)hipFree(p->d_dtiles);
   if (p->d_drows) (void)hipFree(p->d_drows);
   if (p->d_dedge) (void)hipFree(p->d_dedge);
+  if (p->d_dedge_tap) (void)hipFree(p->d_dedge_tap);
   for (auto& t : p->ols) {
     if (t.H) (void)hipFree(t.H);
     if (t.tw1) (void)hipFree(t.tw1);
@@ -298,16 +299,15 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
   std::vector<std::vector<std::complex<double>>> bank;
   fdas::template_bank(desc->z_max, bank);
   p->direct = desc->method == FDAS_CONV_DIRECT_MFMA;
-  std::vector<float> Bpk, tscale;
-  std::vector<uint16_t> Bsp;
-  std::vector<int> dtiles, drows, dedge;
-  if (p->direct && desc->precision != FDAS_PREC_FP32) {
-    fdas::direct_pack_split(bank, desc->z_max, desc->precision == FDAS_PREC_SPLIT_BF16, Bsp, tscale, dtiles, drows,
-                            &p->dP_max, &p->dP8_max);
-    p->dtiles = (int)dtiles.size() / 4;
-  } else if (p->direct) {
-    fdas::direct_pack(bank, desc->z_max, Bpk, dtiles, drows, dedge, p->dgroups, &p->dP_max);
-    p->dtiles = (int)dtiles.size() / 4;
+  const bool split = desc->precision != FDAS_PREC_FP32;
+  fdas::DirectPack pk;
+  if (p->direct) {
+    if (split)
+      fdas::direct_pack_split(bank, desc->z_max, desc->precision == FDAS_PREC_SPLIT_BF16, pk);
+    else
+      fdas::direct_pack(bank, desc->z_max, pk);
+    p->dgroups = pk.groups;
+    p->dP_max = pk.P_max;
   }
   p->h_ta.resize((size_t)desc->n_harm * p->rows);
   for (int k = 1; k <= desc->n_harm; ++k) {
@@ -315,19 +315,14 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
     for (int r = 0; r < p->rows; ++r) p->h_ta[(size_t)(k - 1) * p->rows + r] = t;
   }
 
-  if (p->direct && desc->precision != FDAS_PREC_FP32) {
-    if ((e = upload(&p->d_Bsp, Bsp.data(), Bsp.size() * sizeof(uint16_t))) != hipSuccess ||
-        (e = upload(&p->d_tscale, tscale.data(), tscale.size() * sizeof(float))) != hipSuccess ||
-        (e = upload(&p->d_dtiles, dtiles.data(), dtiles.size() * sizeof(int))) != hipSuccess ||
-        (e = upload(&p->d_drows, drows.data(), drows.size() * sizeof(int))) != hipSuccess) {
-      free_plan(p);
-      return hip_fail(e, "uploading the split direct-method template operand");
-    }
-  } else if (p->direct) {
-    if ((e = upload(&p->d_Bpk, Bpk.data(), Bpk.size() * sizeof(float))) != hipSuccess ||
-        (e = upload(&p->d_dtiles, dtiles.data(), dtiles.size() * sizeof(int))) != hipSuccess ||
-        (e = upload(&p->d_drows, drows.data(), drows.size() * sizeof(int))) != hipSuccess ||
-        (e = upload(&p->d_dedge, dedge.data(), dedge.size() * sizeof(int))) != hipSuccess) {
+  if (p->direct) {
+    if ((split ? (e = upload(&p->d_Bsp, pk.Bsp.data(), pk.Bsp.size() * sizeof(uint16_t))) != hipSuccess ||
+                     (e = upload(&p->d_tscale, pk.tscale.data(), pk.tscale.size() * sizeof(float))) != hipSuccess
+               : (e = upload(&p->d_Bpk, pk.Bpk.data(), pk.Bpk.size() * sizeof(float))) != hipSuccess) ||
+        (e = upload(&p->d_dtiles, pk.tiles.data(), pk.tiles.size() * sizeof(int))) != hipSuccess ||
+        (e = upload(&p->d_drows, pk.rows.data(), pk.rows.size() * sizeof(int))) != hipSuccess ||
+        (e = upload(&p->d_dedge, pk.edge.data(), pk.edge.size() * sizeof(int))) != hipSuccess ||
+        (e = upload(&p->d_dedge_tap, pk.edge_tap.data(), pk.edge_tap.size() * sizeof(float))) != hipSuccess) {
       free_plan(p);
       return hip_fail(e, "uploading the direct-method template operand");
     }
@@ -383,13 +378,13 @@ fdas_status fdas_convolve(fdas_plan* p, const void* d_spectrum, int64_t n, float
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   hipError_t e;
   if (p->direct) {
-    const fdas::DirectTables t{p->d_Bpk,  p->d_dtiles, p->d_drows, p->d_dedge, p->dgroups.data(), (int)p->dgroups.size(),
-                               p->dtiles, p->dP_max,   p->dP8_max, p->d_Bsp,   p->d_tscale};
+    const fdas::DirectTables t{p->d_Bpk,   p->d_Bsp,       p->d_tscale,       p->d_dtiles,           p->d_drows,
+                               p->d_dedge, p->d_dedge_tap, p->dgroups.data(), (int)p->dgroups.size(), p->dP_max};
     if (p->desc.precision == FDAS_PREC_FP32)
       e = fdas::launch_direct_conv(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t, p->cus,
                                    static_cast<hipStream_t>(stream));
     else
-      e = fdas::launch_direct_conv_split(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t,
+      e = fdas::launch_direct_conv_split(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t, p->cus,
                                          p->desc.precision == FDAS_PREC_SPLIT_BF16, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "launching the direct correlation");
   } else {

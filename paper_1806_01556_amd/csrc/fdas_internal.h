@@ -20,23 +20,35 @@ void ols_spectra(const std::vector<std::vector<std::complex<double>>>& bank, int
                  std::vector<float>& out);
 double erlang_threshold(int k, double p_fa);
 
-// Packed template operand of the direct FP32 (matrix-core) correlation: slots
-// of |z| = z_max, ..., 0 in tiles of 8, column 2 t the real and 2 t + 1 the
+// Packed template operand of the direct (matrix-core) correlations: slots of
+// |z| = z_max, ..., 0 in tiles of 8, column 2 t the real and 2 t + 1 the
 // imaginary part of slot t's taps at distances d >= 0 (the taps are symmetric
-// in d and conjugate in z).  tiles[4 g] = {steps of 4 distances, 0, 0, 0};
-// rows[16 g + col] = FOP row of column col (even: +z, odd: -z, -1: none);
-// edge[8 g + t] = L/2 of slot t.  Consecutive tiles form groups that one
-// launch works on together (at most 6 tiles and 64 KiB of operand).  A
-// group's entries of 64 lane-ordered floats are step-major: step p of every
-// tile with more than p steps, then two steps per tile holding the unpaired
-// taps at d = -edge.
+// in d and conjugate in z).  Consecutive tiles form groups that one launch
+// works on together (at most 6 tiles and 64 KiB of operand).  A group's
+// entries are step-major: step p of every tile with more than p steps.
+//   FP32 (Bpk): a step is 4 distances, an entry 64 lane-ordered floats
+//   (column lane % 16, distance 4 p + lane / 16).
+//   Split (Bsp): a step is 32 distances, an entry 64 lanes x 8 hi then 64 x 8
+//   lo 16-bit patterns (distances 32 p + 8 (lane / 16) + e), the tile's values
+//   scaled by 2^eh (largest magnitude brought to about 2^14).
 struct DirectGroup {
   int first, tiles;   // tile range
   int offset, count;  // operand entries
 };
-void direct_pack(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, std::vector<float>& Bpk,
-                 std::vector<int>& tiles, std::vector<int>& rows, std::vector<int>& edge,
-                 std::vector<DirectGroup>& groups, int* P_max);
+struct DirectPack {
+  std::vector<float> Bpk;
+  std::vector<uint16_t> Bsp;
+  std::vector<float> tscale;    // [tiles] 2^-eh (split)
+  std::vector<int> tiles;       // [tiles][4] {steps, 0, 0, 0}
+  std::vector<int> rows;        // [tiles][16] FOP row of a column (even: +z, odd: -z, -1: none)
+  std::vector<int> edge;        // [tiles][8] L/2 of a slot
+  std::vector<float> edge_tap;  // [tiles][16] the unpaired tap at d = -L/2 of a column (x 2^eh)
+  std::vector<DirectGroup> groups;
+  int P_max = 0;                // widest template, L/2
+};
+void direct_pack(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, DirectPack& pk);
+void direct_pack_split(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, bool bf16,
+                       DirectPack& pk);
 
 // ---- overlap-save geometry -------------------------------------------------
 constexpr int kOlsC = 4096;      // default FFT length of one chunk
@@ -95,37 +107,23 @@ struct ConvTrial {
 hipError_t launch_ols_conv_batch(const ConvTrial* trials, int ntrials, int64_t item_begin, int64_t item_end,
                                  const OlsTables& t, int rows, int tmax, int slots, hipStream_t s);
 
-// Split 16-bit operand: templates ordered by |z| (0, -1, 1, -2, 2, ...) in
-// tiles of 8, tiles[4 g] = {P, first 16-tap group, members, P rounded up to 8}
-// and rows[8 g + t] the FOP row of member t; tile g covers 2 P8 taps in P8/8 groups of 16, each group 64
-// lanes x 8 hi values then 64 x 8 lo values (16-bit patterns, lane group
-// kg = lane/16 holding taps 4kg..4kg+3 as (Re, Im) pairs).  Tile values are
-// scaled by 2^eh (largest magnitude brought to about 2^14); tscale[g] = 2^-eh.
-// bf16 selects bfloat16, else FP16.
-void direct_pack_split(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, bool bf16,
-                       std::vector<uint16_t>& Bsp, std::vector<float>& tscale, std::vector<int>& tiles,
-                       std::vector<int>& rows, int* P_max, int* P8_max);
-
+// Device tables of the direct correlations, as DirectPack describes them.
 struct DirectTables {
-  const float* Bpk;    // packed template operand (FP32)
-  const int4* tiles;   // per tile, as direct_pack / direct_pack_split describe
-  const int* rows;     // FOP rows of the tiles' columns
-  const int* edge;     // [ntiles][8] L/2 of every slot (FP32)
-  const DirectGroup* groups;  // host memory (FP32)
+  const float* Bpk;
+  const uint4* Bsp;
+  const float* tscale;
+  const int4* tiles;
+  const int* rows;
+  const int* edge;
+  const float* edge_tap;
+  const DirectGroup* groups;  // host memory
   int ngroups;
-  int ntiles;
-  int P_max;      // widest template, L/2
-  int P8_max;     // largest padded pair count (split precisions)
-  const uint4* Bsp = nullptr;     // split 16-bit operand (split precisions)
-  const float* tscale = nullptr;  // per-tile 2^-eh (split precisions)
+  int P_max;
 };
-int direct_block_bins();
-int direct_max_half_taps();
-size_t direct_lds_bytes(int P_max, int P8_max);
 hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t, int cus,
                               hipStream_t s);
 hipError_t launch_direct_conv_split(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
-                                    bool bf16, hipStream_t s);
+                                    int cus, bool bf16, hipStream_t s);
 
 // Columns handled by one workgroup of the 85-row harmonic-sum kernel.
 int harmsum_tile_columns();

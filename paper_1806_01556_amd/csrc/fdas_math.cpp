@@ -169,116 +169,68 @@ void ols_spectra(const std::vector<std::vector<cd>>& bank, int C, int P, std::ve
   for (auto& t : th) t.join();
 }
 
-void direct_pack(const std::vector<std::vector<cd>>& bank, int z_max, std::vector<float>& Bpk,
-                 std::vector<int>& tiles, std::vector<int>& rows, std::vector<int>& edge,
-                 std::vector<DirectGroup>& groups, int* P_max) {
-  // slots hold |z| = z_max, z_max - 1, ..., 0, eight to a tile
+namespace {
+
+// Tile table of the direct correlations: slots of |z| = z_max .. 0 in tiles of
+// 8, `per_step` distances to a step; groups of consecutive tiles, the fewest
+// equal ones of at most 6 tiles and 64 KiB (`entry_bytes` per entry, `extra`
+// entries per tile beside its steps).
+void tile_table(int z_max, int per_step, int extra, int entry_bytes, DirectPack& pk) {
   const int T = (z_max + 8) / 8;
-  tiles.assign((size_t)T * 4, 0);
-  rows.assign((size_t)T * 16, -1);
-  edge.assign((size_t)T * 8, 0);
-  Bpk.clear();
-  *P_max = tap_count(z_max) / 2;
+  pk.tiles.assign((size_t)T * 4, 0);
+  pk.rows.assign((size_t)T * 16, -1);
+  pk.edge.assign((size_t)T * 8, 0);
+  pk.P_max = tap_count(z_max) / 2;
   for (int g = 0; g < T; ++g) {
-    tiles[4 * g] = (tap_count(z_max - 8 * g) / 2 + 3) / 4;  // distances 0 .. P - 1 of the widest member, in fours
+    // distances 0 .. P - 1 of the widest member
+    pk.tiles[4 * g] = (tap_count(z_max - 8 * g) / 2 + per_step - 1) / per_step;
     for (int t = 0; t < 8 && z_max - 8 * g - t >= 0; ++t) {
       const int az = z_max - 8 * g - t;
-      rows[16 * g + 2 * t] = z_max + az;
-      if (az > 0) rows[16 * g + 2 * t + 1] = z_max - az;
-      edge[8 * g + t] = tap_count(az) / 2;
+      pk.rows[16 * g + 2 * t] = z_max + az;
+      if (az > 0) pk.rows[16 * g + 2 * t + 1] = z_max - az;
+      pk.edge[8 * g + t] = tap_count(az) / 2;
     }
   }
-  // the fewest equal groups whose operands fit in 64 KiB each
   for (int ng = (T + 5) / 6; ng <= T; ++ng) {
-    groups.clear();
+    pk.groups.clear();
     int most = 0;
     for (int q = 0, offset = 0; q < ng; ++q) {
       DirectGroup gr{q * T / ng, (q + 1) * T / ng - q * T / ng, offset, 0};
-      for (int g = gr.first; g < gr.first + gr.tiles; ++g) gr.count += tiles[4 * g] + 2;
+      for (int g = gr.first; g < gr.first + gr.tiles; ++g) gr.count += pk.tiles[4 * g] + extra;
       offset += gr.count;
       most = std::max(most, gr.count);
-      groups.push_back(gr);
+      pk.groups.push_back(gr);
     }
-    if (most * 256 <= 65536) break;
-  }
-  auto entry = [&](int g, int step) {  // step < steps: distances 4 step ..; else edge step (step - steps)
-    const int steps = tiles[4 * g];
-    for (int lane = 0; lane < 64; ++lane) {
-      const int col = lane & 15, kk = lane >> 4, slot = col >> 1;
-      const int az = z_max - 8 * g - slot;
-      cd h(0.0, 0.0);
-      if (az >= 0) {
-        const std::vector<cd>& hz = bank[z_max + az];
-        const int half = (int)hz.size() / 2;
-        if (step < steps) {
-          const int d = 4 * step + kk;
-          if (d < half) h = d == 0 ? 0.5 * hz[half] : hz[half + d];
-        } else if (4 * (step - steps) + kk == slot) {
-          h = hz[0];  // d = -L/2
-        }
-      }
-      Bpk.push_back((float)((col & 1) ? h.imag() : h.real()));
-    }
-  };
-  for (const DirectGroup& gr : groups) {
-    for (int p = 0; p < tiles[4 * gr.first]; ++p)
-      for (int g = gr.first; g < gr.first + gr.tiles && tiles[4 * g] > p; ++g) entry(g, p);
-    for (int g = gr.first; g < gr.first + gr.tiles; ++g)
-      for (int e = 0; e < 2; ++e) entry(g, tiles[4 * g] + e);
+    if (most * entry_bytes <= 65536) break;
   }
 }
 
-// Operand of the split kernel in FP32 and lane order: tap pairs
-// (d, d + 1) of tiles of 8 templates, against (Re X, Im X) of each tap.
-static void pack_pairs(const std::vector<std::vector<cd>>& bank, int z_max, std::vector<float>& Bpk,
-                 std::vector<int>& tiles, std::vector<int>& rows, int* P_max, int* P8_max) {
-  // member order by |z|: 0, -1, 1, -2, 2, ...
-  std::vector<int> order;
-  order.push_back(0);
-  for (int a = 1; a <= z_max; ++a) {
-    order.push_back(-a);
-    order.push_back(a);
-  }
-  const int T = ((int)order.size() + 7) / 8;
-  tiles.assign((size_t)T * 4, 0);
-  rows.assign((size_t)T * 8, -1);
-  Bpk.clear();
-  int pairs = 0, pm = 0, p8m = 0;
-  for (int g = 0; g < T; ++g) {
-    const int cnt = std::min(8, (int)order.size() - 8 * g);
-    int P = 0;
-    for (int t = 0; t < cnt; ++t) P = std::max(P, tap_count(order[8 * g + t]) / 2);
-    const int P8 = (P + 7) / 8 * 8;  // pairs padded with zero values to a multiple of 8
-    pm = std::max(pm, P);
-    p8m = std::max(p8m, P8);
-    tiles[4 * g + 0] = P;
-    tiles[4 * g + 1] = pairs;
-    tiles[4 * g + 2] = cnt;
-    tiles[4 * g + 3] = P8;
-    for (int t = 0; t < cnt; ++t) rows[8 * g + t] = order[8 * g + t] + z_max;
-    for (int p = 0; p < P8; ++p) {
-      for (int lane = 0; lane < 64; ++lane) {
-        const int col = lane & 15, k = lane >> 4;
-        const int slot = col >> 1, part = col & 1;
-        const int d = -P + 2 * p + (k >> 1);  // tap of this k
-        cd h(0.0, 0.0);
-        if (slot < cnt && p < P) {
-          const int z = order[8 * g + slot];
-          const std::vector<cd>& hz = bank[z + z_max];
-          const int L = (int)hz.size();
-          const int t = d + L / 2;
-          if (t >= 0 && t < L) h = hz[t];
-        }
-        // (Re X, Im X) against the Re-column: (Re h, -Im h); against the Im-column: (Im h, Re h)
-        const bool im_x = (k & 1) != 0;
-        const double v = part == 0 ? (im_x ? -h.imag() : h.real()) : (im_x ? h.real() : h.imag());
-        Bpk.push_back((float)v);
-      }
-    }
-    pairs += P8;
-  }
-  *P_max = pm;
-  *P8_max = p8m;
+// The tap of column `col` of tile g at distance d >= 0 (half of it at d = 0,
+// where X[j + d] + X[j - d] counts the bin twice), or the unpaired tap at
+// -L/2 for d < 0; zero beyond the support.
+double slot_tap(const std::vector<std::vector<cd>>& bank, int z_max, int g, int col, int d) {
+  const int az = z_max - 8 * g - (col >> 1);
+  if (az < 0) return 0.0;
+  const std::vector<cd>& hz = bank[z_max + az];
+  const int half = (int)hz.size() / 2;
+  if (d >= half) return 0.0;
+  const cd h = d < 0 ? hz[0] : d == 0 ? 0.5 * hz[half] : hz[half + d];
+  return (col & 1) ? h.imag() : h.real();
+}
+
+}  // namespace
+
+void direct_pack(const std::vector<std::vector<cd>>& bank, int z_max, DirectPack& pk) {
+  tile_table(z_max, 4, 0, 256, pk);
+  auto entry = [&](int g, int step) {
+    for (int lane = 0; lane < 64; ++lane)
+      pk.Bpk.push_back((float)slot_tap(bank, z_max, g, lane & 15, 4 * step + (lane >> 4)));
+  };
+  for (const DirectGroup& gr : pk.groups)
+    for (int p = 0; p < pk.tiles[4 * gr.first]; ++p)
+      for (int g = gr.first; g < gr.first + gr.tiles && pk.tiles[4 * g] > p; ++g) entry(g, p);
+  for (int c = 0; c < (int)pk.rows.size(); ++c)
+    pk.edge_tap.push_back((float)slot_tap(bank, z_max, c / 16, c % 16, -1));
 }
 
 namespace {
@@ -296,55 +248,34 @@ float from_bf16_bits(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b 
 
 }  // namespace
 
-void direct_pack_split(const std::vector<std::vector<cd>>& bank, int z_max, bool bf16, std::vector<uint16_t>& Bsp,
-                       std::vector<float>& tscale, std::vector<int>& tiles, std::vector<int>& rows, int* P_max,
-                       int* P8_max) {
-  std::vector<float> Bpk;
-  pack_pairs(bank, z_max, Bpk, tiles, rows, P_max, P8_max);  // same order, tiles and supports
-  const int T = (int)tiles.size() / 4;
-  tscale.assign(T, 1.0f);
-  Bsp.clear();
-  int groups = 0;
+void direct_pack_split(const std::vector<std::vector<cd>>& bank, int z_max, bool bf16, DirectPack& pk) {
+  tile_table(z_max, 32, 0, 2048, pk);
+  const int T = (int)pk.tiles.size() / 4;
+  std::vector<int> eh(T, 0);
   for (int g = 0; g < T; ++g) {
-    const int P = tiles[4 * g + 0], first_pair = tiles[4 * g + 1], P8 = tiles[4 * g + 3];
-    // FP32 value of (tap d, part) for column col, read back from the FP32 pack:
-    // pair p holds taps -P + 2p (k = 0, 1) and -P + 2p + 1 (k = 2, 3)
-    auto val = [&](int d, int part, int col) -> float {
-      const int t = d + P;
-      const int p = t >> 1, k = 2 * (t & 1) + part;
-      if (p >= P8) return 0.0f;
-      return Bpk[((size_t)(first_pair + p)) * 64 + k * 16 + col];
-    };
     float mx = 0.0f;
-    for (int p = 0; p < P8 * 64; ++p) mx = std::max(mx, std::fabs(Bpk[(size_t)first_pair * 64 + p]));
-    const int eh = mx > 0.0f ? 14 - std::ilogb(mx) : 0;
-    tscale[g] = std::ldexp(1.0f, -eh);
-    tiles[4 * g + 1] = groups;
-    const int G16 = P8 / 8;
-    for (int q = 0; q < G16; ++q) {
-      uint16_t hi[64 * 8], lo[64 * 8];
-      for (int lane = 0; lane < 64; ++lane) {
-        const int col = lane & 15, kg = lane >> 4;
-        for (int e = 0; e < 8; ++e) {
-          const int d = -P + 16 * q + 4 * kg + e / 2;
-          const float v = std::ldexp(val(d, e & 1, col), eh);
-          uint16_t h, l;
-          if (bf16) {
-            h = to_bf16_bits(v);
-            l = to_bf16_bits(v - from_bf16_bits(h));
-          } else {
-            h = to_f16_bits(v);
-            l = to_f16_bits(v - from_f16_bits(h));
-          }
-          hi[lane * 8 + e] = h;
-          lo[lane * 8 + e] = l;
-        }
-      }
-      Bsp.insert(Bsp.end(), hi, hi + 64 * 8);
-      Bsp.insert(Bsp.end(), lo, lo + 64 * 8);
-    }
-    groups += G16;
+    for (int col = 0; col < 16; ++col)
+      for (int d = -1; d < 32 * pk.tiles[4 * g]; ++d) mx = std::max(mx, std::fabs((float)slot_tap(bank, z_max, g, col, d)));
+    eh[g] = mx > 0.0f ? 14 - std::ilogb(mx) : 0;
+    pk.tscale.push_back(std::ldexp(1.0f, -eh[g]));
   }
+  auto entry = [&](int g, int step) {
+    uint16_t hi[64 * 8], lo[64 * 8];
+    for (int lane = 0; lane < 64; ++lane)
+      for (int e = 0; e < 8; ++e) {
+        const float v = std::ldexp((float)slot_tap(bank, z_max, g, lane & 15, 32 * step + 8 * (lane >> 4) + e), eh[g]);
+        const uint16_t h = bf16 ? to_bf16_bits(v) : to_f16_bits(v);
+        hi[lane * 8 + e] = h;
+        lo[lane * 8 + e] = bf16 ? to_bf16_bits(v - from_bf16_bits(h)) : to_f16_bits(v - from_f16_bits(h));
+      }
+    pk.Bsp.insert(pk.Bsp.end(), hi, hi + 64 * 8);
+    pk.Bsp.insert(pk.Bsp.end(), lo, lo + 64 * 8);
+  };
+  for (const DirectGroup& gr : pk.groups)
+    for (int p = 0; p < pk.tiles[4 * gr.first]; ++p)
+      for (int g = gr.first; g < gr.first + gr.tiles && pk.tiles[4 * g] > p; ++g) entry(g, p);
+  for (int c = 0; c < (int)pk.rows.size(); ++c)
+    pk.edge_tap.push_back(std::ldexp((float)slot_tap(bank, z_max, c / 16, c % 16, -1), eh[c / 16]));
 }
 
 void fft_twiddles(int C, std::vector<float>& tw1, std::vector<float>& tw2) {

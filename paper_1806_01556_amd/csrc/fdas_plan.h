@@ -17,14 +17,15 @@ struct fdas_plan {
   fdas::OlsTables ols[3];  // overlap-save tables per chunk length 2048, 4096, 8192 (built on demand)
   int ols_idx = 1;         // chunk length of the single-spectrum calls (the descriptor's)
   bool direct = false;      // FDAS_CONV_DIRECT_MFMA: matrix-core correlation instead of overlap-save
-  float* d_Bpk = nullptr;   // direct, FP32: packed template operand
-  int4* d_dtiles = nullptr; // direct: tile table
-  int* d_drows = nullptr;   // direct: FOP rows of the tiles' columns
-  int* d_dedge = nullptr;   // direct, FP32: L/2 of every slot
-  std::vector<fdas::DirectGroup> dgroups;  // direct, FP32: tiles of every launch
-  int dtiles = 0, dP_max = 0, dP8_max = 0;
-  uint4* d_Bsp = nullptr;   // direct, split precisions: hi/lo 16-bit operand
-  float* d_tscale = nullptr;  // direct, split precisions: per-tile 2^-eh
+  float* d_Bpk = nullptr;       // direct, FP32: packed template operand
+  uint4* d_Bsp = nullptr;       // direct, split precisions: hi/lo 16-bit operand
+  float* d_tscale = nullptr;    // direct, split precisions: per-tile 2^-eh
+  int4* d_dtiles = nullptr;     // direct: tile table
+  int* d_drows = nullptr;       // direct: FOP rows of the tiles' columns
+  int* d_dedge = nullptr;       // direct: L/2 of every slot
+  float* d_dedge_tap = nullptr; // direct: unpaired tap of every column
+  std::vector<fdas::DirectGroup> dgroups;  // direct: tiles of every launch
+  int dP_max = 0;
   float* d_ta = nullptr;    // [n_harm][rows] default thresholds
   std::vector<float> h_ta;
   fdas_cand* d_sort_a = nullptr;  // [n_harm * cand_capacity] packed candidates

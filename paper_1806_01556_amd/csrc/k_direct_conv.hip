@@ -64,6 +64,35 @@ __device__ __forceinline__ float swap_pair(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
 }
 
+// What the epilogue needs of a column, staged in LDS: a global load there would
+// wait for the stores of the tile before it.
+struct ColumnInfo {
+  int row;    // FOP row, -1: none
+  int edge;   // L/2
+  float tap;  // unpaired tap
+  float scale;
+};
+
+__device__ __forceinline__ void load_columns(ColumnInfo* col, int columns, const int* __restrict__ rows,
+                                             const int* __restrict__ edge, const float* __restrict__ edge_tap,
+                                             const float* __restrict__ tscale, int tid) {
+  if (tid < columns) col[tid] = {rows[tid], edge[tid / 2], edge_tap[tid], tscale ? tscale[tid / 16] : 1.0f};
+}
+
+// The unpaired tap at d = -P of this lane's column: a += X[j - P] h for its 4
+// bins of each sub-tile, STEP bins apart.
+template <int STEP, int N>
+__device__ __forceinline__ void edge_add(const float2* __restrict__ here, int P, float h, v4f (&ar)[N], v4f (&ai)[N]) {
+#pragma unroll
+  for (int s = 0; s < N; ++s)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float2 f = here[STEP * s + v - P];
+      ar[s][v] = fmaf(f.x, h, ar[s][v]);
+      ai[s][v] = fmaf(f.y, h, ai[s][v]);
+    }
+}
+
 // Powers of one +-z pair from its two real-filter correlations, and their
 // store.  An even lane holds A = X * Re h (a: its real, b: its imaginary
 // part), its odd neighbour B = X * Im h; Y_z = A + iB, Y_-z = A - iB.  The even
@@ -93,20 +122,24 @@ __device__ __forceinline__ void pair_store(const v4f& a, const v4f& b, int row, 
 
 // A group of TG tiles at once: tiles[t] = {folded steps, 0, 0, 0} (steps fall
 // with t), rows[t * 16 + col] = FOP row of column col (-1: none),
-// edge[t * 8 + slot] = L/2 of the slot's template.  The operand holds 64
+// edge[t * 8 + slot] = L/2 of the slot's template, edge_tap[t * 16 + col] its
+// unpaired tap.  The operand holds 64
 // floats per (step, tile) in lane order: step p (lane group kk: distance
-// d = 4 p + kk) of every tile with more than p steps, then two edge steps per
-// tile (step e: the taps at -edge[4 e + kk]).  Dynamic LDS: the operand
-// (`count` entries) and two strips of X (Pm + 8 bins on either side of the
-// workgroup's bins).
+// d = 4 p + kk) of every tile with more than p steps.  Dynamic LDS: the operand
+// (`count` entries, and as much again as one step holds, read ahead) and two
+// strips of X (Pm + 8 bins on either side of the workgroup's bins).  The
+// unpaired taps are added on the vector units (8 multiply-adds per tile and
+// sub-tile against 4 matrix instructions of 32 cycles).
 //
 // Bound by the FP32 matrix pipe (2 instructions of 32 cycles per 4 distances,
 // 16 bins and 8 |z|).  A folded operand is read and added once and used by
 // every tile that still runs at its distance: the accumulators of all tiles
 // stay in registers (8 per tile and sub-tile), which leaves two waves per
 // SIMD, so the next step's LDS reads are issued before this step's products.
-// Measured on 2^20 bins and 85 templates: 0.393 ms, 127 TFLOP/s issued, matrix
-// pipe busy 80 %; without the two symmetries 1.265 ms; one tile at a time with
+// FP32 matrix and vector instructions do not overlap on a SIMD (measured side
+// by side: the times add), so every vector instruction counts.
+// Measured on 2^20 bins and 85 templates: 0.382 ms, the matrix pipe busy 80 % of
+// the time; without the two symmetries 1.265 ms; one tile at a time with
 // the folded operand re-read per tile and three or four waves per SIMD
 // 0.413-0.456 ms.
 template <int TG>
@@ -132,7 +165,7 @@ __device__ __forceinline__ void fold_steps(FoldState<TG>& st, const int4* __rest
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) bv[t] = st.b[t];
-    // reads past the last step stay inside the strip's padding and the edge steps
+    // reads past the last step stay inside the strip's padding and the operand's tail
     st.up += 4;
     st.dn -= 4;
     st.bp += 64 * T;
@@ -158,14 +191,16 @@ __device__ __forceinline__ void fold_steps(FoldState<TG>& st, const int4* __rest
 template <int TG>
 __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const float4* __restrict__ Bpk,
-    const int4* __restrict__ tiles, const int* __restrict__ rows, const int* __restrict__ edge, int count, int Pm,
-    int blocks) {
+    const int4* __restrict__ tiles, const int* __restrict__ rows, const int* __restrict__ edge,
+    const float* __restrict__ edge_tap, int count, int Pm, int blocks) {
   extern __shared__ float4 lds4[];
+  __shared__ ColumnInfo cols[16 * TG];
   const int tid = threadIdx.x;
+  load_columns(cols, 16 * TG, rows, edge, edge_tap, nullptr, tid);
   const int halo = Pm + FOLD_PAD;
   const int strip = BLK_BINS + 2 * halo;  // bins jb - halo + u
   const float* bs = reinterpret_cast<const float*>(lds4);
-  float2* xs = reinterpret_cast<float2*>(lds4 + 16 * count);
+  float2* xs = reinterpret_cast<float2*>(lds4 + 16 * (count + TG));
   for (int i = tid; i < count * 16; i += DW * 64) lds4[i] = Bpk[i];
   const int lane = tid & 63;
   const int w = tid >> 6;
@@ -201,21 +236,12 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     fold_steps<TG, TG>(st, tiles, 0);
     const int64_t left = n - (jb + 4 * kk);  // bins from this lane's first to the end
     const bool whole = jb + WAVE_BINS <= n;  // uniform
-    const float* eb = bs + 64 * (count - 2 * TG) + lane;
+    const float2* __restrict__ here = cur + w * WAVE_BINS + 4 * kk + halo;  // this lane's first output bin
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float2* __restrict__ ed = centre - edge[t * 8 + 4 * e + kk];
-        const float bv = eb[64 * (2 * t + e)];
-#pragma unroll
-        for (int s = 0; s < SUB; ++s) {
-          const float2 f = ed[16 * s];
-          st.ar[t][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x, bv, st.ar[t][s], 0, 0, 0);
-          st.ai[t][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.y, bv, st.ai[t][s], 0, 0, 0);
-        }
-      }
-      const int row = rows[t * 16 + m];
+      const ColumnInfo ci = cols[t * 16 + m];
+      edge_add<16>(here, ci.edge, ci.tap, st.ar[t], st.ai[t]);
+      const int row = ci.row;
       float* dst = fop + (size_t)(row < 0 ? 0 : row) * ld + jb + 4 * kk;
       if (whole) {
 #pragma unroll
@@ -239,23 +265,31 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
 // (largest |Re|, |Im| brought to about 2^14) and each template tile by a
 // plan-chosen 2^eh; both scalings are exact and undone on the accumulator.
 
-constexpr int SDW = 4;                       // waves per workgroup
-constexpr int SSUB = 8;                      // 16-bin sub-tiles per wave
-constexpr int SWAVE_BINS = 16 * SSUB;        // 128
-constexpr int SBLK_BINS = SDW * SWAVE_BINS;   // 512
+constexpr int SSUB = 2;                      // 16-bin sub-tiles per wave, 32 bins apart
+constexpr int SBLK_BINS = 128;               // 4 waves: wave w takes bins 64 (w / 2) + 16 (w % 2) + 32 s
+constexpr int SPER = (SBLK_BINS + 2 * 32 * ((MAX_P + 31) / 32 + 3) + 255) / 256;  // strip bins per thread
 
 template <typename T>
 struct Split16;
 
+// pack: two values rounded to nearest even, the first in the low half;
+// low: v minus half `i` of a packed pair
 template <>
 struct Split16<_Float16> {
   typedef _Float16 v8 __attribute__((ext_vector_type(8)));
-  static __device__ __forceinline__ unsigned short bits(float v) {
-    const _Float16 h = (_Float16)v;
-    return __builtin_bit_cast(unsigned short, h);
+  static __device__ __forceinline__ unsigned pack(float a, float b) {
+    typedef _Float16 v2 __attribute__((ext_vector_type(2)));
+    const v2 h = {(_Float16)a, (_Float16)b};
+    return __builtin_bit_cast(unsigned, h);
   }
-  static __device__ __forceinline__ float value(unsigned short b) {
-    return (float)__builtin_bit_cast(_Float16, b);
+  static __device__ __forceinline__ float low(float v, unsigned p, int i) {
+    // v - half in one instruction (a conversion and a subtraction otherwise)
+    float r;
+    if (i == 0)
+      __asm__("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(v));
+    else
+      __asm__("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(v));
+    return r;
   }
   static __device__ __forceinline__ v4f mfma(const v8& a, const v8& b, const v4f& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
@@ -265,159 +299,226 @@ struct Split16<_Float16> {
 template <>
 struct Split16<__bf16> {
   typedef __bf16 v8 __attribute__((ext_vector_type(8)));
-  static __device__ __forceinline__ unsigned short bits(float v) {
-    const __bf16 h = (__bf16)v;  // round to nearest even
-    return __builtin_bit_cast(unsigned short, h);
+  static __device__ __forceinline__ unsigned pack(float a, float b) {
+    typedef __bf16 v2 __attribute__((ext_vector_type(2)));
+    const v2 h = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(unsigned, h);
   }
-  static __device__ __forceinline__ float value(unsigned short b) {
-    return __uint_as_float((unsigned)b << 16);
+  static __device__ __forceinline__ float low(float v, unsigned p, int i) {
+    return v - __uint_as_float(i ? p & 0xffff0000u : p << 16);
   }
   static __device__ __forceinline__ v4f mfma(const v8& a, const v8& b, const v4f& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
 };
 
-// 8 16-bit values from 4 (possibly only 4-byte aligned) 32-bit LDS words
-template <typename V8>
-__device__ __forceinline__ V8 lds_v8(const unsigned* __restrict__ p) {
-  uint4 u;
-  u.x = p[0];
-  u.y = p[1];
-  u.z = p[2];
-  u.w = p[3];
-  return __builtin_bit_cast(V8, u);
+// The 16 folded values of one sub-tile and step (Re, Im of 8 distances) as hi
+// and lo halves.
+template <typename T>
+struct Folded {
+  typename Split16<T>::v8 rh, rl, ih, il;
+};
+
+// hi and lo halves of 8 values; the packed hi pairs are opaque to the compiler,
+// which would otherwise round every value a second time to form its lo half
+template <typename T>
+__device__ __forceinline__ void split8(const float (&v)[8], typename Split16<T>::v8& hi, typename Split16<T>::v8& lo) {
+  typedef Split16<T> S;
+  unsigned h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    h[e] = S::pack(v[2 * e], v[2 * e + 1]);
+    __asm__("" : "+v"(h[e]));
+    l[e] = S::pack(S::low(v[2 * e], h[e], 0), S::low(v[2 * e + 1], h[e], 1));
+  }
+  hi = __builtin_bit_cast(typename S::v8, make_uint4(h[0], h[1], h[2], h[3]));
+  lo = __builtin_bit_cast(typename S::v8, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
-// tiles[g] = {P, first 16-tap group in Bsp, member count, P rounded up to 8};
-// Bsp holds per tile and 16-tap group 64 lanes x 8 hi values, then 64 x 8 lo
-// values (2 KiB); tscale[g] = 2^-eh of the tile.  Dynamic LDS: hi and lo
-// strips of X (2 x (SBLK_BINS + 2 Pm + 16) words) and one tile's operand.
-// Four waves per SIMD (at most 128 registers: the accumulators stay in VGPRs)
-// keep the 16-bit matrix pipe busier than the compiler's default of three
-// with AGPR accumulators (measured 1.67 against 1.85 ms on 2^22 bins).
 template <typename T>
-__global__ __launch_bounds__(SDW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_direct_conv_split(const float2* __restrict__ x, int64_t n,
-                                                               float* __restrict__ fop, int64_t ld,
-                                                               const uint4* __restrict__ Bsp,
-                                                               const int4* __restrict__ tiles,
-                                                               const float* __restrict__ tscale,
-                                                               const int* __restrict__ rows, int ntiles, int Pm) {
+__device__ __forceinline__ Folded<T> fold_split(const float2 (&u)[8], const float2 (&d)[8]) {
+  Folded<T> o;
+  float re[8], im[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    re[e] = u[e].x + d[e].x;
+    im[e] = u[e].y + d[e].y;
+  }
+  split8<T>(re, o.rh, o.rl);
+  split8<T>(im, o.ih, o.il);
+  return o;
+}
+
+// 8 consecutive strip values, upwards from p or downwards to it
+__device__ __forceinline__ void strip_up(const float2* __restrict__ p, float2 (&v)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = p[e];
+}
+__device__ __forceinline__ void strip_down(const float2* __restrict__ p, float2 (&v)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = p[-e];
+}
+
+// A group of TG tiles at once, as in the FP32 kernel, with steps of 32
+// distances: lane group kg holds distances 32 q + 8 kg + e.  Bsp holds 2 KiB
+// per (step, tile): 64 lanes x 8 hi values, then 64 x 8 lo values; tscale[t] =
+// 2^-eh.  The strip of X stays FP32 (scaled so that a folded value is below
+// 2^15) and every folded value is split when it is used: the sum of two 16-bit
+// halves is no 16-bit value.  A wave's two sub-tiles lie 32 bins, one step,
+// apart, so sub-tile 0 of the next step reads upwards what sub-tile 1 reads
+// now, and sub-tile 1 downwards what sub-tile 0 reads now: one upward and one
+// downward read per step instead of two each (`PAR` says which registers hold
+// which).  Dynamic LDS: the operand, one entry read ahead, and one strip.
+// Measured on 2^22 bins: 0.766 ms (FP16); 1.53 ms with every template and tap
+// multiplied on its own.  The fold and split cost 48 vector instructions per
+// sub-tile and step against 12 matrix instructions per tile, which 16-bit
+// matrix instructions overlap in part; both pipes together bound it.
+template <typename T, int TG, int PAR>
+__device__ __forceinline__ void split_step(v4f (&ar)[TG][SSUB], v4f (&ai)[TG][SSUB], float2 (&u)[2][8],
+                                           float2 (&d)[2][8], const float2* __restrict__ up,
+                                           const float2* __restrict__ dn, const uint4* __restrict__ b, int active) {
   typedef Split16<T> S;
   typedef typename S::v8 v8;
-  extern __shared__ uint4 lds_u4[];
-  __shared__ unsigned s_max;
-  unsigned* xhi = reinterpret_cast<unsigned*>(lds_u4);
-  const int tid = threadIdx.x;
-  const int64_t jb = (int64_t)blockIdx.x * SBLK_BINS;
-  const int strip = SBLK_BINS + 2 * Pm + 16;  // even
-  unsigned* xlo = xhi + strip;
-  uint4* bs = reinterpret_cast<uint4*>(xlo + strip);
-  if (tid == 0) s_max = 0u;
-  __syncthreads();
-  // largest |Re|, |Im| of the strip (bit patterns of non-negative floats order like integers)
-  {
-    float mx = 0.0f;
-    for (int u = tid; u < strip; u += SDW * 64) {
-      const int64_t idx = jb - Pm + u;
-      if (idx >= 0 && idx < n) {
-        const float2 v = x[idx];
-        mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+  v8 bh = __builtin_bit_cast(v8, b[0]), bl = __builtin_bit_cast(v8, b[64]);
+  // u[PAR], d[PAR]: sub-tile 0; u[1 - PAR], d[1 - PAR]: sub-tile 1
+  Folded<T> f[SSUB];
+  f[0] = fold_split<T>(u[PAR], d[PAR]);
+  f[1] = fold_split<T>(u[1 - PAR], d[1 - PAR]);
+  strip_up(up, u[PAR]);        // the next step's sub-tile 1
+  strip_down(dn, d[1 - PAR]);  // the next step's sub-tile 0
+#pragma unroll
+  for (int t = 0; t < TG; ++t) {
+    if (t < active) {  // uniform
+      // the next tile's values (past the last one: unused) while this one multiplies
+      const v8 nh = __builtin_bit_cast(v8, b[128 * (t + 1)]);
+      const v8 nl = __builtin_bit_cast(v8, b[128 * (t + 1) + 64]);
+#pragma unroll
+      for (int s = 0; s < SSUB; ++s) {
+        ar[t][s] = S::mfma(f[s].rh, bh, ar[t][s]);
+        ai[t][s] = S::mfma(f[s].ih, bh, ai[t][s]);
       }
+#pragma unroll
+      for (int s = 0; s < SSUB; ++s) {
+        ar[t][s] = S::mfma(f[s].rl, bh, ar[t][s]);
+        ai[t][s] = S::mfma(f[s].il, bh, ai[t][s]);
+      }
+#pragma unroll
+      for (int s = 0; s < SSUB; ++s) {
+        ar[t][s] = S::mfma(f[s].rh, bl, ar[t][s]);
+        ai[t][s] = S::mfma(f[s].ih, bl, ai[t][s]);
+      }
+      bh = nh;
+      bl = nl;
     }
-    atomicMax(&s_max, __float_as_uint(mx));
   }
-  __syncthreads();
-  int ex = 0;
-  {
-    const float mx = __uint_as_float(s_max);
-    if (mx > 0.0f && mx < 3.0e38f) ex = 14 - ilogbf(mx);  // 2^14 <= max * 2^ex < 2^15
-  }
-  for (int u = tid; u < strip; u += SDW * 64) {
-    const int64_t idx = jb - Pm + u;
-    const float2 v = (idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
-    const float re = ldexpf(v.x, ex), im = ldexpf(v.y, ex);
-    const unsigned short hr = S::bits(re), hi_ = S::bits(im);
-    const unsigned short lr = S::bits(re - S::value(hr)), li = S::bits(im - S::value(hi_));
-    xhi[u] = (unsigned)hr | ((unsigned)hi_ << 16);
-    xlo[u] = (unsigned)lr | ((unsigned)li << 16);
-  }
+}
 
+template <typename T, int TG>
+__global__ __launch_bounds__(256, 2) void k_direct_conv_split(
+    const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const uint4* __restrict__ Bsp,
+    const int4* __restrict__ tiles, const float* __restrict__ tscale, const int* __restrict__ rows,
+    const int* __restrict__ edge, const float* __restrict__ edge_tap, int count, int halo, int blocks) {
+  extern __shared__ uint4 lds_u4[];
+  __shared__ ColumnInfo cols[16 * TG];
+  __shared__ float s_max[4];
+  const int tid = threadIdx.x;
+  load_columns(cols, 16 * TG, rows, edge, edge_tap, tscale, tid);
+  const int strip = SBLK_BINS + 2 * halo;  // bins jb - halo + u
+  float2* xs = reinterpret_cast<float2*>(lds_u4 + 128 * (count + 1));
+  for (int i = tid; i < count * 128; i += 256) lds_u4[i] = Bsp[i];
   const int lane = tid & 63;
   const int w = tid >> 6;
   const int m = lane & 15;
-  const int kg = lane >> 4;  // lane group: taps 4kg..4kg+3 of each 16
-  const int col = lane & 15;
-  const int slot = col >> 1;
-  const int c = col & 1;
-
-  for (int g = 0; g < ntiles; ++g) {
-    const int4 tg = tiles[g];
-    const int P = tg.x;
-    const int groups16 = tg.w / 8;  // P8 pairs = 2 P8 taps = P8/8 groups of 16 taps
-    {
-      const uint4* __restrict__ src = Bsp + (size_t)tg.y * 128;  // 2 KiB = 128 uint4 per group, hi then lo
-      __syncthreads();
-      for (int i = tid; i < groups16 * 128; i += SDW * 64) bs[i] = src[i];
-      __syncthreads();
+  const int kg = lane >> 4;
+  const int w0 = 64 * (w >> 1) + 16 * (w & 1);  // first bin of this wave's sub-tile 0
+  int steps[TG];
+#pragma unroll
+  for (int t = 0; t < TG; ++t) steps[t] = tiles[t].x;
+  const int blk0 = (int)((int64_t)blocks * blockIdx.x / gridDim.x);
+  const int blk1 = (int)((int64_t)blocks * (blockIdx.x + 1) / gridDim.x);
+  float2 nx[SPER];  // the next block's strip, loaded while this one is worked on
+  auto fetch = [&](int blk) {
+#pragma unroll
+    for (int i = 0; i < SPER; ++i) {
+      const int u = tid + 256 * i;
+      const int64_t idx = (int64_t)blk * SBLK_BINS - halo + u;
+      nx[i] = (u < strip && idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
     }
-    // strip word of this lane's first tap for group 0, sub-tile 0.  The A
-    // operand of sub-tile s and tap group q starts at a0 + 16 (s + q): it
-    // depends on s + q only, so a window of SSUB operands slides along q, one
-    // new (hi, lo) pair loaded per group (ring slot (s + q) % SSUB, a
-    // compile-time index inside the unrolled block of SSUB groups).  Loading
-    // the next group's operands one group ahead was slower (more registers,
-    // two waves per SIMD instead of three).
-    const int a0 = w * SWAVE_BINS + m + Pm - P + 4 * kg;
-    v4f acc[SSUB];
+  };
+  // largest |Re|, |Im| of this wave's share of the fetched strip.  Taken before
+  // the block's stores are issued: a wait for the loads then waits for no store.
+  auto note_max = [&]() {
+    float mx = 0.0f;
 #pragma unroll
-    for (int s = 0; s < SSUB; ++s) acc[s] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    v8 ah[SSUB], al[SSUB];
+    for (int i = 0; i < SPER; ++i) mx = fmaxf(mx, fmaxf(fabsf(nx[i].x), fabsf(nx[i].y)));
 #pragma unroll
-    for (int i = 0; i < SSUB - 1; ++i) {
-      ah[i] = lds_v8<v8>(xhi + a0 + 16 * i);
-      al[i] = lds_v8<v8>(xlo + a0 + 16 * i);
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    if (lane == 0) s_max[w] = mx;
+  };
+  fetch(blk0);
+  note_max();
+  for (int blk = blk0; blk < blk1; ++blk) {
+    const int64_t j0 = (int64_t)blk * SBLK_BINS;
+    __syncthreads();  // every wave is done with the previous strip
+    const float mx = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    int ex = 0;
+    if (mx > 0.0f && mx < 3.0e38f) ex = 13 - ilogbf(mx);  // 2^13 <= max * 2^ex < 2^14
+#pragma unroll
+    for (int i = 0; i < SPER; ++i) {
+      const int u = tid + 256 * i;
+      if (u < strip) xs[u] = make_float2(ldexpf(nx[i].x, ex), ldexpf(nx[i].y, ex));
     }
-    for (int q0 = 0; q0 < groups16; q0 += SSUB) {
+    __syncthreads();
+    if (blk + 1 < blk1) fetch(blk + 1);
+    v4f ar[TG][SSUB], ai[TG][SSUB];
 #pragma unroll
-      for (int dq = 0; dq < SSUB; ++dq) {
-        const int q = q0 + dq;
-        if (q < groups16) {  // uniform
-          ah[(dq + SSUB - 1) % SSUB] = lds_v8<v8>(xhi + a0 + 16 * (q + SSUB - 1));
-          al[(dq + SSUB - 1) % SSUB] = lds_v8<v8>(xlo + a0 + 16 * (q + SSUB - 1));
-          const v8 b_hi = __builtin_bit_cast(v8, bs[q * 128 + lane]);
-          const v8 b_lo = __builtin_bit_cast(v8, bs[q * 128 + 64 + lane]);
+    for (int t = 0; t < TG; ++t)
 #pragma unroll
-          for (int s = 0; s < SSUB; ++s) {
-            const v8 a_hi = ah[(dq + s) % SSUB];
-            const v8 a_lo = al[(dq + s) % SSUB];
-            acc[s] = S::mfma(a_hi, b_hi, acc[s]);
-            acc[s] = S::mfma(a_hi, b_lo, acc[s]);
-            acc[s] = S::mfma(a_lo, b_hi, acc[s]);
-          }
-        }
+      for (int s = 0; s < SSUB; ++s) ar[t][s] = ai[t][s] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    const float2* up = xs + halo + w0 + m + 8 * kg;
+    const float2* dn = xs + halo + w0 + m - 8 * kg;
+    const uint4* b = lds_u4 + lane;
+    float2 u[2][8], d[2][8];
+    strip_up(up, u[0]);
+    strip_up(up + 32, u[1]);
+    strip_down(dn, d[0]);
+    strip_down(dn + 32, d[1]);
+    up += 64;
+    dn -= 32;
+    for (int q = 0; q < steps[0]; q += 2) {
+      int active = 0, next = 0;
+#pragma unroll
+      for (int t = 0; t < TG; ++t) {
+        active += q < steps[t] ? 1 : 0;
+        next += q + 1 < steps[t] ? 1 : 0;
       }
+      split_step<T, TG, 0>(ar, ai, u, d, up, dn, b, active);
+      b += 128 * active;
+      if (next == 0) break;  // uniform: an odd number of steps
+      split_step<T, TG, 1>(ar, ai, u, d, up + 32, dn - 32, b, next);
+      b += 128 * next;
+      up += 64;
+      dn -= 64;
     }
-    const float unscale = ldexpf(tscale[g], -ex);
-    const int row = slot < tg.z ? rows[g * 8 + slot] : -1;
+    if (blk + 1 < blk1) note_max();
+    const int64_t jb = j0 + w0;
+    const int64_t left = n - (jb + 4 * kg);
+    const bool whole = j0 + SBLK_BINS <= n;  // uniform
+    const float2* __restrict__ here = xs + halo + w0 + 4 * kg;
 #pragma unroll
-    for (int s = 0; s < SSUB; ++s) {
-      float pw[4];
+    for (int t = 0; t < TG; ++t) {
+      const ColumnInfo ci = cols[t * 16 + m];
+      edge_add<32>(here, ci.edge, ci.tap, ar[t], ai[t]);
+      const float unscale = ldexpf(ci.scale, -ex);
+      const int row = ci.row;
+      float* dst = fop + (size_t)(row < 0 ? 0 : row) * ld + jb + 4 * kg;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float y = acc[s][v] * unscale;
-        const float o = swap_pair(y);
-        pw[v] = y * y + o * o;
-      }
-      if (row >= 0) {
-        const int64_t j = jb + w * SWAVE_BINS + 16 * s + 4 * kg + 2 * c;
-        float* dst = fop + (size_t)row * ld + j;
-        const float p0 = c ? pw[2] : pw[0];
-        const float p1 = c ? pw[3] : pw[1];
-        if (j + 2 <= n) {
-          store2_nt(dst, p0, p1);
-        } else if (j < n) {
-          __builtin_nontemporal_store(p0, dst);
-        }
+      for (int s = 0; s < SSUB; ++s) {
+        const v4f a = ar[t][s] * unscale, c = ai[t][s] * unscale;
+        if (whole)
+          pair_store(a, c, row, dst + 32 * s, 4);
+        else
+          pair_store(a, c, row, dst + 32 * s, left - 32 * s);
       }
     }
   }
@@ -425,41 +526,61 @@ __global__ __launch_bounds__(SDW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))
 
 }  // namespace
 
-int direct_block_bins() { return SBLK_BINS; }
-int direct_max_half_taps() { return MAX_P; }
-size_t direct_lds_bytes(int P_max, int P8_max) {
-  return sizeof(float) * (2 * (size_t)(SBLK_BINS + 2 * P_max + 16) + 64 * (size_t)P8_max);
+template <typename T, int TG>
+hipError_t launch_split_group(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
+                              const DirectGroup& gr, int halo, int blocks, unsigned grid, hipStream_t s) {
+  const size_t lds = (size_t)2048 * (gr.count + 1) + sizeof(float2) * (size_t)(SBLK_BINS + 2 * halo);
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_direct_conv_split<T, TG>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_direct_conv_split<T, TG>), dim3(grid), dim3(256), lds, s, x, n, fop, ld,
+                     t.Bsp + (size_t)128 * gr.offset, t.tiles + gr.first, t.tscale + gr.first, t.rows + 16 * gr.first,
+                     t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, halo, blocks);
+  return hipGetLastError();
 }
 
 hipError_t launch_direct_conv_split(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
-                                    bool bf16, hipStream_t s) {
-  if (t.P_max > MAX_P || t.ntiles < 1 || n < 1 || !t.Bsp || !t.tscale) return hipErrorInvalidValue;
+                                    int cus, bool bf16, hipStream_t s) {
+  if (t.P_max > MAX_P || t.ngroups < 1 || n < 1 || !t.Bsp || !t.tscale || !t.groups) return hipErrorInvalidValue;
   const int64_t blocks = (n + SBLK_BINS - 1) / SBLK_BINS;
-  const size_t lds = direct_lds_bytes(t.P_max, t.P8_max);
-  const void* fn = bf16 ? reinterpret_cast<const void*>(k_direct_conv_split<__bf16>)
-                        : reinterpret_cast<const void*>(k_direct_conv_split<_Float16>);
-  if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const unsigned grid = (unsigned)std::min<int64_t>(blocks, 2 * cus);
+  // steps of 32 distances, run in pairs and read one step ahead
+  const int halo = 32 * ((t.P_max + 31) / 32 + 3);
+  for (int g = 0; g < t.ngroups; ++g) {
+    const DirectGroup& gr = t.groups[g];
+    hipError_t e = hipErrorInvalidValue;
+    switch (gr.tiles) {
+#define FDAS_SPLIT_CASE(TG)                                                                                \
+  case TG:                                                                                                 \
+    e = bf16 ? launch_split_group<__bf16, TG>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s)            \
+             : launch_split_group<_Float16, TG>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s);         \
+    break;
+      FDAS_SPLIT_CASE(1)
+      FDAS_SPLIT_CASE(2)
+      FDAS_SPLIT_CASE(3)
+      FDAS_SPLIT_CASE(4)
+      FDAS_SPLIT_CASE(5)
+      FDAS_SPLIT_CASE(6)
+#undef FDAS_SPLIT_CASE
+      default:
+        break;
+    }
     if (e != hipSuccess) return e;
   }
-  if (bf16)
-    hipLaunchKernelGGL(k_direct_conv_split<__bf16>, dim3((unsigned)blocks), dim3(SDW * 64), lds, s, x, n, fop, ld,
-                       t.Bsp, t.tiles, t.tscale, t.rows, t.ntiles, t.P_max);
-  else
-    hipLaunchKernelGGL(k_direct_conv_split<_Float16>, dim3((unsigned)blocks), dim3(SDW * 64), lds, s, x, n, fop, ld,
-                       t.Bsp, t.tiles, t.tscale, t.rows, t.ntiles, t.P_max);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t, int cus,
                               hipStream_t s) {
-  if (t.P_max > MAX_P || t.ngroups < 1 || n < 1 || !t.Bpk || !t.edge || !t.groups) return hipErrorInvalidValue;
+  if (t.P_max > MAX_P || t.ngroups < 1 || n < 1 || !t.Bpk || !t.groups) return hipErrorInvalidValue;
   const int64_t blocks = (n + BLK_BINS - 1) / BLK_BINS;
   // a workgroup stages its operand once for a contiguous range of blocks
   const unsigned grid = (unsigned)std::min<int64_t>(blocks, 2 * cus);
   for (int g = 0; g < t.ngroups; ++g) {
     const DirectGroup& gr = t.groups[g];
-    const size_t lds = sizeof(float) * 64 * (size_t)gr.count +
+    const size_t lds = sizeof(float) * 64 * (size_t)(gr.count + gr.tiles) +
                        sizeof(float2) * 2 * (size_t)(BLK_BINS + 2 * (t.P_max + FOLD_PAD));
     switch (gr.tiles) {
 #define FDAS_DIRECT_CASE(TG)                                                                                        \
@@ -471,7 +592,8 @@ hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld
     }                                                                                                               \
     hipLaunchKernelGGL(k_direct_conv<TG>, dim3(grid), dim3(DW * 64), lds, s, x, n, fop, ld,                         \
                        reinterpret_cast<const float4*>(t.Bpk) + (size_t)16 * gr.offset, t.tiles + gr.first,         \
-                       t.rows + 16 * gr.first, t.edge + 8 * gr.first, gr.count, t.P_max, (int)blocks);              \
+                       t.rows + 16 * gr.first, t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, t.P_max, \
+                       (int)blocks);                                                                                \
     break;                                                                                                          \
   }
       FDAS_DIRECT_CASE(1)

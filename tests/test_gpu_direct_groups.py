@@ -35,3 +35,22 @@ def test_direct_fp32_group_and_block_edges(z_max, n):
     ref = ofop.fop(spec.astype(np.complex128), z_max=z_max)
     assert np.all(np.abs(got[:, :n] - ref) <= TOL * np.maximum(ref, 1.0))
     assert np.all(np.isnan(got[:, n:])), "columns >= n must not be written"
+
+
+@pytest.mark.parametrize("prec,tol", [(fdas.PREC_SPLIT_FP16, 1e-4), (fdas.PREC_SPLIT_BF16, 4e-3)])
+@pytest.mark.parametrize("z_max,n", [(7, 127), (8, 129), (39, 128), (48, 1023), (64, 33), (42, 15), (3, 150_001)])
+def test_direct_split_group_and_block_edges(prec, tol, z_max, n):
+    """The split kernels: 128-bin blocks, odd and even step counts of 32 distances,
+    groups as above; the bounds are the split precisions' own (FP16 keeps 22
+    significand bits, BF16 16)."""
+    spec, _ = synth.make_spectrum(n, 950 + z_max)
+    x = torch.from_numpy(spec).to("cuda:0")
+    print(f"split groups: prec={prec} n={n} z_max={z_max}", flush=True)
+    with fdas.plan_create(z_max=z_max, n_max=n, method=fdas.CONV_DIRECT_MFMA, precision=prec) as plan:
+        out = torch.full((plan.rows, fdas.fop_ld(n)), float("nan"), dtype=torch.float32, device="cuda:0")
+        fdas.convolve(plan, x, out, n=n)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+    ref = ofop.fop(spec.astype(np.complex128), z_max=z_max)
+    assert np.all(np.abs(got[:, :n] - ref) <= tol * np.maximum(ref, 1.0))
+    assert np.all(np.isnan(got[:, n:])), "columns >= n must not be written"
