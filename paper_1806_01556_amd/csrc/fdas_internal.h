@@ -236,19 +236,30 @@ struct PsBuffers {
   float* m;              // Adam moments
   float* v;
   unsigned short* wbf;   // BF16 copy used by the kernels
-  unsigned short* wflip; // [32][32][9] transposed, flipped kernel of one layer
   unsigned short* wpack; // layers 1..3 as matrix-core A operands (kPsPackShorts)
-  float *a1, *a2, *a3, *r4;               // activations [B][32][1024 / 256 / 64 / 64]
-  unsigned char *arg1, *arg2, *arg3;      // max-pool positions
-  float *dz1, *dz2, *dz3, *dz4;           // pre-activation gradients [B][32][4096 / 1024 / 256 / 64]
+  float* wtrain;         // the same layers as the training kernels' operands (ps_operand_floats)
+  float *a1, *a2, *a3;                        // pooled activations [B][32][1024 / 256 / 64]
+  unsigned char *arg1, *arg2, *arg3, *arg4;   // max-pool positions, as a1..a3; [B][32] for the last maximum
+  float *g1, *g2, *g3, *g4;                   // gradients of the pooled values, as arg1..arg4
+  float *h, *dlogit, *lossb;                  // [B][32] channel maxima, [B] logit gradients, [B] losses
+  float* part;                                // partial weight gradients (ps_partial_floats)
 };
 int ps_param_count();
 constexpr int kPsPackShorts = 3 * 2 * 9 * 64 * 8;
 // features of listed 4096-bin blocks: log(1 + |X|^2)
 hipError_t ps_features(const float2* x, int64_t n, const int* blocks, int nb, float* out, hipStream_t s);
-// forward (logits); with labels also the loss (atomically added, mean) and the gradient into pb.grad
-hipError_t ps_forward_backward(const PsBuffers& pb, const float* feats, int nb, const float* labels, float pos_weight,
-                               float* logits, float* loss, hipStream_t s);
+// parameter offsets: weights and biases of layer l = 0..3, the head
+int ps_off_w(int l);
+int ps_off_b(int l);
+int ps_off_fc();
+size_t ps_operand_floats();
+size_t ps_partial_floats();
+hipError_t ps_operands(const PsBuffers& pb, hipStream_t s);  // wbf -> wtrain
+// logits of nb feature blocks
+hipError_t ps_forward(const PsBuffers& pb, const float* feats, int nb, float* logits, hipStream_t s);
+// logits, mean loss, and the mean gradient into pb.grad (and grad2 unless NULL)
+hipError_t ps_gradient(const PsBuffers& pb, const float* feats, int nb, const float* labels, float pos_weight,
+                       float* logits, float* loss, float* grad2, hipStream_t s);
 // logits of blocks 0..nb-1 of an n-bin spectrum, the features computed in the inference kernel
 hipError_t ps_infer_spectrum(const PsBuffers& pb, const float2* x, int64_t n, int nb, float* logits, hipStream_t s);
 hipError_t ps_adam(const PsBuffers& pb, float lr, float b1, float b2, float c1, float c2, float eps, hipStream_t s);

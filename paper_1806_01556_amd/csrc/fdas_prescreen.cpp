@@ -81,14 +81,16 @@ fdas_status fdas_prescreen_create(int32_t device, int32_t max_batch, fdas_prescr
   PsBuffers& b = ps->pb;
   if ((e = alloc(ps, &b.theta, np)) != hipSuccess || (e = alloc(ps, &b.grad, np)) != hipSuccess ||
       (e = alloc(ps, &b.m, np)) != hipSuccess || (e = alloc(ps, &b.v, np)) != hipSuccess ||
-      (e = alloc(ps, &b.wbf, np)) != hipSuccess || (e = alloc(ps, &b.wflip, C * C * 9)) != hipSuccess ||
-      (e = alloc(ps, &b.wpack, kPsPackShorts)) != hipSuccess ||
+      (e = alloc(ps, &b.wbf, np)) != hipSuccess || (e = alloc(ps, &b.wpack, kPsPackShorts)) != hipSuccess ||
+      (e = alloc(ps, &b.wtrain, ps_operand_floats())) != hipSuccess ||
       (e = alloc(ps, &b.a1, B * C * 1024)) != hipSuccess || (e = alloc(ps, &b.a2, B * C * 256)) != hipSuccess ||
-      (e = alloc(ps, &b.a3, B * C * 64)) != hipSuccess || (e = alloc(ps, &b.r4, B * C * 64)) != hipSuccess ||
-      (e = alloc(ps, &b.arg1, B * C * 1024)) != hipSuccess || (e = alloc(ps, &b.arg2, B * C * 256)) != hipSuccess ||
-      (e = alloc(ps, &b.arg3, B * C * 64)) != hipSuccess || (e = alloc(ps, &b.dz1, B * C * 4096)) != hipSuccess ||
-      (e = alloc(ps, &b.dz2, B * C * 1024)) != hipSuccess || (e = alloc(ps, &b.dz3, B * C * 256)) != hipSuccess ||
-      (e = alloc(ps, &b.dz4, B * C * 64)) != hipSuccess) {
+      (e = alloc(ps, &b.a3, B * C * 64)) != hipSuccess || (e = alloc(ps, &b.arg1, B * C * 1024)) != hipSuccess ||
+      (e = alloc(ps, &b.arg2, B * C * 256)) != hipSuccess || (e = alloc(ps, &b.arg3, B * C * 64)) != hipSuccess ||
+      (e = alloc(ps, &b.arg4, B * C)) != hipSuccess || (e = alloc(ps, &b.g1, B * C * 1024)) != hipSuccess ||
+      (e = alloc(ps, &b.g2, B * C * 256)) != hipSuccess || (e = alloc(ps, &b.g3, B * C * 64)) != hipSuccess ||
+      (e = alloc(ps, &b.g4, B * C)) != hipSuccess || (e = alloc(ps, &b.h, B * C)) != hipSuccess ||
+      (e = alloc(ps, &b.dlogit, B)) != hipSuccess || (e = alloc(ps, &b.lossb, B)) != hipSuccess ||
+      (e = alloc(ps, &b.part, ps_partial_floats())) != hipSuccess) {
     free_ps(ps);
     return hip_fail(e, "allocating the pre-screen workspace");
   }
@@ -179,8 +181,7 @@ fdas_status fdas_prescreen_forward(fdas_prescreen* ps, const float* d_features, 
   if (st != FDAS_OK) return st;
   if (!d_features || !d_logits) return fail(FDAS_ERR_INVALID_ARG, "NULL buffer");
   DeviceGuard dg(ps->device);
-  hipError_t e = ps_forward_backward(ps->pb, d_features, nblocks, nullptr, 1.0f, d_logits, nullptr,
-                                     static_cast<hipStream_t>(stream));
+  hipError_t e = ps_forward(ps->pb, d_features, nblocks, d_logits, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "pre-screen forward");
   return ok();
 }
@@ -211,13 +212,8 @@ fdas_status fdas_prescreen_gradient(fdas_prescreen* ps, const float* d_features,
   if (!d_features || !d_labels || !d_logits || !d_loss) return fail(FDAS_ERR_INVALID_ARG, "NULL buffer");
   if (!(pos_weight > 0.0f)) return fail(FDAS_ERR_INVALID_ARG, "pos_weight must be > 0");
   DeviceGuard dg(ps->device);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const int np = ps_param_count();
-  hipError_t e = ps_zero(ps->pb.grad, np, s);
-  if (e == hipSuccess) e = ps_zero(d_loss, 1, s);
-  if (e == hipSuccess) e = ps_forward_backward(ps->pb, d_features, nblocks, d_labels, pos_weight, d_logits, d_loss, s);
-  if (e == hipSuccess && d_grad)
-    e = hipMemcpyAsync(d_grad, ps->pb.grad, np * sizeof(float), hipMemcpyDeviceToDevice, s);
+  hipError_t e = ps_gradient(ps->pb, d_features, nblocks, d_labels, pos_weight, d_logits, d_loss, d_grad,
+                             static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "pre-screen gradient");
   return ok();
 }
