@@ -158,7 +158,7 @@ fdas_status fdas_harmonic_sum(fdas_plan* plan, const float* d_fop, int64_t n, in
  * under HIP graph capture, tight serving loops and harnesses that forbid
  * hipMalloc.  Same arguments, kernels and results as fdas_harmonic_sum; it
  * calls no allocating routine.  Its scratch (hit-row counter, tile order and
- * hit-row list, 16.02 MiB) is a static device array of the library, one per
+ * hit-row list, 16.2 MiB) is a static device array of the library, one per
  * GPU, held until the process ends; calls that overlap on one GPU share it
  * and race, so they must be ordered (one stream, or events).  The array keeps
  * the last call's contents; every call clears the counter and rewrites the

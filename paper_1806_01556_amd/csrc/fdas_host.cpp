@@ -167,7 +167,10 @@ hipError_t tile_order_for(fdas_plan* p, int64_t n, const int** d_order, int* blo
   auto it = p->tile_orders.find(key);
   if (it == p->tile_orders.end()) {
     std::vector<int> order;
-    harmsum_tile_order(n, order, cols);
+    if (cols == kStrideHigh)  // the highest-anchored map's own tiles
+      harmsum_high_order(n, order);
+    else
+      harmsum_tile_order(n, order, cols);
     int* d = nullptr;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), order.size() * sizeof(int));
     if (e == hipSuccess) e = hipMemcpy(d, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice);
@@ -348,7 +351,7 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
         (e = hipMalloc(&p->d_sort_hist, 256 * tiles * sizeof(int))) != hipSuccess ||
         (e = hipMalloc(&p->d_sort_totals, 256 * passes * sizeof(int))) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 8 * sizeof(int32_t), 0)) != hipSuccess ||
-        (e = hipMalloc(&p->d_hitrows, (size_t)((desc->n_max + 3) / 4) * sizeof(int4))) != hipSuccess ||
+        (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max) * sizeof(int4))) != hipSuccess ||
         (e = hipMalloc(&p->d_hitrow_count, sizeof(int32_t))) != hipSuccess) {
       free_plan(p);
       return hip_fail(e, "allocating the candidate sort workspace");
@@ -408,15 +411,18 @@ fdas_status fdas_harmonic_sum(fdas_plan* p, const float* d_fop, int64_t n, int64
   DeviceGuard dg(p->device);
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // workgroup -> column-tile order of the 85-row kernel, built once per spectrum length
+  // workgroup -> column-tile order, built once per spectrum length
   const int* d_order = nullptr;
   int order_blocks = 0;
   {
-    hipError_t e0 = fdas::tile_order_for(p, n, &d_order, &order_blocks);
+    hipError_t e0 = fdas::tile_order_for(p, n, &d_order, &order_blocks,
+                                         p->desc.hsum_index == FDAS_HSUM_HIGHEST ? fdas::kStrideHigh
+                                                                                 : fdas::harmsum_tile_columns());
     if (e0 != hipSuccess) return hip_fail(e0, "uploading the harmonic-sum tile order");
   }
   hipError_t e;
-  fdas::HsWork wk{d_order, order_blocks, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups};
+  fdas::HsWork wk{d_order, order_blocks, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups,
+                  (int)fdas::harmsum_hit_entries(p->desc.n_max)};
   e = fdas::launch_harmsum(d_fop, n, ld, p->desc.z_max, p->desc.n_harm, d_ta ? d_ta : p->d_ta, d_cands,
                            p->desc.cand_capacity, d_counts, wk, p->desc.hsum_index, s);
   if (e != hipSuccess) return hip_fail(e, "launching the harmonic sum");

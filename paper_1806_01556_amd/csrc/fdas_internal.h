@@ -131,6 +131,16 @@ int harmsum_tile_columns();
 // Order in which the 85-row harmonic-sum kernel visits its column tiles of
 // `cols` columns: tile_of_block[b] is the tile of workgroup b (-1: none).
 void harmsum_tile_order(int64_t n, std::vector<int>& tile_of_block, int cols);
+// Tiles of the highest-anchored kernel (256 groups of four columns 840 apart, 840
+// groups to 3360 columns) and their order: chunks of 8 consecutive tiles in the
+// octave order, a chunk's tiles one after another on one XCD (neighbours share
+// the cache lines at their edges), eight chunks at a time over the XCDs.
+constexpr int kStrideHigh = 840;
+constexpr int kHighChunk = 8;
+inline int64_t harmsum_high_tiles(int64_t n) {
+  return ((n + 4 * kStrideHigh - 1) / (4 * kStrideHigh) * kStrideHigh + 255) / 256;
+}
+void harmsum_high_order(int64_t n, std::vector<int>& tile_of_block);
 // Tile widths (columns) the 85-row batch harmonic sum is built for: 256, 512, 1024.
 bool harmsum_tile_built(int cols);
 
@@ -138,10 +148,14 @@ bool harmsum_tile_built(int cols);
 struct HsWork {
   const int* tile_of_block;  // workgroup -> column tile (-1: none)
   int blocks;                // workgroups of phase 1
-  int4* hitrows;             // {j0, row mask words}: ceil(n/4) entries at most
+  int4* hitrows;             // {first column, row mask words}
   int32_t* hitrow_count;     // entries appended by phase 1
   int emit_blocks;           // workgroups of phase 2 (0: default)
+  int hit_cap;               // entries the list holds, at least harmsum_hit_entries of the plan's n_max
 };
+// Hit-row entries a plan for spectra of up to n_max bins needs: one per thread
+// of phase 1, row segments of short spectra included.
+int64_t harmsum_hit_entries(int64_t n_max);
 
 // One spectrum of a batch for the harmonic sum (device table entry).
 struct HsTrial {

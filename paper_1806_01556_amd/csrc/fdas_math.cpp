@@ -359,10 +359,9 @@ void stretch_source_rows(int Z, int nh, int* lo, int* hi) {
 // 8t(+7) next to each other, so a tile's k = 2, 4, 8 sources were read moments
 // before.  The sorted list is split into 8 contiguous segments, one per XCD
 // (workgroup b runs on XCD b mod 8), so a chain also shares one L2.
-void harmsum_tile_order(int64_t n, std::vector<int>& tile_of_block, int cols) {
-  const int T = (int)((n + cols - 1) / cols);
+static std::vector<int> octave_order(int T) {
   int top = 0;
-  while ((1LL << (top + 1)) <= (int64_t)std::max(1, T - 1)) ++top;  // octave of the largest tile index
+  while ((1LL << (top + 1)) <= (int64_t)std::max(1, T - 1)) ++top;  // octave of the largest index
   std::vector<std::pair<uint64_t, int>> key(T);
   for (int t = 0; t < T; ++t) {
     if (t == 0) {
@@ -375,14 +374,34 @@ void harmsum_tile_order(int64_t n, std::vector<int>& tile_of_block, int cols) {
     key[t] = {(frac << 6) | (uint64_t)(o + 1), t};
   }
   std::sort(key.begin(), key.end());
+  std::vector<int> order(T);
+  for (int q = 0; q < T; ++q) order[q] = key[q].second;
+  return order;
+}
+
+void harmsum_tile_order(int64_t n, std::vector<int>& tile_of_block, int cols) {
+  const int T = (int)((n + cols - 1) / cols);
+  const std::vector<int> order = octave_order(T);
   const int xcd = 8;
   const int per = (T + xcd - 1) / xcd;
   tile_of_block.assign((size_t)per * xcd, -1);
   for (int b = 0; b < per * xcd; ++b) {
     const int seg = b % xcd, q = b / xcd;
     const int idx = seg * per + q;
-    if (q < per && idx < T) tile_of_block[b] = key[idx].second;
+    if (q < per && idx < T) tile_of_block[b] = order[idx];
   }
+}
+
+void harmsum_high_order(int64_t n, std::vector<int>& tile_of_block) {
+  const int T = (int)harmsum_high_tiles(n), xcd = 8, ch = kHighChunk;
+  const std::vector<int> order = octave_order((T + ch - 1) / ch);
+  const int nch = (int)order.size(), rounds = (nch + xcd - 1) / xcd;
+  tile_of_block.assign((size_t)rounds * xcd * ch, -1);
+  for (int q = 0; q < nch; ++q)
+    for (int e = 0; e < ch; ++e) {
+      const int t = order[q] * ch + e;
+      if (t < T) tile_of_block[(size_t)((q / xcd) * ch + e) * xcd + q % xcd] = t;
+    }
 }
 
 }  // namespace fdas

@@ -13,6 +13,8 @@
 // (floor(j/k) spans <= 2 values).  The kernels of the other index maps
 // interleave a thread's columns across the wave instead (see there).
 
+#include <algorithm>
+
 #include "fdas_internal.h"
 
 namespace fdas {
@@ -20,33 +22,94 @@ namespace {
 
 constexpr int HS_THREADS = 256;
 
-// Appends one record to list k.  A plan keeps (2 z_max + 1) n_max below 2^31,
-// so a count cannot wrap; the unsigned compare still keeps any slot that is
-// not in [0, cap) from being written.
-__device__ __forceinline__ void emit(int k, int i, int j, float p, fdas_cand* __restrict__ cands, int cap,
-                                     int32_t* __restrict__ counts) {
-  const int slot = atomicAdd(&counts[k - 1], 1);
-  if ((unsigned)slot < (unsigned)cap) {
-    int4 rec = make_int4(k, i, j, __float_as_int(p));
-    *reinterpret_cast<int4*>(cands + (size_t)(k - 1) * cap + slot) = rec;
+// ---------------------------------------------------------------------------
+// Any row count, and the two other index maps (plan option hsum_index).  A
+// pulsar whose fundamental sits at (z, r) has its m-th harmonic at (m z, m r).
+//
+// All three work in two phases, as the 85-row kernel below does.  Phase 1 gives
+// a thread four columns and a segment of the rows, and only notes which rows
+// hold a cell above threshold: the maximum of a row's four sums is compared once
+// per plane, and one bit per row is kept.  Phase 2 (k_emit_map) gives every
+// noted (columns, row) to a lane, forms its sums again from memory in the same
+// order and appends the candidates.  Appending inside phase 1 made a row cost
+// some 20 vector instructions per plane whether it had a hit or not, and left a
+// tile near a strong pulsar waiting for 85 rows of atomics one after another:
+// 244 us for the fundamental-anchored sum of 20,003 bins, 0.93 ms of 2^22.
+//
+// The row segments (blockIdx.y) fill the chip where the columns alone do not:
+// 256 columns make a wave, so n below about 3072 waves x 256 = 786,432 bins is
+// split, up to 8 ways.  A launch covers at most 96 rows (the bits of an entry).
+
+constexpr int XT = 4 * HS_THREADS;
+constexpr int kRowsPerPass = 96;
+constexpr int kSplitBins = 786432;
+constexpr int kMaxSegs = 8;
+// entries past ceil(n / 4): the last tile's or block's threads hold fewer than four columns each
+constexpr int kHitSlack = kMaxSegs * 1024;
+
+// Columns of a thread's group: c0 + STRIDE a, a = 0..3.
+constexpr int kStrideFund = HS_THREADS;  // a wave's load covers 64 columns at stride m
+// 840 = lcm(1..8): rho(p (j + 840 a), q) = rho(p j, q) + 840 a p / q, so the
+// four columns' source offsets differ by constants and one offset per fraction
+// serves them (kStrideHigh)
+static_assert(kStrideHigh == 840 && HS_THREADS == 256, "harmsum_high_tiles counts 256 groups of 840 to a block");
+
+// rows [r0, r1) of this block: segment blockIdx.y of the launch's [rbase, rend)
+__device__ __forceinline__ void row_segment(int rbase, int rend, int& r0, int& r1) {
+  const int len = rend - rbase;
+  r0 = rbase + (int)((int64_t)len * blockIdx.y / gridDim.y);
+  r1 = rbase + (int)((int64_t)len * (blockIdx.y + 1) / gridDim.y);
+}
+
+struct RowMask {
+  unsigned w[3] = {0u, 0u, 0u};
+  // bit is uniform: the branches are scalar
+  __device__ __forceinline__ void note(bool hit, int bit) {
+    const unsigned v = hit ? 1u << (bit & 31) : 0u;
+    if (bit < 32)
+      w[0] |= v;
+    else if (bit < 64)
+      w[1] |= v;
+    else
+      w[2] |= v;
+  }
+};
+
+// Append {c0, mask} of the threads with hits to the list (at most `cap` entries;
+// the launch has checked that every thread's would fit).
+__device__ __forceinline__ void flush_mask(const RowMask& mk, int c0, int4* __restrict__ hitrows, int cap,
+                                           int32_t* __restrict__ hit_count) {
+  const bool any = (mk.w[0] | mk.w[1] | mk.w[2]) != 0u;
+  const unsigned long long b = __ballot(any);
+  if (b == 0ull) return;  // uniform
+  const int lead = (int)__builtin_ctzll(b);
+  int base = 0;
+  if ((int)(threadIdx.x & 63) == lead) base = atomicAdd(hit_count, __popcll(b));
+  base = __shfl(base, lead);
+  if (any) {
+    const int pos =
+        base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
+    if ((unsigned)pos < (unsigned)cap) hitrows[pos] = make_int4(c0, (int)mk.w[0], (int)mk.w[1], (int)mk.w[2]);
   }
 }
 
-// ---------------------------------------------------------------------------
-// Generic path (any row count): runtime row loop; a source value of harmonic k
-// is fetched once per change of trunc(i/k) and kept across the k rows sharing it.
-template <int NH>
-__global__ __launch_bounds__(HS_THREADS) void k_harmsum(const float* __restrict__ fop, int64_t ld, int n,
-                                                        int z_max, const float* __restrict__ ta,
-                                                        fdas_cand* __restrict__ cands, int cap,
-                                                        int32_t* __restrict__ counts) {
-  const int64_t g = (int64_t)blockIdx.x * HS_THREADS + threadIdx.x;
-  const int64_t j0l = g * 4;
-  if (j0l >= n) return;
-  const int j0 = (int)j0l;
-  const bool full = j0 + 4 <= n;
-  const int rows = 2 * z_max + 1;
+__device__ __forceinline__ float max4(const float (&v)[4]) { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); }
 
+// Stretch map, any row count: four adjacent columns; a source value of harmonic
+// k is fetched once per change of trunc(i/k) and kept across the k rows sharing
+// it.
+template <int NH>
+__global__ __launch_bounds__(HS_THREADS) void k_detect_stretch(const float* __restrict__ fop, int64_t ld, int n,
+                                                               int z_max, int rbase, int rend,
+                                                               const int* __restrict__,
+                                                               const float* __restrict__ ta,
+                                                               int4* __restrict__ hitrows, int hit_cap,
+                                                               int32_t* __restrict__ hit_count) {
+  const int64_t g = (int64_t)blockIdx.x * HS_THREADS + threadIdx.x;
+  const int rows = 2 * z_max + 1;
+  int r0, r1;
+  row_segment(rbase, rend, r0, r1);
+  const int j0 = (int)min((int64_t)n - 1, g * 4) / 4 * 4;
   int lo[NH + 1], hi[NH + 1];
   bool selhi[NH + 1][4];
 #pragma unroll
@@ -57,174 +120,138 @@ __global__ __launch_bounds__(HS_THREADS) void k_harmsum(const float* __restrict_
     for (int a = 0; a < 4; ++a) selhi[m][a] = ((j0 + a) / m) != lo[m];
   }
   float cache[NH + 1][4];
-#pragma unroll
-  for (int m = 0; m <= NH; ++m)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) cache[m][a] = 0.0f;
-
-  for (int r = 0; r < rows; ++r) {
+  RowMask mk;
+  for (int r = r0; r < r1; ++r) {
     const int i = r - z_max;
-    const float* row = fop + (size_t)r * ld;
-    float hp[4];
-    if (full) {
-      const float4 q = *reinterpret_cast<const float4*>(row + j0);
-      hp[0] = q.x;
-      hp[1] = q.y;
-      hp[2] = q.z;
-      hp[3] = q.w;
-    } else {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) hp[a] = (j0 + a < n) ? row[j0 + a] : 0.0f;
-    }
-    {
-      const float t = ta[r];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        if (hp[a] > t && j0 + a < n) emit(1, i, j0 + a, hp[a], cands, cap, counts);
-    }
+    // ld >= n and ld % 4 == 0: the last group's read stays inside the row, and
+    // phase 2 does not emit columns past n - 1
+    const float4 q = *reinterpret_cast<const float4*>(fop + (size_t)r * ld + j0);
+    float hp[4] = {q.x, q.y, q.z, q.w};
+    bool hit = max4(hp) > ta[r];
 #pragma unroll
     for (int m = 2; m <= NH; ++m) {
       const int si = i / m;  // C division: truncation toward zero
-      if (r == 0 || si != (i - 1) / m) {
+      if (r == r0 || si != (i - 1) / m) {
         const float* src = fop + (size_t)(si + z_max) * ld;
         const float vl = src[lo[m]];
         const float vh = src[hi[m]];
 #pragma unroll
         for (int a = 0; a < 4; ++a) cache[m][a] = selhi[m][a] ? vh : vl;
       }
-      const float t = ta[(m - 1) * rows + r];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        hp[a] = hp[a] + cache[m][a];
-        if (hp[a] > t && j0 + a < n) emit(m, i, j0 + a, hp[a], cands, cap, counts);
-      }
+      for (int a = 0; a < 4; ++a) hp[a] = hp[a] + cache[m][a];
+      hit = hit || max4(hp) > ta[(m - 1) * rows + r];
     }
+    mk.note(hit, r - rbase);
   }
-}
-
-// ---------------------------------------------------------------------------
-// Alternative index maps (plan option hsum_index), any row count.  A pulsar
-// whose fundamental sits at (z, r) has its m-th harmonic at (m z, m r).
-//
-// Both kernels take a column tile of XT = 4 * HS_THREADS columns per
-// workgroup (tile from tile_of_block when given, else blockIdx.x) and give
-// thread t the columns tile * XT + t + HS_THREADS * a, a = 0..3, so that a
-// wave's load of one source row covers 64 consecutive output columns: 64
-// consecutive source columns for the fundamental, 64 at stride m for FOP(k i,
-// k j), 64 nearly consecutive ones (stretch factor <= 1) for rho(m j, k).
-// Candidates are appended with one atomic per wave and plane (hits are rare;
-// a dense plane still costs one reservation per wave).
-
-constexpr int XT = 4 * HS_THREADS;
-
-// Lane offsets inside the wave from ballots of each lane's 3-bit hit count;
-// the lowest active lane reserves the wave's slots in list m.  Every lane of
-// the wave calls this with the same m (the caller is wave-uniform).
-__device__ __forceinline__ void wave_append(int m, int i, const int (&col)[4], const float (&v)[4], unsigned bits,
-                                            fdas_cand* __restrict__ cands, int cap, int32_t* __restrict__ counts) {
-  const int c = __popc(bits);
-  const unsigned long long b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
-  const int total = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-  if (total == 0) return;  // uniform
-  auto below = [](unsigned long long b) {
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
-  };
-  const int mine = below(b0) + 2 * below(b1) + 4 * below(b2);
-  const unsigned long long act = __ballot(1);
-  const int lead = (int)__builtin_ctzll(act);
-  int base = 0;
-  if ((int)(threadIdx.x & 63) == lead) base = atomicAdd(&counts[m - 1], total);
-  int slot = __shfl(base, lead) + mine;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    if ((bits >> a) & 1u) {
-      if ((unsigned)slot < (unsigned)cap)
-        *reinterpret_cast<int4*>(cands + (size_t)(m - 1) * cap + slot) = make_int4(m, i, col[a], __float_as_int(v[a]));
-      ++slot;
-    }
-  }
-}
-
-// Tile of this workgroup (-1: none) and the thread's four columns.
-__device__ __forceinline__ int xt_tile(const int* __restrict__ tile_of_block, int n) {
-  const int tile = tile_of_block ? tile_of_block[blockIdx.x] : (int)blockIdx.x;
-  return (tile >= 0 && (int64_t)tile * XT < n) ? tile : -1;
+  if (g * 4 >= n) mk = RowMask();
+  flush_mask(mk, j0, hitrows, hit_cap, hit_count);
 }
 
 // Raw buffer resource over part of one FOP row: loads at byte offsets >=
 // bytes read 0 (the hardware range check), so columns past n - 1 need no
 // compare.  The resource starts at the first column a workgroup reads, so
-// offsets stay below 32 KB whatever n is.
+// offsets stay below 64 KB whatever n is.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const float* base, int64_t cols_left) {
   const uint32_t bytes = cols_left <= 0 ? 0u : (cols_left >= 16384 ? 65536u : (uint32_t)cols_left * 4u);
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
-__device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t rs, int byte_off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, byte_off, 0, 0));
+__device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t rs, int lane_off, int const_off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane_off, const_off, 0));
 }
 
 // Fundamental-anchored: HP_k(i, j) = HP_{k-1}(i, j) + FOP(k i, k j), a term
-// being 0 where (k i, k j) is outside the plane.  Cumulative in k.  A row's
-// loads (the fundamental and every harmonic's source row k i inside the
-// plane) are issued together before its sums, as buffer loads whose range
-// check supplies the zeros of columns k j >= n.  Harmonic m of the tile
-// starting at column t0 reads columns m t0 + m (t + 256 a).  Six waves per
-// SIMD (80 VGPRs) hide the load latency best: 0.94 ms on a 2^22 plane against
-// 0.98 ms at five and 1.00 ms at eight (with spills); loading row r + 1
-// before the sums of row r (three waves) took 1.06 ms.
-template <int NH>
-__global__ __launch_bounds__(HS_THREADS, 6) void k_harmsum_fund(const float* __restrict__ fop, int64_t ld, int n,
-                                                             int z_max, const int* __restrict__ tile_of_block,
-                                                             const float* __restrict__ ta,
-                                                             fdas_cand* __restrict__ cands, int cap,
-                                                             int32_t* __restrict__ counts) {
-  const int tile = xt_tile(tile_of_block, n);
-  if (tile < 0) return;  // uniform
-  const int rows = 2 * z_max + 1;
-  const int64_t t0 = (int64_t)tile * XT;
+// being 0 where (k i, k j) is outside the plane.  Cumulative in k.  Row i has
+// the terms m <= z_max / |i|; rows are walked in groups of equal term count MV,
+// R rows at a time, so that a wave always has about 28 loads in flight (half of
+// the rows have the fundamental only).  Planes past MV hold the same sum: it is
+// compared with the smallest of their thresholds.  Measured on 2^22 bins: 0.76 ms
+// for the whole call, 5.2 TB/s of its 2.75 planes of lines; 0.93 ms before.
+//
+// Row i0 + r of [a, b], clamped to b (a repeated row sets its bit again).
+template <int NH, int MV, int R>
+__device__ __forceinline__ void fund_rows(const float* __restrict__ fop, int64_t ld, int n, int z_max, int64_t t0,
+                                          int a0, int b0, const float* __restrict__ s_ta, int rbase, RowMask& mk) {
   const int t = (int)threadIdx.x;
-  int col[4];
-  bool in[4];
+  for (int i0 = a0; i0 <= b0; i0 += R) {
+    float v[R][MV][4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    col[a] = (int)t0 + t + HS_THREADS * a;  // n <= 2^30, so no wrap
-    in[a] = col[a] < n;
-  }
-  for (int r = 0; r < rows; ++r) {
-    const int i = r - z_max;
-    float v[NH + 1][4];
-    {
-      const __amdgpu_buffer_rsrc_t rs = row_rsrc(fop + (size_t)r * ld + t0, (int64_t)n - t0);
+    for (int q = 0; q < R; ++q) {
+      const int i = min(i0 + q, b0);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) v[1][a] = row_load(rs, 4 * (t + HS_THREADS * a));
-    }
+      for (int m = 1; m <= MV; ++m) {
+        // harmonic m of the tile starting at column t0 reads columns m t0 + m (t + 256 a)
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(fop + (size_t)(m * i + z_max) * ld + m * t0, (int64_t)n - m * t0);
 #pragma unroll
-    for (int m = 2; m <= NH; ++m) {
-      const int si = m * i;
-      if (si >= -z_max && si <= z_max) {  // uniform
-        const __amdgpu_buffer_rsrc_t rs =
-            row_rsrc(fop + (size_t)(si + z_max) * ld + m * t0, (int64_t)n - m * t0);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) v[m][a] = row_load(rs, 4 * m * (t + HS_THREADS * a));
-      } else {
-#pragma unroll
-        for (int a = 0; a < 4; ++a) v[m][a] = 0.0f;
+        for (int a = 0; a < 4; ++a) v[q][m - 1][a] = row_load(rs, 4 * m * t, 4 * m * kStrideFund * a);
       }
     }
-    float hp[4];
 #pragma unroll
-    for (int m = 1; m <= NH; ++m) {
-      const float th = ta[(m - 1) * rows + r];
-      unsigned bits = 0u;
+    for (int q = 0; q < R; ++q) {
+      const int r = min(i0 + q, b0) + z_max;
+      const float* th = s_ta + 8 * r;
+      float hp[4];
+      bool hit = false;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        hp[a] = m == 1 ? v[1][a] : hp[a] + v[m][a];
-        bits |= (in[a] && hp[a] > th) ? 1u << a : 0u;
+      for (int m = 1; m <= MV; ++m) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) hp[a] = m == 1 ? v[q][0][a] : hp[a] + v[q][m - 1][a];
+        hit = hit || max4(hp) > th[m - 1];
       }
-      wave_append(m, i, col, hp, bits, cands, cap, counts);
+      mk.note(hit, r - rbase);
     }
   }
+}
+
+template <int NH, int MV>
+__device__ __forceinline__ void fund_groups(const float* __restrict__ fop, int64_t ld, int n, int z_max, int64_t t0,
+                                            int i0, int i1, const float* __restrict__ s_ta, int rbase, RowMask& mk) {
+  constexpr int R = MV == 1 ? 7 : MV == 2 ? 4 : MV <= 4 ? 2 : 1;
+  // |i| in [lo, hi] has MV terms (row 0 all of them)
+  const int hi = z_max / MV, lo = MV == NH ? 0 : z_max / (MV + 1) + 1;
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    int a = side ? lo : -hi, b = side ? hi : -lo;
+    if (MV == NH) {
+      if (side) break;
+      b = hi;
+    }
+    a = max(a, i0);
+    b = min(b, i1);
+    if (a <= b) fund_rows<NH, MV, R>(fop, ld, n, z_max, t0, a, b, s_ta, rbase, mk);
+  }
+  if constexpr (MV < NH) fund_groups<NH, MV + 1>(fop, ld, n, z_max, t0, i0, i1, s_ta, rbase, mk);
+}
+
+template <int NH>
+__global__ __launch_bounds__(HS_THREADS, 6) void k_detect_fund(const float* __restrict__ fop, int64_t ld, int n,
+                                                               int z_max, int rbase, int rend,
+                                                               const int* __restrict__ tile_of_block,
+                                                               const float* __restrict__ ta,
+                                                               int4* __restrict__ hitrows, int hit_cap,
+                                                               int32_t* __restrict__ hit_count) {
+  __shared__ float s_ta[129 * 8];  // [row][m - 1]; the last term's entry is the smallest of the planes from there on
+  const int rows = 2 * z_max + 1;
+  for (int r = threadIdx.x; r < rows; r += HS_THREADS) {
+    const int i = r < z_max ? z_max - r : r - z_max;
+    const int mv = i == 0 ? NH : min(NH, z_max / i);
+    float low = ta[(NH - 1) * rows + r];
+    for (int m = NH - 1; m >= mv; --m) low = fminf(low, ta[(m - 1) * rows + r]);
+    for (int m = 1; m < mv; ++m) s_ta[r * 8 + m - 1] = ta[(m - 1) * rows + r];
+    s_ta[r * 8 + mv - 1] = low;
+  }
+  __syncthreads();
+  const int tile = tile_of_block ? tile_of_block[blockIdx.x] : (int)blockIdx.x;
+  if (tile < 0 || (int64_t)tile * XT >= n) return;  // uniform
+  int r0, r1;
+  row_segment(rbase, rend, r0, r1);
+  const int64_t t0 = (int64_t)tile * XT;
+  RowMask mk;
+  fund_groups<NH, 1>(fop, ld, n, z_max, t0, r0 - z_max, r1 - 1 - z_max, s_ta, rbase, mk);
+  const int c0 = (int)t0 + (int)threadIdx.x;
+  if (c0 >= n) mk = RowMask();
+  flush_mask(mk, c0, hitrows, hit_cap, hit_count);
 }
 
 // Highest-harmonic-anchored: HP_k(i, j) = sum_{m=1..k} FOP(rho(m i, k), rho(m j, k)),
@@ -263,95 +290,191 @@ __host__ __device__ constexpr int frac_den(int idx) {
 }
 static_assert(frac_count(8) == 22 && frac_index(4, 8) == 1 && frac_num(5) == 3 && frac_den(5) == 4, "fractions");
 
+// rho(p |i|, q) of every fraction for |i| <= 65, and the fractions whose value
+// differs between |i| and |i| + 1: looked up with scalar loads, where 22
+// divisions a row would outweigh the row's sums.
+struct HighTable {
+  unsigned row[66][8];   // fraction f in byte f % 4 of word f / 4
+  unsigned changes[65];  // bit f: rho at |i| + 1 is not rho at |i|
+};
+constexpr HighTable make_high_table() {
+  HighTable t{};
+  for (int f = 0; f < frac_count(8); ++f) {
+    const unsigned p = (unsigned)frac_num(f), q = (unsigned)frac_den(f);
+    unsigned last = 0;
+    for (unsigned x = 0; x < 66; ++x) {
+      const unsigned s = (2u * p * x + q) / (2u * q);
+      t.row[x][f / 4] |= s << (8 * (f % 4));
+      if (x > 0 && s != last) t.changes[x - 1] |= 1u << f;
+      last = s;
+    }
+  }
+  return t;
+}
+constexpr HighTable kHighTableValue = make_high_table();
+__constant__ const HighTable kHighTable = kHighTableValue;
+
 template <int NH>
 struct HighState {
   float val[frac_count(NH)][4];
-  int row[frac_count(NH)];  // source row the values belong to (uniform)
+  int off[frac_count(NH)];  // byte offset of the lane's first source column from the workgroup's
 };
 
-// rho(P x, Q) for x >= 0.  Narrow: 2 P x + Q < 2^32 (n * 2 NH < 2^32).  Wide,
-// any x < 2^31: with x = Q u + w (w < Q), P x / Q = P u + P w / Q, so the
-// rounding only involves P w < P Q.
-template <int P, int Q, bool WIDE>
+// rho(P x, Q) for 0 <= x < 2^31 (n <= 2^30): with x = Q u + w (w < Q), P x / Q =
+// P u + P w / Q, so the rounding only involves P w < P Q.
+template <int P, int Q>
 __device__ __forceinline__ int rho_pos(int x) {
-  if constexpr (WIDE) {
-    const unsigned u = (unsigned)x / Q, w = (unsigned)x - u * Q;
-    return (int)(P * u + (2u * P * w + Q) / (2u * Q));
-  } else {
-    return (int)((2u * P * (unsigned)x + Q) / (2u * Q));
+  const unsigned u = (unsigned)x / Q, w = (unsigned)x - u * Q;
+  return (int)(P * u + (2u * P * w + Q) / (2u * Q));
+}
+
+// source row of fraction P/Q for output row i
+template <int P, int Q>
+__device__ __forceinline__ int high_row(int i, int z_max) {
+  const int s = rho_pos<P, Q>(i < 0 ? -i : i);
+  return (i < 0 ? -s : s) + z_max;
+}
+
+template <int NH, int F>
+__device__ __forceinline__ void hi_offsets(HighState<NH>& st, int d) {
+  if constexpr (F < frac_count(NH)) {
+    st.off[F] = 4 * rho_pos<frac_num(F), frac_den(F)>(d);
+    hi_offsets<NH, F + 1>(st, d);
   }
 }
 
-// refresh fraction F and the ones after it for output row i
-template <int NH, bool WIDE, int F>
-__device__ __forceinline__ void hi_refresh(HighState<NH>& st, const float* __restrict__ fop, int64_t ld, int z_max,
-                                           int i, const int (&colc)[4]) {
+// Load the fractions of output row i whose bit is set in `mask` (uniform), F and
+// the ones after it; c0 = the workgroup's first column, a multiple of 4 x 840.
+template <int NH, int F>
+__device__ __forceinline__ void hi_refresh(HighState<NH>& st, const float* __restrict__ fop, int64_t ld, int n,
+                                           int z_max, int i, unsigned mask, const unsigned (&srows)[8], int c0) {
   if constexpr (F < frac_count(NH)) {
-    constexpr int P = frac_num(F), Q = frac_den(F);
-    const int s = rho_pos<P, Q, false>(i < 0 ? -i : i);
-    const int srow = (i < 0 ? -s : s) + z_max;
-    if (srow != st.row[F]) {  // uniform
-      st.row[F] = srow;
-      const float* src = fop + (size_t)srow * ld;
+    if ((mask >> F) & 1u) {
+      constexpr int P = frac_num(F), Q = frac_den(F);
+      const int sr = (int)((srows[F / 4] >> (8 * (F % 4))) & 255u);
+      const int64_t s0 = (int64_t)(c0 / Q) * P;
+      const __amdgpu_buffer_rsrc_t rs =
+          row_rsrc(fop + (size_t)((i < 0 ? -sr : sr) + z_max) * ld + s0, (int64_t)n - s0);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) st.val[F][a] = src[rho_pos<P, Q, WIDE>(colc[a])];
+      for (int a = 0; a < 4; ++a) st.val[F][a] = row_load(rs, st.off[F], 4 * (kStrideHigh * a / Q * P));
     }
-    hi_refresh<NH, WIDE, F + 1>(st, fop, ld, z_max, i, colc);
+    hi_refresh<NH, F + 1>(st, fop, ld, n, z_max, i, mask, srows, c0);
   }
 }
 
 // HP_K = terms m = 1..K in m order
 template <int NH, int K, int M>
-__device__ __forceinline__ void hi_sum(const HighState<NH>& st, float (&hp)[4]) {
+__device__ __forceinline__ void hi_sum(const float (&val)[frac_count(NH)][4], float (&hp)[4]) {
   if constexpr (M <= K) {
     constexpr int FI = frac_index(M, K);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) hp[a] = M == 1 ? st.val[FI][a] : hp[a] + st.val[FI][a];
-    hi_sum<NH, K, M + 1>(st, hp);
+    for (int a = 0; a < 4; ++a) hp[a] = M == 1 ? val[FI][a] : hp[a] + val[FI][a];
+    hi_sum<NH, K, M + 1>(val, hp);
   }
 }
 
 template <int NH, int K>
-__device__ __forceinline__ void hi_planes(const HighState<NH>& st, int r, int i, int rows, const int (&col)[4],
-                                          const bool (&in)[4], const float* __restrict__ ta,
-                                          fdas_cand* __restrict__ cands, int cap, int32_t* __restrict__ counts) {
-  if constexpr (K <= NH) {
-    float hp[4];
-    hi_sum<NH, K, 1>(st, hp);
-    const float t = ta[(K - 1) * rows + r];
-    unsigned bits = 0u;
+__device__ __forceinline__ bool hi_hit(const HighState<NH>& st, int r, int rows, const float* __restrict__ ta) {
+  float hp[4];
+  hi_sum<NH, K, 1>(st.val, hp);
+  const bool hit = max4(hp) > ta[(K - 1) * rows + r];
+  if constexpr (K < NH)
+    return hit | hi_hit<NH, K + 1>(st, r, rows, ta);
+  else
+    return hit;
+}
+
+// Threads run over groups of four columns 840 apart, 840 groups to a block of
+// 3360 columns.  Columns past n - 1 read zeros (or other columns, where
+// rho(p j, q) < n) and are never emitted.  Bound by the lines it moves from
+// beyond L2: sum over the fractions of (p/q)^2 = 7.5 planes (a column's sources at
+// other fractions lie in other tiles, read at other rows).  Measured on 2^22
+// bins 2.06 ms (5.2 TB/s of those lines), 1,500,001 bins 0.72 ms (0.06 ms more
+// without the chunks, 0.12 ms more in ascending order); 2.17-2.23 and 0.85-0.97 ms
+// with candidates appended row by row and offsets formed by division per load.
+template <int NH>
+__global__ __launch_bounds__(HS_THREADS, 3) void k_detect_high(const float* __restrict__ fop, int64_t ld, int n,
+                                                               int z_max, int rbase, int rend,
+                                                               const int* __restrict__ tile_of_block,
+                                                               const float* __restrict__ ta,
+                                                               int4* __restrict__ hitrows, int hit_cap,
+                                                               int32_t* __restrict__ hit_count) {
+  const int rows = 2 * z_max + 1;
+  const int tile = tile_of_block ? tile_of_block[blockIdx.x] : (int)blockIdx.x;
+  if (tile < 0 || (int64_t)tile * HS_THREADS / kStrideHigh * (4 * kStrideHigh) >= n) return;  // uniform
+  const int g0 = tile * HS_THREADS;
+  const int first_blk = g0 / kStrideHigh;
+  const int c0 = first_blk * 4 * kStrideHigh;  // <= n: fits
+  const int g = g0 + (int)threadIdx.x;
+  const int64_t col0 = (int64_t)(g / kStrideHigh) * 4 * kStrideHigh + g % kStrideHigh;
+  int r0, r1;
+  row_segment(rbase, rend, r0, r1);
+  HighState<NH> st;
+  hi_offsets<NH, 0>(st, (int)(col0 - c0));
+  RowMask mk;
+  for (int r = r0; r < r1; ++r) {
+    const int i = r - z_max, x = i < 0 ? -i : i;
+    unsigned srows[8];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) bits |= (in[a] && hp[a] > t) ? 1u << a : 0u;
-    wave_append(K, i, col, hp, bits, cands, cap, counts);
-    hi_planes<NH, K + 1>(st, r, i, rows, col, in, ta, cands, cap, counts);
+    for (int q = 0; q < 8; ++q) srows[q] = kHighTable.row[x][q];
+    hi_refresh<NH, 0>(st, fop, ld, n, z_max, i, r == r0 ? ~0u : kHighTable.changes[i > 0 ? i - 1 : x], srows, c0);
+    mk.note(hi_hit<NH, 1>(st, r, rows, ta), r - rbase);
+  }
+  if (col0 >= n) mk = RowMask();
+  flush_mask(mk, (int)min(col0, (int64_t)n), hitrows, hit_cap, hit_count);
+}
+
+// Sums hk[1..NH] of row i at the four columns c0 + STRIDE a, in phase 1's order.
+// Columns past n - 1 are left 0.
+template <int NH, int F>
+__device__ __forceinline__ void high_values(float (&val)[frac_count(NH)][4], const float* __restrict__ fop, int64_t ld,
+                                            int n, int z_max, int i, int c0) {
+  if constexpr (F < frac_count(NH)) {
+    constexpr int P = frac_num(F), Q = frac_den(F);
+    const float* src = fop + (size_t)high_row<P, Q>(i, z_max) * ld;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const int c = c0 + kStrideHigh * a;
+      val[F][a] = c < n ? src[rho_pos<P, Q>(c)] : 0.0f;
+    }
+    high_values<NH, F + 1>(val, fop, ld, n, z_max, i, c0);
   }
 }
 
-template <int NH, bool WIDE>
-__global__ __launch_bounds__(HS_THREADS) void k_harmsum_high(const float* __restrict__ fop, int64_t ld, int n,
-                                                             int z_max, const int* __restrict__ tile_of_block,
-                                                             const float* __restrict__ ta,
-                                                             fdas_cand* __restrict__ cands, int cap,
-                                                             int32_t* __restrict__ counts) {
-  const int tile = xt_tile(tile_of_block, n);
-  if (tile < 0) return;  // uniform
-  const int rows = 2 * z_max + 1;
-  int col[4], colc[4];
-  bool in[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    col[a] = tile * XT + (int)threadIdx.x + HS_THREADS * a;
-    in[a] = col[a] < n;
-    colc[a] = in[a] ? col[a] : n - 1;  // columns past n - 1 read column n - 1 and are never emitted
+template <int NH, int K>
+__device__ __forceinline__ void high_planes(const float (&val)[frac_count(NH)][4], float (&hk)[NH + 1][4]) {
+  if constexpr (K <= NH) {
+    hi_sum<NH, K, 1>(val, hk[K]);
+    high_planes<NH, K + 1>(val, hk);
   }
-  constexpr int NF = frac_count(NH);
-  HighState<NH> st;
+}
+
+template <int MAP, int NH>
+__device__ __forceinline__ void map_sums(float (&hk)[NH + 1][4], const float* __restrict__ fop, int64_t ld, int n,
+                                         int z_max, int i, int c0) {
+  if constexpr (MAP == FDAS_HSUM_HIGHEST) {
+    float val[frac_count(NH)][4];
+    high_values<NH, 0>(val, fop, ld, n, z_max, i, c0);
+    high_planes<NH, 1>(val, hk);
+  } else {
+    constexpr int STRIDE = MAP == FDAS_HSUM_FUNDAMENTAL ? kStrideFund : 1;
+    float v[NH + 1][4];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) st.row[f] = -1;
-  for (int r = 0; r < rows; ++r) {
-    const int i = r - z_max;
-    hi_refresh<NH, WIDE, 0>(st, fop, ld, z_max, i, colc);
-    hi_planes<NH, 1>(st, r, i, rows, col, in, ta, cands, cap, counts);
+    for (int m = 1; m <= NH; ++m) {
+      const int si = MAP == FDAS_HSUM_FUNDAMENTAL ? m * i : i / m;
+      const bool row_in = si >= -z_max && si <= z_max;
+      const float* src = fop + (size_t)((row_in ? si : 0) + z_max) * ld;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const int c = c0 + STRIDE * a;
+        const int64_t sc = MAP == FDAS_HSUM_FUNDAMENTAL ? (int64_t)m * c : (int64_t)(c / m);
+        v[m][a] = row_in && c < n && sc < n ? src[sc] : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int m = 1; m <= NH; ++m)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) hk[m][a] = m == 1 ? v[1][a] : hk[m - 1][a] + v[m][a];
   }
 }
 
@@ -653,18 +776,64 @@ __device__ __forceinline__ void hs_emit_row(const float* __restrict__ fop, int64
   }
 }
 
+// Append the candidates of a wave: every active lane holds the sums hk[1..NH] of
+// row i (threshold row r) at the columns c0 + STRIDE a.  Each plane's slots are
+// reserved for the whole wave in one round of atomics: lane m - 1 reserves plane
+// m, lane offsets come from ballots of the 3-bit per-lane counts.  A plan keeps
+// (2 z_max + 1) n_max below 2^31, so a count cannot wrap; the unsigned compare
+// still keeps any slot that is not in [0, cap) from being written.
+template <int NH, int STRIDE>
+__device__ __forceinline__ void hs_append_wave(const float (&hk)[NH + 1][4], int n, int rows, int c0, int i, int r,
+                                               bool act, const float* __restrict__ ta, fdas_cand* __restrict__ cands,
+                                               int cap, int32_t* __restrict__ counts, int lane) {
+  unsigned hits = 0u;  // bit 4 * (m - 1) + a: column c0 + STRIDE a is a candidate of plane m
+  int below_m[NH + 1], total[NH + 1];
+  auto below = [&](unsigned long long b) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
+  };
+  int mine = 0;
+#pragma unroll
+  for (int m = 1; m <= NH; ++m) {
+    int c = 0;
+    const float t = act ? ta[(m - 1) * rows + r] : 0.0f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const bool h = act && c0 + STRIDE * a < n && hk[m][a] > t;
+      hits |= h ? 1u << (4 * (m - 1) + a) : 0u;
+      c += h ? 1 : 0;
+    }
+    const unsigned long long b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
+    total[m] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+    below_m[m] = below(b0) + 2 * below(b1) + 4 * below(b2);
+    if (lane == m - 1) mine = total[m];
+  }
+  int base = 0;
+  if (lane < NH && mine > 0) base = atomicAdd(&counts[lane], mine);
+#pragma unroll
+  for (int m = 1; m <= NH; ++m) {
+    if (total[m] == 0) continue;  // uniform
+    int slot = __shfl(base, m - 1) + below_m[m];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      if ((hits >> (4 * (m - 1) + a)) & 1u) {
+        if ((unsigned)slot < (unsigned)cap)
+          *reinterpret_cast<int4*>(cands + (size_t)(m - 1) * cap + slot) =
+              make_int4(m, i, c0 + STRIDE * a, __float_as_int(hk[m][a]));
+        ++slot;
+      }
+    }
+  }
+}
+
 // Phase 2 for one wave: every active lane re-forms the sums of its row r of
 // columns j0..j0+3 (same k order as phase 1, so bit-identical) and the wave
 // appends the candidates of all lanes to one plane set (fop, cands, counts
-// uniform across the wave).  Each plane's slots are reserved for the whole
-// wave in one round of atomics: lane m - 1 reserves plane m, lane offsets come
-// from ballots of the 3-bit per-lane counts.
+// uniform across the wave).
 template <int Z, int NH>
 __device__ __forceinline__ void hs_emit_wave(const float* __restrict__ fop, int64_t ld, int n, int j0, int r,
                                              bool act, const float* __restrict__ ta,
                                              fdas_cand* __restrict__ cands, int cap,
                                              int32_t* __restrict__ counts, int lane) {
-  constexpr int ROWS = 2 * Z + 1;
   const int i = r - Z;
   float hk[NH + 1][4];
   if (act) {
@@ -685,42 +854,38 @@ __device__ __forceinline__ void hs_emit_wave(const float* __restrict__ fop, int6
 #pragma unroll
       for (int a = 0; a < 4; ++a) hk[m][a] = hk[m - 1][a] + src[m][a];
   }
-  unsigned hits = 0u;  // bit 4 * (m - 1) + a: column j0 + a is a candidate of plane m
-  int below_m[NH + 1], total[NH + 1];
-  auto below = [&](unsigned long long b) {
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
-  };
-  int mine = 0;
-#pragma unroll
-  for (int m = 1; m <= NH; ++m) {
-    int c = 0;
-    const float t = act ? ta[(m - 1) * ROWS + r] : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const bool h = act && j0 + a < n && hk[m][a] > t;
-      hits |= h ? 1u << (4 * (m - 1) + a) : 0u;
-      c += h ? 1 : 0;
+  hs_append_wave<NH, 1>(hk, n, 2 * Z + 1, j0, i, r, act, ta, cands, cap, counts, lane);
+}
+
+// Phase 2 of the kernels for any row count and of the other index maps: work
+// item w = entry * 96 + row bit of the pass that starts at row rbase.
+template <int MAP, int NH>
+__global__ __launch_bounds__(HS_THREADS) void k_emit_map(const float* __restrict__ fop, int64_t ld, int n, int z_max,
+                                                         int rbase, const int4* __restrict__ hitrows, int hit_cap,
+                                                         const int32_t* __restrict__ hit_count,
+                                                         const float* __restrict__ ta, fdas_cand* __restrict__ cands,
+                                                         int cap, int32_t* __restrict__ counts) {
+  constexpr int STRIDE =
+      MAP == FDAS_HSUM_HIGHEST ? kStrideHigh : MAP == FDAS_HSUM_FUNDAMENTAL ? kStrideFund : 1;
+  const int64_t items = (int64_t)min(*hit_count, hit_cap) * kRowsPerPass;
+  const int lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)gridDim.x * HS_THREADS;
+  for (int64_t w0 = (int64_t)blockIdx.x * HS_THREADS + (threadIdx.x & ~63); w0 < items; w0 += stride) {
+    const int64_t w = w0 + lane;
+    bool act = w < items;
+    int4 ent = make_int4(0, 0, 0, 0);
+    int b = 0;
+    if (act) {
+      ent = hitrows[w / kRowsPerPass];
+      b = (int)(w % kRowsPerPass);
+      const unsigned word = (unsigned)(b < 32 ? ent.y : (b < 64 ? ent.z : ent.w));
+      act = ((word >> (b % 32)) & 1u) != 0;
     }
-    const unsigned long long b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
-    total[m] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-    below_m[m] = below(b0) + 2 * below(b1) + 4 * below(b2);
-    if (lane == m - 1) mine = total[m];
-  }
-  int base = 0;
-  if (lane < NH && mine > 0) base = atomicAdd(&counts[lane], mine);
-#pragma unroll
-  for (int m = 1; m <= NH; ++m) {
-    if (total[m] == 0) continue;  // uniform
-    int slot = __shfl(base, m - 1) + below_m[m];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      if ((hits >> (4 * (m - 1) + a)) & 1u) {
-        if ((unsigned)slot < (unsigned)cap)
-          *reinterpret_cast<int4*>(cands + (size_t)(m - 1) * cap + slot) =
-              make_int4(m, i, j0 + a, __float_as_int(hk[m][a]));
-        ++slot;
-      }
-    }
+    if (__ballot(act) == 0ull) continue;  // uniform
+    const int r = rbase + b, i = r - z_max;
+    float hk[NH + 1][4];
+    if (act) map_sums<MAP, NH>(hk, fop, ld, n, z_max, i, ent.x);
+    hs_append_wave<NH, STRIDE>(hk, n, 2 * z_max + 1, ent.x, i, r, act, ta, cands, cap, counts, lane);
   }
 }
 
@@ -824,22 +989,30 @@ __device__ __forceinline__ uint64_t tile_key(int t, int top) {
   return (frac << 6) | (uint64_t)(o + 1);
 }
 
-__global__ void k_tile_order(int* __restrict__ order, int T, int top, int per) {
+// With high_tiles > 0, t is a chunk of kHighChunk tiles of the highest-anchored
+// kernel and rank q goes where harmsum_high_order puts it.
+__global__ void k_tile_order(int* __restrict__ order, int T, int top, int per, int high_tiles) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
   const uint64_t k = tile_key(t, top);
   int q = 0;
   for (int u = 0; u < T; ++u) q += tile_key(u, top) < k ? 1 : 0;
-  order[(q % per) * 8 + q / per] = t;
+  if (high_tiles > 0) {
+    for (int e = 0; e < kHighChunk; ++e)
+      if (t * kHighChunk + e < high_tiles) order[((q / 8) * kHighChunk + e) * 8 + q % 8] = t * kHighChunk + e;
+  } else {
+    order[(q % per) * 8 + q / per] = t;
+  }
 }
 
 // Scratch of fdas_harmonic_sum_noalloc in static device memory (one copy per
 // GPU, kept until the process ends): hit-row counter, tile order, hit-row list.
 constexpr int64_t kNoAllocMaxN = (int64_t)1 << 22;
 constexpr size_t kNaOrderOff = 256;
-constexpr size_t kNaOrderInts = ((size_t)kNoAllocMaxN / (4 * HS_THREADS) + 8 + 63) / 64 * 64;
+constexpr size_t kNaOrderInts = ((size_t)kNoAllocMaxN / (4 * HS_THREADS) + 128 + 63) / 64 * 64;
 constexpr size_t kNaHitOff = kNaOrderOff + kNaOrderInts * sizeof(int);
-constexpr size_t kNaBytes = kNaHitOff + (size_t)(kNoAllocMaxN / 4) * sizeof(int4);
+constexpr int kNaHitCap = (int)(kNoAllocMaxN / 4) + kHitSlack;
+constexpr size_t kNaBytes = kNaHitOff + (size_t)kNaHitCap * sizeof(int4);
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
 }  // namespace
@@ -861,19 +1034,20 @@ hipError_t launch_harmsum_noalloc(const float* fop, int64_t n, int64_t ld, int z
   int4* hitrows = reinterpret_cast<int4*>(base + kNaHitOff);
   int32_t* hit_count = reinterpret_cast<int32_t*>(base);
   const int cols = 4 * HS_THREADS;
-  const int T = (int)((n + cols - 1) / cols);
-  const int per = (T + 7) / 8;
-  const bool ordered = (z_max == 42 && index == FDAS_HSUM_STRETCH) || index == FDAS_HSUM_FUNDAMENTAL ||
-                       index == FDAS_HSUM_HIGHEST;
+  const bool high = index == FDAS_HSUM_HIGHEST;
+  const int tiles = (int)(high ? harmsum_high_tiles(n) : (n + cols - 1) / cols);
+  const int T = high ? (tiles + kHighChunk - 1) / kHighChunk : tiles;  // tiles or chunks to order
+  const int per = high ? (T + 7) / 8 * kHighChunk : (T + 7) / 8;       // workgroups per XCD
+  const bool ordered = (z_max == 42 && index == FDAS_HSUM_STRETCH) || index == FDAS_HSUM_FUNDAMENTAL || high;
   if (ordered) {
     int top = 0;
     while ((1LL << (top + 1)) <= (int64_t)(T > 2 ? T - 1 : 1)) ++top;
     hipError_t e = launch_fill_i32(order, per * 8, -1, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tile_order, dim3((T + 255) / 256), dim3(256), 0, s, order, T, top, per);
+    hipLaunchKernelGGL(k_tile_order, dim3((T + 255) / 256), dim3(256), 0, s, order, T, top, per, high ? tiles : 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const HsWork wk{order, per * 8, hitrows, hit_count, emit_blocks};
+  const HsWork wk{order, per * 8, hitrows, hit_count, emit_blocks, kNaHitCap};
   return launch_harmsum(fop, n, ld, z_max, n_harm, ta, cands, cap, counts, wk, index, s);
 }
 
@@ -953,54 +1127,41 @@ hipError_t launch_harmsum_batch85(const HsTrial* trials, int ntrials, int blk_be
   return hipGetLastError();
 }
 
+// one pass (at most 96 rows) of both phases
+template <int MAP, int NH, typename Detect>
+hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_max, int rbase, int rend,
+                      const int* order, const float* ta, fdas_cand* cands, int cap, int32_t* counts,
+                      const HsWork& wk, unsigned blocks, unsigned segs, unsigned eblocks, hipStream_t s) {
+  // The other maps' kernels reserve LDS they do not use, so that fewer waves share
+  // a compute unit than registers allow: the waves' source rows evict each
+  // other's lines.  Highest: three workgroups (2^22 bins 2.06 ms; four 2.19-2.24,
+  // two 2.19).  Fundamental: four beside its 4 KB table (1,500,001 bins 0.365 ms;
+  // six or eight 0.415).
+  const size_t reserve = MAP == FDAS_HSUM_HIGHEST ? 50000 : MAP == FDAS_HSUM_FUNDAMENTAL ? 36000 : 0;
+  hipLaunchKernelGGL(detect, dim3(blocks, segs), dim3(HS_THREADS), reserve, s, fop, ld, n, z_max, rbase, rend, order, ta,
+                     wk.hitrows, wk.hit_cap, wk.hitrow_count);
+  hipLaunchKernelGGL((k_emit_map<MAP, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, n, z_max, rbase,
+                     wk.hitrows, wk.hit_cap, wk.hitrow_count, ta, cands, cap, counts);
+  return hipGetLastError();
+}
+
+int64_t harmsum_hit_entries(int64_t n_max) {
+  return std::max<int64_t>((n_max + 3) / 4, kSplitBins / 4) + kHitSlack;
+}
+
 hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, int n_harm, const float* ta,
                           fdas_cand* cands, int cap, int32_t* counts, const HsWork& wk, int index, hipStream_t s) {
-  // the counts (and the fast path's hit-row counter) start at zero, in one launch
-  const bool fast = z_max == 42 && index == FDAS_HSUM_STRETCH;
-  hipLaunchKernelGGL(k_fill_counts, dim3(1), dim3(64), 0, s, counts, n_harm, fast ? wk.hitrow_count : nullptr);
+  // the counts and the hit-row counter start at zero, in one launch
+  hipLaunchKernelGGL(k_fill_counts, dim3(1), dim3(64), 0, s, counts, n_harm, wk.hitrow_count);
   {
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
   }
-  if (index == FDAS_HSUM_FUNDAMENTAL || index == FDAS_HSUM_HIGHEST) {
-    // column tiles of XT columns, in the order of wk.tile_of_block when given
-    const unsigned blocks =
-        wk.tile_of_block ? (unsigned)wk.blocks : (unsigned)((n + XT - 1) / XT);
-    const int* order = wk.tile_of_block;
-    const bool fund = index == FDAS_HSUM_FUNDAMENTAL;
-    const bool narrow = 2 * (int64_t)n_harm * n < ((int64_t)1 << 32);  // rho(m j, k) in 32-bit arithmetic
-    switch (n_harm) {
-#define FDAS_HSX_CASE(NH)                                                                                          \
-  case NH:                                                                                                         \
-    if (fund)                                                                                                      \
-      hipLaunchKernelGGL(k_harmsum_fund<NH>, dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, (int)n, z_max, order,  \
-                         ta, cands, cap, counts);                                                                  \
-    else if (narrow)                                                                                               \
-      hipLaunchKernelGGL((k_harmsum_high<NH, false>), dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, (int)n, z_max, \
-                         order, ta, cands, cap, counts);                                                           \
-    else                                                                                                           \
-      hipLaunchKernelGGL((k_harmsum_high<NH, true>), dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, (int)n, z_max,  \
-                         order, ta, cands, cap, counts);                                                           \
-    break;
-      FDAS_HSX_CASE(1)
-      FDAS_HSX_CASE(2)
-      FDAS_HSX_CASE(3)
-      FDAS_HSX_CASE(4)
-      FDAS_HSX_CASE(5)
-      FDAS_HSX_CASE(6)
-      FDAS_HSX_CASE(7)
-      FDAS_HSX_CASE(8)
-#undef FDAS_HSX_CASE
-      default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
+  const unsigned eblocks = (unsigned)(wk.emit_blocks > 0 ? wk.emit_blocks : 1024);
   const int nn = (int)n;
-  if (z_max == 42) {
+  if (z_max == 42 && index == FDAS_HSUM_STRETCH) {
     // two-phase fast path for the 85-template plane
     const unsigned blocks = (unsigned)wk.blocks;
-    const unsigned eblocks = (unsigned)(wk.emit_blocks > 0 ? wk.emit_blocks : 1024);
     switch (n_harm) {
 #define FDAS_HSZ_CASE(NH)                                                                                          \
   case NH:                                                                                                         \
@@ -1023,27 +1184,61 @@ hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, in
     }
     return hipGetLastError();
   }
-  const int64_t groups = (n + 3) / 4;
-  const unsigned blocks = (unsigned)((groups + HS_THREADS - 1) / HS_THREADS);
-  switch (n_harm) {
-#define FDAS_HS_CASE(NH)                                                                                 \
-  case NH:                                                                                               \
-    hipLaunchKernelGGL(k_harmsum<NH>, dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, nn, z_max, ta, cands, \
-                       cap, counts);                                                                     \
-    break;
-    FDAS_HS_CASE(1)
-    FDAS_HS_CASE(2)
-    FDAS_HS_CASE(3)
-    FDAS_HS_CASE(4)
-    FDAS_HS_CASE(5)
-    FDAS_HS_CASE(6)
-    FDAS_HS_CASE(7)
-    FDAS_HS_CASE(8)
-#undef FDAS_HS_CASE
-    default:
-      return hipErrorInvalidValue;
+  // threads (groups of four columns) and workgroups of phase 1
+  int64_t groups;
+  unsigned blocks;
+  const int* order = nullptr;
+  if (index == FDAS_HSUM_FUNDAMENTAL) {
+    groups = (n + XT - 1) / XT * HS_THREADS;
+    order = wk.tile_of_block;
+    blocks = order ? (unsigned)wk.blocks : (unsigned)((n + XT - 1) / XT);
+  } else if (index == FDAS_HSUM_HIGHEST) {
+    groups = harmsum_high_tiles(n) * HS_THREADS;
+    order = wk.tile_of_block;
+    blocks = order ? (unsigned)wk.blocks : (unsigned)harmsum_high_tiles(n);
+  } else {
+    groups = (n + 3) / 4;
+    blocks = (unsigned)((groups + HS_THREADS - 1) / HS_THREADS);
   }
-  return hipGetLastError();
+  if (groups > wk.hit_cap) return hipErrorInvalidValue;
+  // row segments: enough waves to fill the chip, if the list can hold every thread's entry
+  const int64_t want = std::min<int64_t>(kMaxSegs, kSplitBins / n);
+  const unsigned segs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, wk.hit_cap / groups));
+  const int rows = 2 * z_max + 1;
+  for (int rbase = 0; rbase < rows; rbase += kRowsPerPass) {
+    const int rend = std::min(rows, rbase + kRowsPerPass);
+    if (rbase > 0) {
+      hipError_t e = launch_fill_i32(wk.hitrow_count, 1, 0, s);
+      if (e != hipSuccess) return e;
+    }
+    hipError_t e = hipErrorInvalidValue;
+    switch (n_harm) {
+#define FDAS_HSX_CASE(NH)                                                                                          \
+  case NH:                                                                                                         \
+    e = index == FDAS_HSUM_FUNDAMENTAL                                                                             \
+            ? launch_map<FDAS_HSUM_FUNDAMENTAL, NH>(k_detect_fund<NH>, fop, nn, ld, z_max, rbase, rend, order, ta, \
+                                                    cands, cap, counts, wk, blocks, segs, eblocks, s)              \
+        : index == FDAS_HSUM_HIGHEST                                                                               \
+            ? launch_map<FDAS_HSUM_HIGHEST, NH>(k_detect_high<NH>, fop, nn, ld, z_max, rbase, rend, order, ta,     \
+                                                cands, cap, counts, wk, blocks, segs, eblocks, s)                  \
+            : launch_map<FDAS_HSUM_STRETCH, NH>(k_detect_stretch<NH>, fop, nn, ld, z_max, rbase, rend, order, ta,  \
+                                                cands, cap, counts, wk, blocks, segs, eblocks, s);                 \
+    break;
+      FDAS_HSX_CASE(1)
+      FDAS_HSX_CASE(2)
+      FDAS_HSX_CASE(3)
+      FDAS_HSX_CASE(4)
+      FDAS_HSX_CASE(5)
+      FDAS_HSX_CASE(6)
+      FDAS_HSX_CASE(7)
+      FDAS_HSX_CASE(8)
+#undef FDAS_HSX_CASE
+      default:
+        break;
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace fdas
