@@ -45,6 +45,7 @@ void free_batch(fdas_plan* p) {
   if (p->d_bsort_b) (void)hipFree(p->d_bsort_b);
   if (p->d_bsort_hist) (void)hipFree(p->d_bsort_hist);
   if (p->d_bsort_totals) (void)hipFree(p->d_bsort_totals);
+  if (p->d_bbucket) (void)hipFree(p->d_bbucket);
 }
 
 }  // namespace fdas
@@ -400,8 +401,24 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
             hipSuccess ||
         (e = hipEventRecord(p->stage_done, s)) != hipSuccess)
       return hip_fail(e, "uploading the readback table");
-    e = launch_sort_batch(p->d_rb_tab, count, cap, nh, (int)M, p->rows, p->desc.z_max, p->bits_r, p->d_bsort_a,
-                          p->d_bsort_b, p->d_bsort_hist, p->d_bsort_totals, &sorted, s);
+    if (sort_buckets(cap)) {
+      if (count > p->bbucket_cap) {
+        if (p->d_bbucket) (void)hipFree(p->d_bbucket);
+        p->d_bbucket = nullptr;
+        p->bbucket_cap = 0;
+        const size_t bytes = bucket_work_ints(count) * sizeof(int);
+        if ((e = hipMalloc(reinterpret_cast<void**>(&p->d_bbucket), bytes)) != hipSuccess ||
+            (e = hipMemsetAsync(p->d_bbucket, 0, bytes, s)) != hipSuccess)
+          return hip_fail(e, "allocating the batch bucket counters");
+        p->bbucket_cap = count;
+      }
+      sorted = p->d_bsort_b;
+      e = launch_bucket_sort(nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, M, M,
+                             p->d_bsort_a, p->d_bbucket, sorted, nullptr, s);
+    } else {
+      e = launch_sort_batch(p->d_rb_tab, count, cap, nh, (int)M, p->rows, p->desc.z_max, p->bits_r, p->d_bsort_a,
+                            p->d_bsort_b, p->d_bsort_hist, p->d_bsort_totals, &sorted, s);
+    }
     if (e != hipSuccess) return hip_fail(e, "ordering candidates");
   }
   if (p->desc.top_k <= 0) {

@@ -56,6 +56,7 @@ void free_plan(fdas_plan* p) {
   if (p->d_sort_b) (void)hipFree(p->d_sort_b);
   if (p->d_sort_hist) (void)hipFree(p->d_sort_hist);
   if (p->d_sort_totals) (void)hipFree(p->d_sort_totals);
+  if (p->d_bucket) (void)hipFree(p->d_bucket);
   if (p->h_counts) (void)hipHostFree(p->h_counts);
   if (p->h_result) (void)hipHostFree(p->h_result);
   if (p->h_result_counts) (void)hipHostFree(p->h_result_counts);
@@ -160,6 +161,19 @@ hipError_t ols_tables(fdas_plan* p, int C, const OlsTables** out) {
   }
   *out = &t;
   return hipSuccess;
+}
+
+// Queue the ordering of one candidate list.  Bucket-sorted lists go to `out` when
+// it is given (with the counts to counts_out); *sorted is where the records land.
+hipError_t order_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_t* d_counts, fdas_cand* out,
+                            int32_t* counts_out, fdas_cand** sorted, hipStream_t s) {
+  const int nh = p->desc.n_harm, cap = p->desc.cand_capacity;
+  if (!sort_buckets(cap))
+    return launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r, p->d_sort_a,
+                                  p->d_sort_b, p->d_sort_hist, p->d_sort_totals, sorted, s);
+  *sorted = out ? out : p->d_sort_b;
+  return launch_bucket_sort(d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r,
+                            (int64_t)nh * cap, (int64_t)nh * cap, p->d_sort_a, p->d_bucket, *sorted, counts_out, s);
 }
 
 hipError_t tile_order_for(fdas_plan* p, int64_t n, const int** d_order, int* blocks, int cols) {
@@ -348,8 +362,12 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
     const size_t passes = (size_t)fdas::sort_passes(p->rows, bits);
     if ((e = hipMalloc(&p->d_sort_a, total * sizeof(fdas_cand))) != hipSuccess ||
         (e = hipMalloc(&p->d_sort_b, total * sizeof(fdas_cand))) != hipSuccess ||
-        (e = hipMalloc(&p->d_sort_hist, 256 * tiles * sizeof(int))) != hipSuccess ||
-        (e = hipMalloc(&p->d_sort_totals, 256 * passes * sizeof(int))) != hipSuccess ||
+        (!fdas::sort_buckets(desc->cand_capacity) &&
+         ((e = hipMalloc(&p->d_sort_hist, 256 * tiles * sizeof(int))) != hipSuccess ||
+          (e = hipMalloc(&p->d_sort_totals, 256 * passes * sizeof(int))) != hipSuccess)) ||
+        (e = hipMalloc(&p->d_bucket, fdas::bucket_work_ints(1) * sizeof(int))) != hipSuccess ||
+        (e = hipMemset(p->d_bucket, 0, fdas::bucket_work_ints(1) * sizeof(int))) != hipSuccess ||
+        (e = hipDeviceSynchronize()) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 8 * sizeof(int32_t), 0)) != hipSuccess ||
         (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max) * sizeof(int4))) != hipSuccess ||
         (e = hipMalloc(&p->d_hitrow_count, sizeof(int32_t))) != hipSuccess) {
@@ -470,8 +488,7 @@ fdas_status fdas_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
   // order on the device first (sizes come from the device counts), then one
   // wait for the counts, then the copy of the ordered records
   fdas_cand* sorted = nullptr;
-  hipError_t e = fdas::launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r,
-                                              p->d_sort_a, p->d_sort_b, p->d_sort_hist, p->d_sort_totals, &sorted, s);
+  hipError_t e = fdas::order_candidates(p, d_cands, d_counts, nullptr, nullptr, &sorted, s);
   if (e != hipSuccess) return hip_fail(e, "ordering candidates");
   int32_t* counts = p->h_counts;
   e = hipMemcpyAsync(counts, d_counts, nh * sizeof(int32_t), hipMemcpyDeviceToHost, s);
@@ -491,7 +508,7 @@ fdas_status fdas_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
     // paper mode (Table 1's N_cand): each plane keeps its top_k powers (ties:
     // lower z, then lower r), selected on the device into the other buffer
     fdas_cand* kept = sorted == p->d_sort_a ? p->d_sort_b : p->d_sort_a;
-    e = fdas::launch_topk(sorted, cap, nh, d_counts, p->desc.top_k, kept, s);
+    e = fdas::launch_topk(sorted, cap, nh, d_counts, p->desc.top_k, kept, nullptr, s);
     if (e != hipSuccess) return hip_fail(e, "selecting the top candidates");
     src = kept;
     total = 0;
@@ -539,17 +556,15 @@ fdas_status fdas_candidates_mapped(fdas_plan* p, const fdas_cand* d_cands, const
     return hip_fail(e, "mapping the result buffer");
   fdas_cand* sorted = nullptr;
   const int keep = p->desc.top_k > 0 ? std::min(p->desc.top_k, cap) : 0;
-  e = fdas::launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r, p->d_sort_a,
-                                   p->d_sort_b, p->d_sort_hist, p->d_sort_totals, &sorted, s);
-  if (e == hipSuccess && keep > 0) {
-    // paper mode: the top-k selection on the device, into the other buffer
-    fdas_cand* kept = sorted == p->d_sort_a ? p->d_sort_b : p->d_sort_a;
-    e = fdas::launch_topk(sorted, cap, nh, d_counts, keep, kept, s);
-    sorted = kept;
-  }
-  if (e == hipSuccess)
-    e = fdas::launch_copy_out(sorted, cap, nh, d_counts, nh * cap, static_cast<fdas_cand*>(d_res),
-                              static_cast<int32_t*>(d_rc), s, keep);
+  fdas_cand* res = static_cast<fdas_cand*>(d_res);
+  int32_t* rc = static_cast<int32_t*>(d_rc);
+  // the last kernel writes the result buffer: the top-k selection (paper mode),
+  // the bucket sort, or a copy of the radix-sorted records
+  e = fdas::order_candidates(p, d_cands, d_counts, keep > 0 ? nullptr : res, keep > 0 ? nullptr : rc, &sorted, s);
+  if (e == hipSuccess && keep > 0)
+    e = fdas::launch_topk(sorted, cap, nh, d_counts, keep, res, rc, s);
+  else if (e == hipSuccess && sorted != res)
+    e = fdas::launch_copy_out(sorted, cap, nh, d_counts, nh * cap, res, rc, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "ordering and reading candidates");
   const int32_t* counts = p->h_result_counts;

@@ -201,17 +201,17 @@ int sort_tile_count(int m);
 int sort_passes(int rows, int bits_r);
 
 // Ordered records [0, min(total, out_cap)) and the nh counts copied into
-// device-visible page-locked host memory by a kernel; with keep > 0 every
-// plane holds at most keep records (the layout launch_topk writes).
+// device-visible page-locked host memory by a kernel.
 hipError_t launch_copy_out(const fdas_cand* sorted, int cap, int nh, const int32_t* counts, int out_cap,
-                           fdas_cand* out, int32_t* counts_out, hipStream_t s, int keep = 0);
+                           fdas_cand* out, int32_t* counts_out, hipStream_t s);
 
 // Table 1's N_cand per plane on the device: from the ordered array (planes
 // packed, min(count, cap) records each) keep each plane's top_k highest
 // powers (ties: lower z, then lower r), in (z, r) order, packed into out
-// (plane k after sum_{k' < k} min(top_k, its records)).
+// (plane k after sum_{k' < k} min(top_k, its records)).  out and counts_out (the
+// device counts; NULL skips them) may be page-locked host memory.
 hipError_t launch_topk(const fdas_cand* sorted, int cap, int nh, const int32_t* counts, int top_k, fdas_cand* out,
-                       hipStream_t s);
+                       int32_t* counts_out, hipStream_t s);
 
 // out[t * nh + k] = ptrs[t][k] for t < count, k < nh
 hipError_t launch_gather_counts(int32_t* const* ptrs, int count, int nh, int32_t* out, hipStream_t s);
@@ -234,6 +234,19 @@ struct RbTrial {
   int64_t off;
   int64_t pad;
 };
+
+// Ordering by buckets, for lists of up to 65,536 records per plane
+// (sort_buckets): one list (planes, counts; trials = 1, tab NULL) or the trials of
+// a batch (tab).  `most` is at least the number of records in all, `scratch`
+// holds `most` records; work holds bucket_work_ints(trials) ints that were zero
+// before the first call.  The ordered records go to out (up to out_cap), which,
+// like counts_out (one list's counts; NULL skips them), may be page-locked host
+// memory.
+bool sort_buckets(int cap);
+size_t bucket_work_ints(int trials);
+hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
+                              int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
+                              int* work, fdas_cand* out, int32_t* counts_out, hipStream_t s);
 
 int sort_passes_batch(int count, int rows, int bits_r);
 

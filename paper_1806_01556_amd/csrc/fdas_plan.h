@@ -32,6 +32,7 @@ struct fdas_plan {
   fdas_cand* d_sort_b = nullptr;  // radix-sort ping-pong buffer
   int* d_sort_hist = nullptr;     // [256 * tiles] digit histograms
   int* d_sort_totals = nullptr;   // [256 * passes] digit totals per pass
+  int* d_bucket = nullptr;      // bucket counters of the single-list readback (zero between calls)
   int32_t* h_counts = nullptr;    // pinned host copy of the device counts
   fdas_cand* h_result = nullptr;  // page-locked result records of fdas_candidates_mapped
   int32_t* h_result_counts = nullptr;
@@ -63,6 +64,8 @@ struct fdas_plan {
   fdas_cand* d_bsort_b = nullptr;
   int* d_bsort_hist = nullptr;           // [256 * tiles]
   int* d_bsort_totals = nullptr;         // [256 * 8]
+  int* d_bbucket = nullptr;              // bucket counters of a batch readback (zero between calls)
+  int bbucket_cap = 0;                   // trials they serve
   int64_t rb_sort_cap = 0;
   hipStream_t cap_stream = nullptr;      // stream the batch graph is recorded on
   hipStream_t side_stream = nullptr;     // harmonic sums overlapping later convolutions

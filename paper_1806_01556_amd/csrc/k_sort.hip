@@ -3,8 +3,20 @@
 // The harmonic-sum kernel appends candidates to per-plane lists in arrival
 // order.  Algorithm 1 visits cells in (k, i, j) order, so the list is ordered
 // by the key ((k-1)*rows + row) * 2^bits_r + r, which is unique per cell.
-// The lists are packed into one array and sorted by that key with an LSD
-// radix sort (8-bit digits, stable passes):
+//
+// Lists of up to 65,536 records per plane (kBucketCap) are ordered in three
+// launches, one bucket per (plane, row):
+//   k_bucket_count    records per bucket
+//   k_bucket_scatter  (r, power) pairs to their bucket's range, in any order
+//   k_bucket_sort     a workgroup orders one bucket by r and writes the records
+// The list sizes are read from the device counts, so nothing waits for the host.
+// A readback is bound by launches and their dependent latencies, not by its
+// few megabytes: 229 k records took 73 us in the 13 launches of the radix sort
+// below and take 19 us here, 7 k records 35 and 11 us.  A bucket holds the cells of
+// one row, some hundreds; the one workgroup that orders it keeps up to 4096 in
+// LDS and passes over memory for more.  That does not scale to a row of millions
+// of candidates, so longer lists are packed into one array and sorted by the
+// whole key with an LSD radix sort (8-bit digits, stable passes):
 //   k_sort_pack    packs the per-plane lists (sizes read from the device
 //                  counts, so nothing waits for the host) and clears the
 //                  per-pass digit totals
@@ -18,12 +30,11 @@
 // Every kernel is launched for the largest possible list (n_harm * capacity
 // records); tiles past the actual count return at once.
 //
-// A batch of trials is ordered as one array (k_sort_pack_batch): while they
-// are sorted, records carry their trial number in bits 8 and up of the
-// harmonic field and the key puts the trial above the plane slot, so the
-// sorted array is trial-major with every trial's records in its own canonical
-// order; the last scatter pass clears the tag.  The batch record count is
-// known to the host, so those launches are sized exactly.
+// A batch of trials is ordered into one trial-major array: every trial has its
+// own buckets, or, in the radix sort (k_sort_pack_batch), records carry their
+// trial number in bits 8 and up of the harmonic field and the key puts the trial
+// above the plane slot; the last scatter pass clears the tag.  The batch record
+// count is known to the host, so those launches are sized exactly.
 
 #include <algorithm>
 
@@ -261,13 +272,14 @@ __device__ __forceinline__ unsigned long long topk_key(const int4* __restrict__ 
 
 __global__ __launch_bounds__(TK) void k_topk(const int4* __restrict__ sorted, int cap, int nh,
                                              const int32_t* __restrict__ counts, int top_k,
-                                             int4* __restrict__ out) {
+                                             int4* __restrict__ out, int32_t* __restrict__ counts_out) {
   __shared__ int s_hist[256];
-  __shared__ int s_scan[TK];
+  __shared__ int s_wave[TK / 64];
   __shared__ unsigned long long s_prefix;
-  __shared__ int s_need;
-  const int k = blockIdx.x, t = threadIdx.x;
+  __shared__ int s_need, s_done;
+  const int k = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
   if (k >= nh) return;
+  if (counts_out && t == 0) counts_out[k] = counts[k];
   int off[9], okeep[9];
   pack_offsets(counts, nh, cap, off);
   pack_offsets(counts, nh, cap, okeep, top_k);
@@ -278,63 +290,350 @@ __global__ __launch_bounds__(TK) void k_topk(const int4* __restrict__ sorted, in
     for (int i = t; i < m; i += TK) dst[i] = plane[i];
     return;
   }
-  // radix select of the top_k-th largest key
+  // radix select of the top_k-th largest key, until a digit's records are all
+  // kept (usually within the four digits of the power)
   if (t == 0) {
     s_prefix = 0ull;
     s_need = top_k;
+    s_done = 0;
   }
   for (int shift = 56; shift >= 0; shift -= 8) {
-    for (int d = t; d < 256; d += TK) s_hist[d] = 0;
+    if (t < 256) s_hist[t] = 0;
     __syncthreads();
     const unsigned long long prefix = s_prefix;
     const unsigned long long hmask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-    for (int i = t; i < m; i += TK) {
-      const unsigned long long key = topk_key(plane, i);
-      if ((key & hmask) == prefix) atomicAdd(&s_hist[(int)((key >> shift) & 255ull)], 1);
-    }
-    __syncthreads();
-    if (t == 0) {
-      // the digit D at which the count of keys with a larger digit stays
-      // below the need and the count with digit >= D reaches it
-      int need = s_need, above = 0, D = 255;
-      for (; D > 0; --D) {
-        if (above + s_hist[D] >= need) break;
-        above += s_hist[D];
+    for (int i0 = 0; i0 < m; i0 += TK) {
+      const int i = i0 + t;
+      const unsigned long long key = i < m ? topk_key(plane, i) : 0ull;
+      const bool in = i < m && (key & hmask) == prefix;
+      const int d = in ? (int)((key >> shift) & 255ull) : 0;
+      // one LDS atomic per distinct digit of a wave: the powers' top digits are alike
+      unsigned long long peers = __ballot(in);
+      if (peers == 0ull) continue;  // uniform
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const unsigned long long m1 = __ballot((d >> b) & 1);
+        peers &= ((d >> b) & 1) ? m1 : ~m1;
       }
-      s_need = need - above;
-      s_prefix = prefix | ((unsigned long long)D << shift);
+      const int rank =
+          __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
+      if (in && rank == 0) atomicAdd(&s_hist[d], __popcll(peers));
     }
     __syncthreads();
+    // thread t < 256 looks at digit 255 - t: the records with a larger digit stay
+    // below the need, those with it or a larger one reach it
+    const int need = s_need;
+    int own = 0, incl = 0;
+    if (t < 256) {
+      own = incl = s_hist[255 - t];
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+      }
+      if (lane == 63) s_wave[wv] = incl;
+    }
+    __syncthreads();
+    if (t < 256) {
+      for (int q = 0; q < wv; ++q) incl += s_wave[q];
+      if (incl >= need && incl - own < need) {
+        const int left = need - (incl - own);
+        s_need = left;
+        s_prefix = prefix | ((unsigned long long)(255 - t) << shift);
+        s_done = left == own ? 1 : 0;
+      }
+    }
+    __syncthreads();
+    if (s_done) break;  // uniform: every record of this digit is kept
   }
   const unsigned long long kth = s_prefix;  // keys are distinct: exactly top_k are >= kth
   // stable compaction of the keys >= kth
   int base = 0;
   for (int i0 = 0; i0 < m; i0 += TK) {
     const int i = i0 + t;
-    const int f = (i < m && topk_key(plane, i) >= kth) ? 1 : 0;
-    s_scan[t] = f;
+    const bool f = i < m && topk_key(plane, i) >= kth;
+    const unsigned long long b = __ballot(f);
+    if (lane == 0) s_wave[wv] = __popcll(b);
     __syncthreads();
-    for (int o = 1; o < TK; o <<= 1) {
-      const int u = t >= o ? s_scan[t - o] : 0;
-      __syncthreads();
-      s_scan[t] += u;
-      __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < TK / 64; ++q) {
+      const int c = s_wave[q];
+      before += q < wv ? c : 0;
+      all += c;
     }
-    if (f) dst[base + s_scan[t] - 1] = plane[i];
-    base += s_scan[TK - 1];
+    if (f)
+      dst[base + before +
+          __builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u))] = plane[i];
+    base += all;
     __syncthreads();
   }
 }
 
+constexpr int kBucketCap = 65536;
+
+// --- bucket sort ----------------------------------------------------------------
+// Bucket (k - 1) * rows + row; blockIdx.y is the trial.  Work arrays per trial:
+// totals[kMaxBuckets] and cursor[kMaxBuckets], zero between calls (the plan
+// clears them once, k_bucket_sort after use), and starts[kMaxBuckets + 1].
+
+constexpr int kMaxBuckets = 8 * 129;
+constexpr int kBucketInts = 3 * kMaxBuckets + 8;  // per trial
+constexpr int kBucketLds = 4096;                  // records a workgroup orders in LDS
+
+struct BucketList {
+  const int4* planes;     // one list
+  const int32_t* counts;
+  const RbTrial* tab;     // or a batch's
+  int cap, nh, rows, z_max;
+  int* work;              // [trials][kBucketInts]
+};
+
+__device__ __forceinline__ BucketList trial_list(const BucketList& bl, int64_t& base) {
+  BucketList one = bl;
+  base = 0;
+  if (bl.tab) {
+    one.planes = bl.tab[blockIdx.y].cands;
+    one.counts = bl.tab[blockIdx.y].counts;
+    base = bl.tab[blockIdx.y].off;
+  }
+  one.work = bl.work + (size_t)blockIdx.y * kBucketInts;
+  return one;
+}
+
+// this workgroup's share [lo, hi) of a list's m records, at least 1024 to a workgroup
+__device__ __forceinline__ void bucket_share(int m, int& lo, int& hi) {
+  const int active = min((int)gridDim.x, (m + 1023) / 1024);
+  lo = hi = 0;
+  if ((int)blockIdx.x < active) {
+    lo = (int)((int64_t)m * blockIdx.x / active);
+    hi = (int)((int64_t)m * (blockIdx.x + 1) / active);
+  }
+}
+
+// record i of the packed list and its bucket (a row outside the plane, which no
+// harmonic sum writes, is clamped)
+__device__ __forceinline__ int4 bucket_record(const BucketList& bl, const int (&off)[9], int i, int& bucket) {
+  int k = 0;
+  while (k + 1 < bl.nh && i >= off[k + 1]) ++k;
+  const int4 rec = bl.planes[(size_t)k * bl.cap + (i - off[k])];
+  bucket = k * bl.rows + min(max(rec.y + bl.z_max, 0), bl.rows - 1);
+  return rec;
+}
+
+__global__ __launch_bounds__(ST) void k_bucket_count(BucketList all) {
+  __shared__ int h[kMaxBuckets];
+  int64_t base;
+  const BucketList bl = trial_list(all, base);
+  int off[9], lo, hi;
+  bucket_share(pack_offsets(bl.counts, bl.nh, bl.cap, off), lo, hi);
+  if (lo == hi) return;  // uniform
+  const int nb = bl.nh * bl.rows;
+  for (int b = threadIdx.x; b < nb; b += ST) h[b] = 0;
+  __syncthreads();
+  for (int i = lo + threadIdx.x; i < hi; i += ST) {
+    int b;
+    bucket_record(bl, off, i, b);
+    atomicAdd(&h[b], 1);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < nb; b += ST)
+    if (h[b]) atomicAdd(&bl.work[b], h[b]);
+}
+
+__global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __restrict__ pairs) {
+  __shared__ int start[kMaxBuckets + 1];
+  __shared__ int h[kMaxBuckets];
+  __shared__ int s_wave[ST / 64];
+  int64_t base;
+  const BucketList bl = trial_list(all, base);
+  int off[9], lo, hi;
+  const int m = pack_offsets(bl.counts, bl.nh, bl.cap, off);
+  bucket_share(m, lo, hi);
+  if (lo == hi && blockIdx.x > 0) return;  // uniform; workgroup 0 writes the starts of an empty list too
+  const int nb = bl.nh * bl.rows, t = threadIdx.x;
+  const int* totals = bl.work;
+  int* cursor = bl.work + kMaxBuckets;
+  int* starts = bl.work + 2 * kMaxBuckets;
+  // exclusive sums of the totals: PER consecutive buckets to a thread
+  constexpr int PER = (kMaxBuckets + ST - 1) / ST;
+  int own[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int b = t * PER + q;
+    own[q] = b < nb ? totals[b] : 0;
+    sum += own[q];
+  }
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(incl, o);
+    if ((t & 63) >= o) incl += u;
+  }
+  if ((t & 63) == 63) s_wave[t >> 6] = incl;
+  __syncthreads();
+  int at = incl - sum;
+  for (int q = 0; q < (t >> 6); ++q) at += s_wave[q];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int b = t * PER + q;
+    if (b < nb) {
+      start[b] = at;
+      h[b] = 0;
+      if (blockIdx.x == 0) starts[b] = at;
+      at += own[q];
+    }
+  }
+  if (blockIdx.x == 0 && t == 0) starts[nb] = m;
+  __syncthreads();
+  for (int i = lo + t; i < hi; i += ST) {
+    int b;
+    bucket_record(bl, off, i, b);
+    atomicAdd(&h[b], 1);
+  }
+  __syncthreads();
+  for (int b = t; b < nb; b += ST) {
+    if (h[b]) start[b] += atomicAdd(&cursor[b], h[b]);
+    h[b] = 0;
+  }
+  __syncthreads();
+  for (int i = lo + t; i < hi; i += ST) {
+    int b;
+    const int4 rec = bucket_record(bl, off, i, b);
+    pairs[base + start[b] + atomicAdd(&h[b], 1)] = make_int2(rec.z, rec.w);
+  }
+}
+
+// Stable LSD radix sort by r of c pairs in memory by one workgroup; returns the
+// buffer that holds the result.
+__device__ int2* bucket_radix(int2* a, int2* tmp, int c, int passes, int* hist, int (*wcnt)[256]) {
+  const int t = threadIdx.x, w = t >> 6;
+  __shared__ int s_wave[ST / 64];
+  int2 *src = a, *dst = tmp;
+  for (int p = 0; p < passes; ++p) {
+    const int shift = 8 * p;
+    hist[t] = 0;
+#pragma unroll
+    for (int q = 0; q < ST / 64; ++q) wcnt[q][t] = 0;
+    __syncthreads();
+    for (int i = t; i < c; i += ST) atomicAdd(&hist[((unsigned)src[i].x >> shift) & 255u], 1);
+    __syncthreads();
+    const int own = hist[t];
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if ((t & 63) >= o) incl += u;
+    }
+    if ((t & 63) == 63) s_wave[w] = incl;
+    __syncthreads();
+    for (int q = 0; q < w; ++q) incl += s_wave[q];
+    hist[t] = incl - own;
+    __syncthreads();
+    for (int i0 = 0; i0 < c; i0 += ST) {
+      const int i = i0 + t;
+      const bool valid = i < c;
+      const int2 v = valid ? src[i] : make_int2(0, 0);
+      const int d = valid ? (int)(((unsigned)v.x >> shift) & 255u) : 0;
+      unsigned long long peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const unsigned long long m1 = __ballot((d >> b) & 1);
+        peers &= ((d >> b) & 1) ? m1 : ~m1;
+      }
+      const int rank =
+          __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
+      if (valid && rank == 0) wcnt[w][d] = __popcll(peers);
+      __syncthreads();
+      if (valid) {
+        int pos = hist[d] + rank;
+        for (int q = 0; q < w; ++q) pos += wcnt[q][d];
+        dst[pos] = v;
+      }
+      __syncthreads();
+      int add = 0;
+#pragma unroll
+      for (int q = 0; q < ST / 64; ++q) {
+        add += wcnt[q][t];
+        wcnt[q][t] = 0;
+      }
+      hist[t] += add;
+      __syncthreads();
+    }
+    int2* x = src;
+    src = dst;
+    dst = x;
+  }
+  return src;
+}
+
+// Orders bucket blockIdx.x and writes its records; records past out_cap are
+// dropped.  With counts_out the counts go out too (to page-locked memory, like out).
+__global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __restrict__ pairs, int2* __restrict__ tmp,
+                                                    int passes, int64_t out_cap, int4* __restrict__ out,
+                                                    int32_t* __restrict__ counts_out) {
+  __shared__ unsigned long long keys[kBucketLds];
+  int64_t base;
+  const BucketList bl = trial_list(all, base);
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int* starts = bl.work + 2 * kMaxBuckets;
+  const int s0 = starts[b], c = starts[b + 1] - s0;
+  if (counts_out && b == 0 && t < bl.nh) counts_out[t] = bl.counts[t];
+  if (c <= 0) return;  // uniform; its total and cursor are zero
+  if (t == 0) {
+    bl.work[b] = 0;
+    bl.work[kMaxBuckets + b] = 0;
+  }
+  const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
+  int2* mine = pairs + base + s0;
+  int4* dst = out + base + s0;
+  const int64_t room = out_cap - (base + s0);
+  if (c > kBucketLds) {
+    int* h = reinterpret_cast<int*>(keys);
+    const int2* r = bucket_radix(mine, tmp + base + s0, c, passes, h, reinterpret_cast<int(*)[256]>(h + 256));
+    for (int i = t; i < c; i += ST)
+      if (i < room) dst[i] = make_int4(harm, z, r[i].x, r[i].y);
+    return;
+  }
+  int N = 64;
+  while (N < c) N <<= 1;
+  for (int i = t; i < N; i += ST) {
+    const int2 v = i < c ? mine[i] : make_int2(-1, -1);  // padding orders last: r >= 0
+    keys[i] = ((unsigned long long)(unsigned)v.x << 32) | (unsigned)v.y;
+  }
+  __syncthreads();
+  // bitonic sort; pairs at a distance of up to 64 stay within a wave's 128 keys
+  for (int size = 2; size <= N; size <<= 1) {
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      for (int q = t; q < N / 2; q += ST) {
+        const int i = 2 * q - (q & (d - 1)), j = i + d;
+        const unsigned long long x = keys[i], y = keys[j];
+        if ((x > y) == ((i & size) == 0)) {
+          keys[i] = y;
+          keys[j] = x;
+        }
+      }
+      if (d > 64 || (d == 1 && size >= 128))
+        __syncthreads();
+      else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < c; i += ST)
+    if (i < room) dst[i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
+}
+
 // The ordered records and the counts written straight into page-locked host
 // memory (device-visible pointers), so the host waits once: records
-// [0, min(total, out_cap)) of `sorted` (each plane limited to keep records
-// when keep > 0: `sorted` is then the top-k output), counts[0 .. nh).
+// [0, min(total, out_cap)) of `sorted`, counts[0 .. nh).
 __global__ __launch_bounds__(ST) void k_copy_out(const int4* __restrict__ sorted, int cap, int nh,
-                                                 const int32_t* __restrict__ counts, int out_cap, int keep,
+                                                 const int32_t* __restrict__ counts, int out_cap,
                                                  int4* __restrict__ out, int32_t* __restrict__ counts_out) {
   int off[9];
-  const int m = min(pack_offsets(counts, nh, cap, off, keep), out_cap);
+  const int m = min(pack_offsets(counts, nh, cap, off), out_cap);
   if (blockIdx.x == 0 && (int)threadIdx.x < nh) counts_out[threadIdx.x] = counts[threadIdx.x];
   for (int i = blockIdx.x * ST + threadIdx.x; i < m; i += gridDim.x * ST) out[i] = sorted[i];
 }
@@ -342,18 +641,18 @@ __global__ __launch_bounds__(ST) void k_copy_out(const int4* __restrict__ sorted
 }  // namespace
 
 hipError_t launch_copy_out(const fdas_cand* sorted, int cap, int nh, const int32_t* counts, int out_cap,
-                           fdas_cand* out, int32_t* counts_out, hipStream_t s, int keep) {
+                           fdas_cand* out, int32_t* counts_out, hipStream_t s) {
   const int blocks = std::max(1, std::min(1024, (nh * cap + ST - 1) / ST));
   hipLaunchKernelGGL(k_copy_out, dim3(blocks), dim3(ST), 0, s, reinterpret_cast<const int4*>(sorted), cap, nh,
-                     counts, out_cap, keep, reinterpret_cast<int4*>(out), counts_out);
+                     counts, out_cap, reinterpret_cast<int4*>(out), counts_out);
   return hipGetLastError();
 }
 
 hipError_t launch_topk(const fdas_cand* sorted, int cap, int nh, const int32_t* counts, int top_k, fdas_cand* out,
-                       hipStream_t s) {
+                       int32_t* counts_out, hipStream_t s) {
   if (top_k <= 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_topk, dim3(nh), dim3(TK), 0, s, reinterpret_cast<const int4*>(sorted), cap, nh, counts, top_k,
-                     reinterpret_cast<int4*>(out));
+                     reinterpret_cast<int4*>(out), counts_out);
   return hipGetLastError();
 }
 
@@ -369,6 +668,26 @@ int sort_tile_count(int m) { return (m + TILE - 1) / TILE; }
 int sort_passes(int rows, int bits_r) {
   const int slot_bits = 32 - __builtin_clz((unsigned)(8 * rows));  // covers (k-1)*rows + row < 8*rows
   return (slot_bits + bits_r + 7) / 8;
+}
+
+bool sort_buckets(int cap) { return cap <= kBucketCap; }
+
+size_t bucket_work_ints(int trials) { return (size_t)trials * kBucketInts; }
+
+hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
+                              int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
+                              int* work, fdas_cand* out, int32_t* counts_out, hipStream_t s) {
+  if (nh < 1 || rows < 1 || nh * rows > kMaxBuckets || trials < 1 || !work) return hipErrorInvalidValue;
+  const BucketList bl{reinterpret_cast<const int4*>(planes), counts, tab, cap, nh, rows, z_max, work};
+  // the scratch records hold the scattered pairs and, after them, the radix passes' other buffer
+  int2* pairs = reinterpret_cast<int2*>(scratch);
+  int2* tmp = pairs + most;
+  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)nh * cap + 1023) / 1024));
+  hipLaunchKernelGGL(k_bucket_count, dim3(wgs, trials), dim3(ST), 0, s, bl);
+  hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, pairs);
+  hipLaunchKernelGGL(k_bucket_sort, dim3((unsigned)(nh * rows), trials), dim3(ST), 0, s, bl, pairs, tmp,
+                     (bits_r + 7) / 8, out_cap, reinterpret_cast<int4*>(out), counts_out);
+  return hipGetLastError();
 }
 
 hipError_t launch_sort_candidates(const fdas_cand* planes, int cap, int nh, const int32_t* counts, int rows,
