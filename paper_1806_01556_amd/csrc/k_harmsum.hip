@@ -507,8 +507,9 @@ constexpr int RING = DEPTH / 2 + 3;  // > source rows of one harmonic first used
 
 __host__ __device__ constexpr int src_row(int r, int m, int Z) { return (r - Z) / m + Z; }  // C truncation
 __host__ __device__ constexpr int slot_of(int r, int m, int Z) { return (src_row(r, m, Z) - src_row(0, m, Z)) % RING; }
-__host__ __device__ constexpr bool starts(int r, int m, int Z) {
-  return r == 0 || src_row(r, m, Z) != src_row(r - 1, m, Z);
+// row r of a segment that begins at r0 needs harmonic m's next source row
+__host__ __device__ constexpr bool starts(int r, int m, int Z, int r0) {
+  return r == r0 || src_row(r, m, Z) != src_row(r - 1, m, Z);
 }
 __host__ __device__ constexpr bool needs_hi(int m) { return m != 4 && m != 8; }
 
@@ -522,11 +523,11 @@ struct HsState {
 };
 
 // loads of the stretched source rows first needed at row R
-template <int Z, int NH, int R, int M>
+template <int Z, int NH, int R0, int R, int M>
 __device__ __forceinline__ void hs_issue_m(HsState<NH>& st, const float* __restrict__ fop, int64_t ld,
                                            const int (&lo)[NH + 1]) {
   if constexpr (M <= NH) {
-    if constexpr (starts(R, M, Z)) {
+    if constexpr (starts(R, M, Z, R0)) {
       constexpr int S = src_row(R, M, Z);
       constexpr int SL = slot_of(R, M, Z);
       const float* src = fop + (size_t)S * ld + lo[M];
@@ -539,24 +540,24 @@ __device__ __forceinline__ void hs_issue_m(HsState<NH>& st, const float* __restr
         if constexpr (needs_hi(M)) st.hi_ring[M][SL] = src[1];
       }
     }
-    hs_issue_m<Z, NH, R, M + 1>(st, fop, ld, lo);
+    hs_issue_m<Z, NH, R0, R, M + 1>(st, fop, ld, lo);
   }
 }
 
-template <int Z, int NH, int R>
+template <int Z, int NH, int R0, int R1, int R>
 __device__ __forceinline__ void hs_issue(HsState<NH>& st, const float* __restrict__ fop, int64_t ld, int j0,
                                          const int (&lo)[NH + 1]) {
-  if constexpr (R < 2 * Z + 1) {
+  if constexpr (R < R1) {
     st.ring1[R % DEPTH] = *reinterpret_cast<const float4*>(fop + (size_t)R * ld + j0);
-    hs_issue_m<Z, NH, R, 2>(st, fop, ld, lo);
+    hs_issue_m<Z, NH, R0, R, 2>(st, fop, ld, lo);
   }
 }
 
-template <int Z, int NH, int R, int M>
+template <int Z, int NH, int R0, int R, int M>
 __device__ __forceinline__ void hs_harm(HsState<NH>& st, float (&hp)[4], bool& hit, const int (&rmod)[NH + 1],
                                         const float* __restrict__ s_ta) {
   if constexpr (M <= NH) {
-    if constexpr (starts(R, M, Z)) {
+    if constexpr (starts(R, M, Z, R0)) {
       constexpr int SL = slot_of(R, M, Z);
       const float vl = st.lo_ring[M][SL];
       if constexpr (M == 2) {
@@ -580,34 +581,34 @@ __device__ __forceinline__ void hs_harm(HsState<NH>& st, float (&hp)[4], bool& h
     for (int a = 0; a < 4; ++a) hp[a] = hp[a] + st.val[M][a];
     // one compare per harmonic: any of the 4 columns above threshold (NaN never is)
     hit = hit || fmaxf(fmaxf(hp[0], hp[1]), fmaxf(hp[2], hp[3])) > t;
-    hs_harm<Z, NH, R, M + 1>(st, hp, hit, rmod, s_ta);
+    hs_harm<Z, NH, R0, R, M + 1>(st, hp, hit, rmod, s_ta);
   }
 }
 
-template <int Z, int NH, int R>
+template <int Z, int NH, int R0, int R1, int R>
 __device__ __forceinline__ void hs_rows(HsState<NH>& st, const float* __restrict__ fop, int64_t ld, int j0,
                                         const int (&lo)[NH + 1], const int (&rmod)[NH + 1],
                                         const float* __restrict__ s_ta) {
   // take row R out of its ring slot before the slot is refilled with row R + DEPTH
   const float4 v = st.ring1[R % DEPTH];
-  hs_issue<Z, NH, R + DEPTH>(st, fop, ld, j0, lo);
+  hs_issue<Z, NH, R0, R1, R + DEPTH>(st, fop, ld, j0, lo);
   float hp[4] = {v.x, v.y, v.z, v.w};
   bool hit = fmaxf(fmaxf(hp[0], hp[1]), fmaxf(hp[2], hp[3])) > s_ta[R * 8];
-  hs_harm<Z, NH, R, 2>(st, hp, hit, rmod, s_ta);
+  hs_harm<Z, NH, R0, R, 2>(st, hp, hit, rmod, s_ta);
   st.hitmask[R / 32] |= hit ? (1u << (R % 32)) : 0u;
   // Keep the software pipeline as written: the row's sums are consumed here
   // (an empty asm that reads and rewrites the hit word), and no instruction
   // crosses the row boundary.
   __asm__ volatile("" : "+v"(st.hitmask[R / 32]));
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (R + 1 < 2 * Z + 1) hs_rows<Z, NH, R + 1>(st, fop, ld, j0, lo, rmod, s_ta);
+  if constexpr (R + 1 < R1) hs_rows<Z, NH, R0, R1, R + 1>(st, fop, ld, j0, lo, rmod, s_ta);
 }
 
-template <int Z, int NH, int R>
+template <int Z, int NH, int R0, int R1, int R>
 __device__ __forceinline__ void hs_prologue(HsState<NH>& st, const float* __restrict__ fop, int64_t ld, int j0,
                                             const int (&lo)[NH + 1]) {
-  hs_issue<Z, NH, R>(st, fop, ld, j0, lo);
-  if constexpr (R + 1 < DEPTH) hs_prologue<Z, NH, R + 1>(st, fop, ld, j0, lo);
+  hs_issue<Z, NH, R0, R1, R>(st, fop, ld, j0, lo);
+  if constexpr (R + 1 < R0 + DEPTH) hs_prologue<Z, NH, R0, R1, R + 1>(st, fop, ld, j0, lo);
 }
 
 // Phase 1 over all columns [0, n) in groups of 4 (the last group may be
@@ -615,9 +616,9 @@ __device__ __forceinline__ void hs_prologue(HsState<NH>& st, const float* __rest
 // ld >= n and ld % 4 == 0; a source column j/k + 1 read for k >= 2 is at most
 // (n-1)/2 + 1 <= ld - 1.  Values read beyond column n - 1 only reach columns
 // >= n, which phase 2 never emits.
-// Phase 1 for one thread: columns j0..j0+3 of a plane with n columns.
-// Returns the bit mask of rows holding a cell above threshold (3 words).
-template <int Z, int NH>
+// Phase 1 for one thread: rows [R0, R1) of columns j0..j0+3 of a plane with n
+// columns.  Returns the bit mask of rows holding a cell above threshold (3 words).
+template <int Z, int NH, int R0 = 0, int R1 = 2 * Z + 1>
 __device__ __forceinline__ void hs_phase1_thread(const float* __restrict__ fop, int64_t ld, int j0,
                                                  const float* __restrict__ s_ta, unsigned (&mask)[3]) {
   int lo[NH + 1], rmod[NH + 1];
@@ -628,8 +629,8 @@ __device__ __forceinline__ void hs_phase1_thread(const float* __restrict__ fop, 
   }
   HsState<NH> st;
   st.hitmask[0] = st.hitmask[1] = st.hitmask[2] = 0u;
-  hs_prologue<Z, NH, 0>(st, fop, ld, j0, lo);
-  hs_rows<Z, NH, 0>(st, fop, ld, j0, lo, rmod, s_ta);
+  hs_prologue<Z, NH, R0, R1, R0>(st, fop, ld, j0, lo);
+  hs_rows<Z, NH, R0, R1, R0>(st, fop, ld, j0, lo, rmod, s_ta);
   mask[0] = st.hitmask[0];
   mask[1] = st.hitmask[1];
   mask[2] = st.hitmask[2];
@@ -658,7 +659,14 @@ __device__ __forceinline__ void hs_flush_entries(const int4* __restrict__ s_ent,
 // ld >= n and ld % 4 == 0; a source column j/k + 1 read for k >= 2 is at most
 // (n-1)/2 + 1 <= ld - 1.  Values read beyond column n - 1 only reach columns
 // >= n, which phase 2 never emits.
-template <int Z, int NH, int TH = HS_THREADS>
+// SEGS > 1: blockIdx.y is one of SEGS segments of the rows.  A thread walks its
+// rows one memory latency after another (8 rows ahead), so a spectrum too short
+// to fill the chip takes the time of 85 rows whatever its length: up to 2^18
+// bins (1024 waves) the rows go to four workgroups.  Measured phase 1: 16,384
+// bins 18.8 -> 8.0 us, 200,003 bins 20.4 -> 18.8 us.
+constexpr int kSegRows = 4;
+constexpr int kSegMaxN = 1 << 18;
+template <int Z, int NH, int TH = HS_THREADS, int SEGS = 1>
 __global__ __launch_bounds__(TH) void k_harmsum_z(const float* __restrict__ fop, int64_t ld, int n,
                                                           const int* __restrict__ tile_of_block,
                                                           const float* __restrict__ ta, int4* __restrict__ hitrows,
@@ -677,7 +685,18 @@ __global__ __launch_bounds__(TH) void k_harmsum_z(const float* __restrict__ fop,
   if (tile >= 0 && g < groups) {
     const int j0 = 4 * g;
     unsigned mask[3];
-    hs_phase1_thread<Z, NH>(fop, ld, j0, s_ta, mask);
+    if constexpr (SEGS == 1) {
+      hs_phase1_thread<Z, NH>(fop, ld, j0, s_ta, mask);
+    } else {
+      static_assert(SEGS == 4, "four row segments");
+      constexpr int Q1 = ROWS / 4, Q2 = ROWS / 2, Q3 = 3 * ROWS / 4;
+      switch (blockIdx.y) {
+        case 0: hs_phase1_thread<Z, NH, 0, Q1>(fop, ld, j0, s_ta, mask); break;
+        case 1: hs_phase1_thread<Z, NH, Q1, Q2>(fop, ld, j0, s_ta, mask); break;
+        case 2: hs_phase1_thread<Z, NH, Q2, Q3>(fop, ld, j0, s_ta, mask); break;
+        default: hs_phase1_thread<Z, NH, Q3, ROWS>(fop, ld, j0, s_ta, mask); break;
+      }
+    }
     if (mask[0] | mask[1] | mask[2]) {
       const int pos = atomicAdd(&s_nent, 1);
       s_ent[pos] = make_int4(j0, (int)mask[0], (int)mask[1], (int)mask[2]);
@@ -1162,11 +1181,16 @@ hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, in
   if (z_max == 42 && index == FDAS_HSUM_STRETCH) {
     // two-phase fast path for the 85-template plane
     const unsigned blocks = (unsigned)wk.blocks;
+    const bool segs = n <= kSegMaxN && (n + 3) / 4 * kSegRows <= wk.hit_cap;
     switch (n_harm) {
 #define FDAS_HSZ_CASE(NH)                                                                                          \
   case NH:                                                                                                         \
-    hipLaunchKernelGGL((k_harmsum_z<42, NH>), dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, nn, wk.tile_of_block, \
-                       ta, wk.hitrows, wk.hitrow_count);                                                           \
+    if (segs)                                                                                                      \
+      hipLaunchKernelGGL((k_harmsum_z<42, NH, HS_THREADS, kSegRows>), dim3(blocks, kSegRows), dim3(HS_THREADS), 0, \
+                         s, fop, ld, nn, wk.tile_of_block, ta, wk.hitrows, wk.hitrow_count);                       \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_harmsum_z<42, NH>), dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, nn,                 \
+                         wk.tile_of_block, ta, wk.hitrows, wk.hitrow_count);                                       \
     hipLaunchKernelGGL((k_harmsum_emit<42, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, nn, wk.hitrows,   \
                        wk.hitrow_count, ta, cands, cap, counts);                                                   \
     break;
