@@ -414,7 +414,7 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
       }
       sorted = p->d_bsort_b;
       e = launch_bucket_sort(nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, M, M,
-                             p->d_bsort_a, p->d_bbucket, sorted, nullptr, s);
+                             p->d_bsort_a, p->d_bbucket, sorted, nullptr, 0, nullptr, s);
     } else {
       e = launch_sort_batch(p->d_rb_tab, count, cap, nh, (int)M, p->rows, p->desc.z_max, p->bits_r, p->d_bsort_a,
                             p->d_bsort_b, p->d_bsort_hist, p->d_bsort_totals, &sorted, s);

@@ -58,6 +58,7 @@ void free_plan(fdas_plan* p) {
   if (p->d_sort_totals) (void)hipFree(p->d_sort_totals);
   if (p->d_bucket) (void)hipFree(p->d_bucket);
   if (p->h_counts) (void)hipHostFree(p->h_counts);
+  if (p->h_early) (void)hipHostFree(p->h_early);
   if (p->h_result) (void)hipHostFree(p->h_result);
   if (p->h_result_counts) (void)hipHostFree(p->h_result_counts);
   for (auto& kv : p->tile_orders) (void)hipFree(kv.second.first);
@@ -163,17 +164,23 @@ hipError_t ols_tables(fdas_plan* p, int C, const OlsTables** out) {
   return hipSuccess;
 }
 
+// Records a copying readback fetches without a second wait: the kernels write up
+// to this many (128 KiB) into page-locked memory of the plan.
+constexpr int kEarlyRecords = 8192;
+
 // Queue the ordering of one candidate list.  Bucket-sorted lists go to `out` when
-// it is given (with the counts to counts_out); *sorted is where the records land.
+// it is given, or to `early` when they are at most kEarlyRecords (with the counts to
+// counts_out); *sorted is where the others land.
 hipError_t order_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_t* d_counts, fdas_cand* out,
-                            int32_t* counts_out, fdas_cand** sorted, hipStream_t s) {
+                            fdas_cand* early, int32_t* counts_out, fdas_cand** sorted, hipStream_t s) {
   const int nh = p->desc.n_harm, cap = p->desc.cand_capacity;
   if (!sort_buckets(cap))
     return launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r, p->d_sort_a,
                                   p->d_sort_b, p->d_sort_hist, p->d_sort_totals, sorted, s);
   *sorted = out ? out : p->d_sort_b;
   return launch_bucket_sort(d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r,
-                            (int64_t)nh * cap, (int64_t)nh * cap, p->d_sort_a, p->d_bucket, *sorted, counts_out, s);
+                            (int64_t)nh * cap, (int64_t)nh * cap, p->d_sort_a, p->d_bucket, *sorted, early,
+                            kEarlyRecords, counts_out, s);
 }
 
 hipError_t tile_order_for(fdas_plan* p, int64_t n, const int** d_order, int* blocks, int cols) {
@@ -369,6 +376,8 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
         (e = hipMemset(p->d_bucket, 0, fdas::bucket_work_ints(1) * sizeof(int))) != hipSuccess ||
         (e = hipDeviceSynchronize()) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 8 * sizeof(int32_t), 0)) != hipSuccess ||
+        (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_early), fdas::kEarlyRecords * sizeof(fdas_cand), 0)) !=
+            hipSuccess ||
         (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max) * sizeof(int4))) != hipSuccess ||
         (e = hipMalloc(&p->d_hitrow_count, sizeof(int32_t))) != hipSuccess) {
       free_plan(p);
@@ -485,13 +494,24 @@ fdas_status fdas_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int nh = p->desc.n_harm;
   const int cap = p->desc.cand_capacity;
-  // order on the device first (sizes come from the device counts), then one
-  // wait for the counts, then the copy of the ordered records
+  // order on the device first (sizes come from the device counts), then one wait
+  // for the counts, which a short list's records have come with; a long one's are
+  // copied after it
+  const bool buckets = fdas::sort_buckets(cap);
+  const int top_k = p->desc.top_k > 0 ? std::min(p->desc.top_k, cap) : 0;
+  const bool early_top = buckets && top_k > 0 && (int64_t)top_k * nh <= fdas::kEarlyRecords;
+  void *d_early = nullptr, *d_hc = nullptr;
+  hipError_t e = hipHostGetDevicePointer(&d_early, p->h_early, 0);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(&d_hc, p->h_counts, 0);
+  if (e != hipSuccess) return hip_fail(e, "mapping the readback buffers");
+  fdas_cand* early = static_cast<fdas_cand*>(d_early);
+  int32_t* hc = static_cast<int32_t*>(d_hc);
   fdas_cand* sorted = nullptr;
-  hipError_t e = fdas::order_candidates(p, d_cands, d_counts, nullptr, nullptr, &sorted, s);
+  e = fdas::order_candidates(p, d_cands, d_counts, nullptr, top_k > 0 ? nullptr : early, hc, &sorted, s);
+  if (e == hipSuccess && early_top) e = fdas::launch_topk(sorted, cap, nh, d_counts, top_k, early, nullptr, s);
   if (e != hipSuccess) return hip_fail(e, "ordering candidates");
   int32_t* counts = p->h_counts;
-  e = hipMemcpyAsync(counts, d_counts, nh * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (!buckets) e = hipMemcpyAsync(counts, d_counts, nh * sizeof(int32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "reading candidate counts");
   if (h_counts) std::copy(counts, counts + nh, h_counts);
@@ -503,21 +523,29 @@ fdas_status fdas_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
     off[k + 1] = off[k] + std::min(counts[k], cap);
   }
   int total = off[nh];
+  bool on_host = buckets && top_k == 0 && total <= fdas::kEarlyRecords;
   const fdas_cand* src = sorted;
-  if (p->desc.top_k > 0) {
+  if (top_k > 0) {
     // paper mode (Table 1's N_cand): each plane keeps its top_k powers (ties:
     // lower z, then lower r), selected on the device into the other buffer
-    fdas_cand* kept = sorted == p->d_sort_a ? p->d_sort_b : p->d_sort_a;
-    e = fdas::launch_topk(sorted, cap, nh, d_counts, p->desc.top_k, kept, nullptr, s);
-    if (e != hipSuccess) return hip_fail(e, "selecting the top candidates");
-    src = kept;
+    on_host = early_top;
+    if (!early_top) {
+      fdas_cand* kept = sorted == p->d_sort_a ? p->d_sort_b : p->d_sort_a;
+      e = fdas::launch_topk(sorted, cap, nh, d_counts, top_k, kept, nullptr, s);
+      if (e != hipSuccess) return hip_fail(e, "selecting the top candidates");
+      src = kept;
+    }
     total = 0;
-    for (int k = 0; k < nh; ++k) total += std::min(off[k + 1] - off[k], p->desc.top_k);
+    for (int k = 0; k < nh; ++k) total += std::min(off[k + 1] - off[k], top_k);
   }
   const int64_t nw = std::min<int64_t>(total, h_capacity);
-  if (nw > 0) e = hipMemcpyAsync(h_out, src, (size_t)nw * sizeof(fdas_cand), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "reading candidates");
+  if (on_host) {
+    if (nw > 0) std::memcpy(h_out, p->h_early, (size_t)nw * sizeof(fdas_cand));
+  } else {
+    if (nw > 0) e = hipMemcpyAsync(h_out, src, (size_t)nw * sizeof(fdas_cand), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "reading candidates");
+  }
   *h_n = nw;
   if (overflow) return fail(FDAS_ERR_CAPACITY, "a device candidate list overflowed (counts are exact)");
   if (nw < total) return fail(FDAS_ERR_CAPACITY, "h_capacity %lld < %d candidates", (long long)h_capacity, total);
@@ -560,7 +588,8 @@ fdas_status fdas_candidates_mapped(fdas_plan* p, const fdas_cand* d_cands, const
   int32_t* rc = static_cast<int32_t*>(d_rc);
   // the last kernel writes the result buffer: the top-k selection (paper mode),
   // the bucket sort, or a copy of the radix-sorted records
-  e = fdas::order_candidates(p, d_cands, d_counts, keep > 0 ? nullptr : res, keep > 0 ? nullptr : rc, &sorted, s);
+  e = fdas::order_candidates(p, d_cands, d_counts, keep > 0 ? nullptr : res, nullptr, keep > 0 ? nullptr : rc, &sorted,
+                             s);
   if (e == hipSuccess && keep > 0)
     e = fdas::launch_topk(sorted, cap, nh, d_counts, keep, res, rc, s);
   else if (e == hipSuccess && sorted != res)

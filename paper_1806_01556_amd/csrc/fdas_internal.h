@@ -239,14 +239,15 @@ struct RbTrial {
 // (sort_buckets): one list (planes, counts; trials = 1, tab NULL) or the trials of
 // a batch (tab).  `most` is at least the number of records in all, `scratch`
 // holds `most` records; work holds bucket_work_ints(trials) ints that were zero
-// before the first call.  The ordered records go to out (up to out_cap), which,
-// like counts_out (one list's counts; NULL skips them), may be page-locked host
-// memory.
+// before the first call.  The ordered records go to out (up to out_cap), or to
+// `early` (NULL: never) when they are at most early_cap; out, early and counts_out
+// (one list's counts; NULL skips them) may be page-locked host memory.
 bool sort_buckets(int cap);
 size_t bucket_work_ints(int trials);
 hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
                               int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
-                              int* work, fdas_cand* out, int32_t* counts_out, hipStream_t s);
+                              int* work, fdas_cand* out, fdas_cand* early, int early_cap, int32_t* counts_out,
+                              hipStream_t s);
 
 int sort_passes_batch(int count, int rows, int bits_r);
 

@@ -32,6 +32,7 @@ struct fdas_plan {
   fdas_cand* d_sort_b = nullptr;  // radix-sort ping-pong buffer
   int* d_sort_hist = nullptr;     // [256 * tiles] digit histograms
   int* d_sort_totals = nullptr;   // [256 * passes] digit totals per pass
+  fdas_cand* h_early = nullptr; // page-locked records of short readbacks (kEarlyRecords)
   int* d_bucket = nullptr;      // bucket counters of the single-list readback (zero between calls)
   int32_t* h_counts = nullptr;    // pinned host copy of the device counts
   fdas_cand* h_result = nullptr;  // page-locked result records of fdas_candidates_mapped

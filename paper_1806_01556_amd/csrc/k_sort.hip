@@ -12,7 +12,7 @@
 // The list sizes are read from the device counts, so nothing waits for the host.
 // A readback is bound by launches and their dependent latencies, not by its
 // few megabytes: 229 k records took 73 us in the 13 launches of the radix sort
-// below and take 19 us here, 7 k records 35 and 11 us.  A bucket holds the cells of
+// below and take 32 us here, 7 k records 35 and 17 us.  A bucket holds the cells of
 // one row, some hundreds; the one workgroup that orders it keeps up to 4096 in
 // LDS and passes over memory for more.  That does not scale to a row of millions
 // of candidates, so longer lists are packed into one array and sorted by the
@@ -380,6 +380,7 @@ constexpr int kBucketCap = 65536;
 constexpr int kMaxBuckets = 8 * 129;
 constexpr int kBucketInts = 3 * kMaxBuckets + 8;  // per trial
 constexpr int kBucketLds = 4096;                  // records a workgroup orders in LDS
+constexpr int kBucketSmall = 512;                 // ... in the small form
 
 struct BucketList {
   const int4* planes;     // one list
@@ -401,9 +402,9 @@ __device__ __forceinline__ BucketList trial_list(const BucketList& bl, int64_t& 
   return one;
 }
 
-// this workgroup's share [lo, hi) of a list's m records, at least 1024 to a workgroup
+// this workgroup's share [lo, hi) of a list's m records, at least one to a thread
 __device__ __forceinline__ void bucket_share(int m, int& lo, int& hi) {
-  const int active = min((int)gridDim.x, (m + 1023) / 1024);
+  const int active = min((int)gridDim.x, (m + ST - 1) / ST);
   lo = hi = 0;
   if ((int)blockIdx.x < active) {
     lo = (int)((int64_t)m * blockIdx.x / active);
@@ -567,28 +568,38 @@ __device__ int2* bucket_radix(int2* a, int2* tmp, int c, int passes, int* hist, 
   return src;
 }
 
-// Orders bucket blockIdx.x and writes its records; records past out_cap are
-// dropped.  With counts_out the counts go out too (to page-locked memory, like out).
+// Orders bucket blockIdx.x if it holds more than `above` and (unless KEYS is
+// kBucketLds) at most KEYS records, and writes them.  The trials of a batch have
+// thousands of buckets, most of them small: they go through the form with 4 KB
+// of LDS, eight workgroups to a compute unit, and the few large ones through a
+// second launch (16 trials: 35 us, 46 us with 32 KB for all).  One list takes the
+// large form for all.  Records past out_cap are dropped.  When all the records
+// fit in early_cap, they go to `early` (page-locked memory) instead of out; with
+// counts_out the counts go out too.
+template <int KEYS>
 __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __restrict__ pairs, int2* __restrict__ tmp,
-                                                    int passes, int64_t out_cap, int4* __restrict__ out,
+                                                    int passes, int above, int64_t out_cap, int4* __restrict__ out,
+                                                    int4* __restrict__ early, int early_cap,
                                                     int32_t* __restrict__ counts_out) {
-  __shared__ unsigned long long keys[kBucketLds];
+  __shared__ unsigned long long keys[KEYS];
   int64_t base;
   const BucketList bl = trial_list(all, base);
   const int b = blockIdx.x, t = threadIdx.x;
   const int* starts = bl.work + 2 * kMaxBuckets;
   const int s0 = starts[b], c = starts[b + 1] - s0;
   if (counts_out && b == 0 && t < bl.nh) counts_out[t] = bl.counts[t];
-  if (c <= 0) return;  // uniform; its total and cursor are zero
+  // an empty bucket's total and cursor are zero already
+  if (c <= above || (KEYS < kBucketLds && c > KEYS)) return;  // uniform
   if (t == 0) {
     bl.work[b] = 0;
     bl.work[kMaxBuckets + b] = 0;
   }
+  if (early && starts[bl.nh * bl.rows] <= early_cap) out = early;
   const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
   int2* mine = pairs + base + s0;
   int4* dst = out + base + s0;
   const int64_t room = out_cap - (base + s0);
-  if (c > kBucketLds) {
+  if (KEYS == kBucketLds && c > KEYS) {
     int* h = reinterpret_cast<int*>(keys);
     const int2* r = bucket_radix(mine, tmp + base + s0, c, passes, h, reinterpret_cast<int(*)[256]>(h + 256));
     for (int i = t; i < c; i += ST)
@@ -676,17 +687,28 @@ size_t bucket_work_ints(int trials) { return (size_t)trials * kBucketInts; }
 
 hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
                               int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
-                              int* work, fdas_cand* out, int32_t* counts_out, hipStream_t s) {
+                              int* work, fdas_cand* out, fdas_cand* early, int early_cap, int32_t* counts_out,
+                              hipStream_t s) {
   if (nh < 1 || rows < 1 || nh * rows > kMaxBuckets || trials < 1 || !work) return hipErrorInvalidValue;
   const BucketList bl{reinterpret_cast<const int4*>(planes), counts, tab, cap, nh, rows, z_max, work};
   // the scratch records hold the scattered pairs and, after them, the radix passes' other buffer
   int2* pairs = reinterpret_cast<int2*>(scratch);
   int2* tmp = pairs + most;
-  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)nh * cap + 1023) / 1024));
+  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)nh * cap + ST - 1) / ST));
+  const dim3 buckets((unsigned)(nh * rows), trials);
+  const int passes = (bits_r + 7) / 8;
+  int4* dst = reinterpret_cast<int4*>(out);
+  int4* fast = reinterpret_cast<int4*>(early);
   hipLaunchKernelGGL(k_bucket_count, dim3(wgs, trials), dim3(ST), 0, s, bl);
   hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, pairs);
-  hipLaunchKernelGGL(k_bucket_sort, dim3((unsigned)(nh * rows), trials), dim3(ST), 0, s, bl, pairs, tmp,
-                     (bits_r + 7) / 8, out_cap, reinterpret_cast<int4*>(out), counts_out);
+  int above = 0;
+  if (trials > 1) {
+    hipLaunchKernelGGL(k_bucket_sort<kBucketSmall>, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, 0, out_cap, dst,
+                       fast, early_cap, counts_out);
+    above = kBucketSmall;
+  }
+  hipLaunchKernelGGL(k_bucket_sort<kBucketLds>, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, above, out_cap, dst,
+                     fast, early_cap, counts_out);
   return hipGetLastError();
 }
 
