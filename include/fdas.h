@@ -65,7 +65,8 @@ typedef enum {
 
 /* Arithmetic of the direct method (the overlap-save method is always FP32).
  * The split forms carry every operand value v as hi = round16(v) and
- * lo = round16(v - hi) and each product as hi*hi + hi*lo + lo*hi on the 16-bit
+ * lo = round16(v - hi) and each product as hi*hi + hi*lo + lo*hi (BF16: and
+ * lo*lo) on the 16-bit
  * matrix cores with FP32 accumulation (FP16 operands are scaled by exact
  * powers of two per workgroup strip and per template tile). */
 typedef enum {

@@ -257,13 +257,14 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
 // ---------------------------------------------------------------------------
 // Split precision on the 16-bit matrix cores (v_mfma_f32_16x16x32_{f16,bf16}):
 // every operand value v is carried as hi = round16(v), lo = round16(v - hi),
-// and a product as hi*hi + hi*lo + lo*hi with FP32 accumulation (the lo*lo
-// term, ~2^-22 of the product for FP16, is dropped).  One instruction takes
-// 16 bins x 16 complex taps x 8 templates: K = 32 real values, lane group
-// g = lane/16 holding taps 4g..4g+3 of the 16 as (Re, Im) pairs.  FP16 has a
-// narrow exponent range, so the block's strip of X is scaled by 2^ex
-// (largest |Re|, |Im| brought to about 2^14) and each template tile by a
-// plan-chosen 2^eh; both scalings are exact and undone on the accumulator.
+// and a product as hi*hi + hi*lo + lo*hi with FP32 accumulation.  The lo*lo
+// term is ~2^-22 of a product for FP16 and dropped; for BF16 it is as large as
+// the rounding of the halves and kept (2-norm error 5.1e-6 without it, 4.0e-6
+// with, 2^22 bins 0.77 and 0.85 ms).  One instruction takes 16 bins x 32
+// distances x 16 real filters (8 |z|).  FP16 has a narrow exponent range, so the
+// block's strip of X is scaled by 2^ex (largest |Re|, |Im| brought to about 2^13,
+// a folded value below 2^15) and each template tile by a plan-chosen 2^eh; both
+// scalings are exact and undone on the accumulator.
 
 constexpr int SSUB = 2;                      // 16-bin sub-tiles per wave, 32 bins apart
 constexpr int SBLK_BINS = 128;               // 4 waves: wave w takes bins 64 (w / 2) + 16 (w % 2) + 32 s
@@ -276,6 +277,7 @@ struct Split16;
 // low: v minus half `i` of a packed pair
 template <>
 struct Split16<_Float16> {
+  static constexpr bool kLowLow = false;  // 2^-22 of a product
   typedef _Float16 v8 __attribute__((ext_vector_type(8)));
   static __device__ __forceinline__ unsigned pack(float a, float b) {
     typedef _Float16 v2 __attribute__((ext_vector_type(2)));
@@ -298,6 +300,7 @@ struct Split16<_Float16> {
 
 template <>
 struct Split16<__bf16> {
+  static constexpr bool kLowLow = true;  // up to 2^-16 of a product: as large as the halves' own rounding
   typedef __bf16 v8 __attribute__((ext_vector_type(8)));
   static __device__ __forceinline__ unsigned pack(float a, float b) {
     typedef __bf16 v2 __attribute__((ext_vector_type(2)));
@@ -406,6 +409,13 @@ __device__ __forceinline__ void split_step(v4f (&ar)[TG][SSUB], v4f (&ai)[TG][SS
       for (int s = 0; s < SSUB; ++s) {
         ar[t][s] = S::mfma(f[s].rh, bl, ar[t][s]);
         ai[t][s] = S::mfma(f[s].ih, bl, ai[t][s]);
+      }
+      if constexpr (S::kLowLow) {
+#pragma unroll
+        for (int s = 0; s < SSUB; ++s) {
+          ar[t][s] = S::mfma(f[s].rl, bl, ar[t][s]);
+          ai[t][s] = S::mfma(f[s].il, bl, ai[t][s]);
+        }
       }
       bh = nh;
       bl = nl;
