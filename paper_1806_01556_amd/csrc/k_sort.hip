@@ -380,7 +380,7 @@ constexpr int kBucketCap = 65536;
 constexpr int kMaxBuckets = 8 * 129;
 constexpr int kBucketInts = 3 * kMaxBuckets + 8;  // per trial
 constexpr int kBucketLds = 4096;                  // records a workgroup orders in LDS
-constexpr int kBucketSmall = 512;                 // ... in the small form
+constexpr int kBucketSmall = 512;                 // ... and a wave
 
 struct BucketList {
   const int4* planes;     // one list
@@ -568,20 +568,76 @@ __device__ int2* bucket_radix(int2* a, int2* tmp, int c, int passes, int* hist, 
   return src;
 }
 
-// Orders bucket blockIdx.x if it holds more than `above` and (unless KEYS is
-// kBucketLds) at most KEYS records, and writes them.  The trials of a batch have
-// thousands of buckets, most of them small: they go through the form with 4 KB
-// of LDS, eight workgroups to a compute unit, and the few large ones through a
-// second launch (16 trials: 35 us, 46 us with 32 KB for all).  One list takes the
-// large form for all.  Records past out_cap are dropped.  When all the records
-// fit in early_cap, they go to `early` (page-locked memory) instead of out; with
-// counts_out the counts go out too.
-template <int KEYS>
+// Ascending bitonic sort of N keys (a power of two, at least 64) by TH threads, t
+// this thread's index among them.  Pairs at a distance of up to 64 stay within a
+// wave's 128 keys; with one wave (TH = 64) all of them do.
+template <int TH>
+__device__ __forceinline__ void bitonic(unsigned long long* keys, int N, int t) {
+  for (int size = 2; size <= N; size <<= 1) {
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      for (int q = t; q < N / 2; q += TH) {
+        const int i = 2 * q - (q & (d - 1)), j = i + d;
+        const unsigned long long x = keys[i], y = keys[j];
+        if ((x > y) == ((i & size) == 0)) {
+          keys[i] = y;
+          keys[j] = x;
+        }
+      }
+      if (TH > 64 && (d > 64 || (d == 1 && size >= 128))) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ unsigned long long bucket_key(const int2* mine, int i, int c) {
+  const int2 v = i < c ? mine[i] : make_int2(-1, -1);  // padding orders last: r >= 0
+  return ((unsigned long long)(unsigned)v.x << 32) | (unsigned)v.y;
+}
+
+// Orders the buckets of up to kBucketSmall records, a wave each; larger ones are
+// left to k_bucket_sort.  The trials of a batch have thousands of buckets, most
+// with a few records: 16 trials 46 us with a workgroup and 32 KB of LDS for every
+// bucket, 35 with 4 KB for the small ones, 21 for both launches with a wave each.
+__global__ __launch_bounds__(ST) void k_bucket_sort_small(BucketList all, const int2* __restrict__ pairs,
+                                                          int64_t out_cap, int4* __restrict__ out) {
+  __shared__ unsigned long long s_keys[ST / 64][kBucketSmall];
+  int64_t base;
+  const BucketList bl = trial_list(all, base);
+  const int b = (int)blockIdx.x * (ST / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (b >= bl.nh * bl.rows) return;  // uniform per wave; no barrier follows
+  const int* starts = bl.work + 2 * kMaxBuckets;
+  const int s0 = starts[b], c = starts[b + 1] - s0;
+  if (c <= 0 || c > kBucketSmall) return;
+  if (lane == 0) {
+    bl.work[b] = 0;
+    bl.work[kMaxBuckets + b] = 0;
+  }
+  unsigned long long* keys = s_keys[threadIdx.x >> 6];
+  int N = 64;
+  while (N < c) N <<= 1;
+  for (int i = lane; i < N; i += 64) keys[i] = bucket_key(pairs + base + s0, i, c);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  bitonic<64>(keys, N, lane);
+  const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
+  const int64_t room = out_cap - (base + s0);
+  for (int i = lane; i < c; i += 64)
+    if (i < room) out[base + s0 + i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
+}
+
+// Orders bucket blockIdx.x if it holds more than `above` records and writes them;
+// records past out_cap are dropped.  When all the list's records fit in early_cap,
+// they go to `early` (page-locked memory) instead of out; with counts_out the
+// counts go out too.
 __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __restrict__ pairs, int2* __restrict__ tmp,
                                                     int passes, int above, int64_t out_cap, int4* __restrict__ out,
                                                     int4* __restrict__ early, int early_cap,
                                                     int32_t* __restrict__ counts_out) {
-  __shared__ unsigned long long keys[KEYS];
+  __shared__ unsigned long long keys[kBucketLds];
   int64_t base;
   const BucketList bl = trial_list(all, base);
   const int b = blockIdx.x, t = threadIdx.x;
@@ -589,7 +645,7 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __rest
   const int s0 = starts[b], c = starts[b + 1] - s0;
   if (counts_out && b == 0 && t < bl.nh) counts_out[t] = bl.counts[t];
   // an empty bucket's total and cursor are zero already
-  if (c <= above || (KEYS < kBucketLds && c > KEYS)) return;  // uniform
+  if (c <= above) return;  // uniform
   if (t == 0) {
     bl.work[b] = 0;
     bl.work[kMaxBuckets + b] = 0;
@@ -599,7 +655,7 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __rest
   int2* mine = pairs + base + s0;
   int4* dst = out + base + s0;
   const int64_t room = out_cap - (base + s0);
-  if (KEYS == kBucketLds && c > KEYS) {
+  if (c > kBucketLds) {
     int* h = reinterpret_cast<int*>(keys);
     const int2* r = bucket_radix(mine, tmp + base + s0, c, passes, h, reinterpret_cast<int(*)[256]>(h + 256));
     for (int i = t; i < c; i += ST)
@@ -608,30 +664,9 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __rest
   }
   int N = 64;
   while (N < c) N <<= 1;
-  for (int i = t; i < N; i += ST) {
-    const int2 v = i < c ? mine[i] : make_int2(-1, -1);  // padding orders last: r >= 0
-    keys[i] = ((unsigned long long)(unsigned)v.x << 32) | (unsigned)v.y;
-  }
+  for (int i = t; i < N; i += ST) keys[i] = bucket_key(mine, i, c);
   __syncthreads();
-  // bitonic sort; pairs at a distance of up to 64 stay within a wave's 128 keys
-  for (int size = 2; size <= N; size <<= 1) {
-    for (int d = size >> 1; d > 0; d >>= 1) {
-      for (int q = t; q < N / 2; q += ST) {
-        const int i = 2 * q - (q & (d - 1)), j = i + d;
-        const unsigned long long x = keys[i], y = keys[j];
-        if ((x > y) == ((i & size) == 0)) {
-          keys[i] = y;
-          keys[j] = x;
-        }
-      }
-      if (d > 64 || (d == 1 && size >= 128))
-        __syncthreads();
-      else {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-  }
+  bitonic<ST>(keys, N, t);
   __syncthreads();
   for (int i = t; i < c; i += ST)
     if (i < room) dst[i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
@@ -703,11 +738,11 @@ hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, co
   hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, pairs);
   int above = 0;
   if (trials > 1) {
-    hipLaunchKernelGGL(k_bucket_sort<kBucketSmall>, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, 0, out_cap, dst,
-                       fast, early_cap, counts_out);
+    hipLaunchKernelGGL(k_bucket_sort_small, dim3((unsigned)(nh * rows + ST / 64 - 1) / (ST / 64), trials), dim3(ST), 0, s,
+                       bl, pairs, out_cap, dst);
     above = kBucketSmall;
   }
-  hipLaunchKernelGGL(k_bucket_sort<kBucketLds>, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, above, out_cap, dst,
+  hipLaunchKernelGGL(k_bucket_sort, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, above, out_cap, dst,
                      fast, early_cap, counts_out);
   return hipGetLastError();
 }
