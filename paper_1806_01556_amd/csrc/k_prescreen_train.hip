@@ -394,11 +394,12 @@ __global__ __launch_bounds__(WTH) void k_ps_wgrad32(WgJobs jobs, int nb, float* 
 }
 
 // Weight and bias gradients of the one-channel layer: columns 0..8 are the taps
-// f[t + k - 4], column 9 is one (the bias).  A workgroup walks units of 256
-// positions, its 4 waves 64 each; their sums meet in LDS.  Bound by the compact
-// gradient's read (46 MB for 256 blocks): 26 us at 1024 workgroups, 42 us at 512,
+// f[t + k - 4], column 9 is one (the bias).  A workgroup walks units of 128
+// positions, its 4 waves 32 each; their sums meet in LDS.  Bound by the compact
+// gradient's read (46 MB for 256 blocks) and the latency of a unit's loads: 21 us
+// with 2048 workgroups; 26 us with units of 256 positions and 1024, 42 us with 512;
 // 188 us with the dense gradient and atomics.
-constexpr int W1T = 256;
+constexpr int W1T = 128;
 constexpr int W1DS = W1T + 4;
 __global__ __launch_bounds__(256) void k_ps_wgrad1(const float* __restrict__ g, const unsigned char* __restrict__ arg,
                                                    const float* __restrict__ x, int nb, float* __restrict__ part) {
@@ -420,10 +421,10 @@ __global__ __launch_bounds__(256) void k_ps_wgrad1(const float* __restrict__ g, 
       *reinterpret_cast<float4*>(ds + o * W1DS + 4 * c) = expand4(g, arg, (size_t)b * PC + o, PBLK, 2, t0 + 4 * c);
     }
     __syncthreads();
-    const float* dp = ds + m * W1DS + kk + 64 * wv;
-    const float* xp = fs + kk + m + 64 * wv;
+    const float* dp = ds + m * W1DS + kk + W1T / 4 * wv;
+    const float* xp = fs + kk + m + W1T / 4 * wv;
 #pragma unroll 4
-    for (int p = 0; p < 64; p += 4) {
+    for (int p = 0; p < W1T / 4; p += 4) {
       const float xv = m == PK ? 1.0f : xp[p];
       acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dp[p], xv, acc[0], 0, 0, 0);
       acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dp[p + 16 * W1DS], xv, acc[1], 0, 0, 0);
@@ -442,7 +443,9 @@ __global__ __launch_bounds__(256) void k_ps_wgrad1(const float* __restrict__ g, 
 // Sums of the partials, written to grad (and grad2 when given) and loss.
 // Workgroup = 64 elements x 16 segments of the partials.
 //   blocks 0 .. 431: 144 per 32-channel layer, weights in lane order
-//   432 .. 434: their biases; 435 .. 442: the one-channel layer; 443: head and loss
+//   432 .. 434: their biases; 435: head and loss
+//   436 .. 467: the one-channel layer, 16 elements x 64 segments each (its 2048
+//   partials in 16 segments took longer than all the rest)
 struct ReduceIn {
   const float *part, *partb, *part1;
   int wg0[3], nwg[3], n1;
@@ -450,7 +453,7 @@ struct ReduceIn {
   int nb;
   int off_w[4], off_b[4], off_fc;
 };
-constexpr int kReduceBlocks = 3 * 144 + 3 + 8 + 1;
+constexpr int kReduceBlocks = 3 * 144 + 3 + 1 + 32;
 
 __global__ __launch_bounds__(1024) void k_ps_reduce(ReduceIn in, float* __restrict__ grad, float* __restrict__ grad2,
                                                     float* __restrict__ loss) {
@@ -472,24 +475,31 @@ __global__ __launch_bounds__(1024) void k_ps_reduce(ReduceIn in, float* __restri
     const int q = blk - 432;
     if (lane < PC) {
       const float* p = in.partb + (size_t)in.wg0[q] * PC + lane;
+#pragma unroll 8
       for (int i = seg; i < in.nwg[q]; i += 16) s += p[(size_t)i * PC];
       dst = in.off_b[3 - q] + lane;
     }
-  } else if (blk < 443) {
-    const int reg = blk - 435;
-    const float* p = in.part1 + reg * 64 + lane;
+  } else if (blk > 435) {
+    // element e = 16 (blk - 436) + lane % 16: register e / 64, lane e % 64
+    const int e = 16 * (blk - 436) + (lane & 15);
+    const float* p = in.part1 + e;
 #pragma unroll 8
-    for (int i = seg; i < in.n1; i += 16) s += p[(size_t)i * 512];
-    const int o = 16 * (reg >> 2) + 4 * (lane >> 4) + (reg & 3), col = lane & 15;
-    dst = col < PK ? in.off_w[0] + o * PK + col : col == PK ? in.off_b[0] + o : -1;
+    for (int i = 4 * seg + (lane >> 4); i < in.n1; i += 64) s += p[(size_t)i * 512];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    const int reg = e >> 6, o = 16 * (reg >> 2) + 4 * ((e & 63) >> 4) + (reg & 3), col = e & 15;
+    if (lane < 16) dst = col < PK ? in.off_w[0] + o * PK + col : col == PK ? in.off_b[0] + o : -1;
   } else {
     if (lane < PC) {
+#pragma unroll 8
       for (int b = seg; b < in.nb; b += 16) s = fmaf(in.dlogit[b], in.h[(size_t)b * PC + lane], s);
       dst = in.off_fc + lane;
     } else if (lane == PC) {
+#pragma unroll 8
       for (int b = seg; b < in.nb; b += 16) s += in.dlogit[b];
       dst = in.off_fc + PC;
     } else if (lane == PC + 1) {
+#pragma unroll 8
       for (int b = seg; b < in.nb; b += 16) s += in.loss[b];
       to_loss = true;
     }
@@ -509,7 +519,7 @@ __global__ __launch_bounds__(1024) void k_ps_reduce(ReduceIn in, float* __restri
 }
 
 constexpr int kWg32 = 512;  // workgroups of k_ps_wgrad32, two per compute unit
-constexpr int kWg1 = 1024;
+constexpr int kWg1 = 2048;
 
 }  // namespace
 
