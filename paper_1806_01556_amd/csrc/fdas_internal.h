@@ -79,14 +79,19 @@ void fft_twiddles(int C, std::vector<float>& tw1, std::vector<float>& tw2);
 hipError_t launch_ols_conv(const float2* x, int64_t n, float* fop, int64_t ld, const OlsTables& t, int rows,
                            int slots, hipStream_t s);
 
-// Only the listed overlap-save chunks (chunk_list[0 .. nlist), device array)
-// and templates (FOP rows) z0 .. z0 + nr - 1; zrow is the row of the
-// zero-drift template (written as |X|^2).  With d_nlist the kernel reads
-// the list length from device memory and nlist is only its upper bound (the
-// grid is sized for it).
-hipError_t launch_ols_conv_list(const float2* x, int64_t n, float* fop, int64_t ld, const OlsTables& t, int z0,
-                                int nr, int zrow, int slots, const int* chunk_list, int nlist, hipStream_t s,
-                                const int* d_nlist = nullptr);
+// Only the listed overlap-save chunks, with templates (FOP rows) z0 .. z0 + nr - 1
+// for each: two lists in one launch (either may be empty); zrow is the row of the
+// zero-drift template (written as |X|^2).  With d_n the kernel reads a list's
+// length from device memory and n is only its upper bound (the grid is sized
+// for it).
+struct ChunkList {
+  const int* list = nullptr;  // device array
+  int n = 0;
+  const int* d_n = nullptr;
+  int z0 = 0, nr = 0;
+};
+hipError_t launch_ols_conv_list(const float2* x, int64_t n, float* fop, int64_t ld, const OlsTables& t, ChunkList a,
+                                ChunkList b, int zrow, int slots, hipStream_t s);
 
 // FOP rows the stretched harmonic sums read as sources (k = 2 .. nh) of an
 // 2*Z+1-row plane: [*lo, *hi]; empty (lo > hi) when nh < 2.

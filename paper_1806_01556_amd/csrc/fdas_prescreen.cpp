@@ -375,15 +375,14 @@ fdas_status fdas_search_blocks(fdas_plan* p, const void* d_spectrum, int64_t n, 
        (e = hipMemcpy(p->d_lists, lists.data(), lists.size() * sizeof(int), hipMemcpyHostToDevice)) != hipSuccess))
     return hip_fail(e, "uploading the block lists");
   if (tiles.empty()) e = launch_fill_i32(d_counts, nh, 0, s);  // else the harmonic sum resets them
-  if (e == hipSuccess && !chunks.empty())
-    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot, 0, p->rows, p->desc.z_max,
-                             slots, p->d_lists, (int)chunks.size(), s);
-  if (e == hipSuccess && !src_chunks.empty())
-    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot, r_lo, r_hi - r_lo + 1,
-                             p->desc.z_max, slots, p->d_lists + chunks.size(), (int)src_chunks.size(), s);
+  if (e == hipSuccess)
+    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot,
+                             ChunkList{p->d_lists, (int)chunks.size(), nullptr, 0, p->rows},
+                             ChunkList{p->d_lists + chunks.size(), (int)src_chunks.size(), nullptr, r_lo, r_hi - r_lo + 1},
+                             p->desc.z_max, slots, s);
   if (e == hipSuccess && !tiles.empty()) {
     HsWork wk{p->d_lists + chunks.size() + src_chunks.size(), (int)tiles.size(), p->d_hitrows, p->d_hitrow_count,
-              p->tuning.emit_workgroups};
+              p->tuning.emit_workgroups, (int)harmsum_hit_entries(p->desc.n_max)};
     e = launch_harmsum(d_fop, n, ld, p->desc.z_max, nh, p->d_ta, d_cands, p->desc.cand_capacity, d_counts, wk,
                        FDAS_HSUM_STRETCH, s);
   }
@@ -449,14 +448,14 @@ fdas_status fdas_search_flagged(fdas_plan* p, const void* d_spectrum, int64_t n,
   stretch_source_rows(p->desc.z_max, nh, &r_lo, &r_hi);
   e = ps_search_lists(d_logits, threshold, n, (int)nblk, nh, V, tcols, lists, cap_c, cap_t, s);
   if (e == hipSuccess)
-    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot, 0, p->rows, p->desc.z_max,
-                             slots, lists, cap_c, s, counts3);
-  if (e == hipSuccess)
-    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot, r_lo, r_hi - r_lo + 1,
-                             p->desc.z_max, slots, lists + cap_c + cap_t, cap_c, s, counts3 + 2);
+    e = launch_ols_conv_list(static_cast<const float2*>(d_spectrum), n, d_fop, ld, ot,
+                             ChunkList{lists, cap_c, counts3, 0, p->rows},
+                             ChunkList{lists + cap_c + cap_t, cap_c, counts3 + 2, r_lo, r_hi - r_lo + 1},
+                             p->desc.z_max, slots, s);
   if (e == hipSuccess) {
     // every tile slot gets a workgroup; slots past the selection hold -1 and exit
-    HsWork wk{lists + cap_c, cap_t, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups};
+    HsWork wk{lists + cap_c, cap_t, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups,
+              (int)harmsum_hit_entries(p->desc.n_max)};
     e = launch_harmsum(d_fop, n, ld, p->desc.z_max, nh, p->d_ta, d_cands, p->desc.cand_capacity, d_counts, wk,
                        FDAS_HSUM_STRETCH, s);
   }

@@ -384,30 +384,35 @@ __global__ __launch_bounds__(Shape<C>::NT, 2) void k_ols_conv(const float2* __re
   }
 }
 
-// Listed chunks only, templates z0 .. z0 + nr - 1: pair q = i * nr + (z - z0)
-// over chunk_list[0 .. nlist); with d_nlist the list length is read from
-// device memory (written by an earlier kernel on the stream).
+// Listed chunks only: list a with its templates, then list b with its own, as one
+// range of pairs (q = i * nr + (z - z0) within a list), so that the grid's
+// workgroups finish together once and not once per list.  A list's length is read
+// from device memory when d_n is set (written by an earlier kernel on the stream).
 template <int C>
 __global__ __launch_bounds__(Shape<C>::NT, 2) void k_ols_conv_list(const float2* __restrict__ x, int64_t n,
                                                                    float* __restrict__ fop, int64_t ld,
                                                                    const float2* __restrict__ H,
                                                                    const float2* __restrict__ tw1tab,
-                                                                   const float2* __restrict__ tw2tab, int z0, int nr,
-                                                                   const int* __restrict__ chunk_list, int nlist,
-                                                                   const int* __restrict__ d_nlist, int zrow, int V,
-                                                                   int P) {
+                                                                   const float2* __restrict__ tw2tab, ChunkList a,
+                                                                   ChunkList b, int zrow, int V, int P) {
   __shared__ float2 lds[Shape<C>::LDS];
   const int tid = threadIdx.x;
-  if (d_nlist) nlist = *d_nlist;
+  const int64_t pa = (int64_t)(a.d_n ? *a.d_n : a.n) * a.nr;
+  const int64_t pb = (int64_t)(b.d_n ? *b.d_n : b.n) * b.nr;
   Tw tw;
   load_twiddles<C>(tw1tab, tw2tab, tw, tid);
   int64_t q, hi;
-  pair_range((int64_t)nlist * nr, q, hi);
+  pair_range(pa + pb, q, hi);
   while (q < hi) {
-    const int64_t li = q / nr;
-    const int r_lo = (int)(q - li * nr);
-    const int r_hi = piece_end(q, hi, r_lo, nr, nr);
-    ols_item<C>(x, n, fop, ld, H, chunk_list[li], z0 + r_lo, z0 + r_hi, zrow, V, P, tw, lds, tid);
+    const bool second = q >= pa;  // uniform
+    const int nr = second ? b.nr : a.nr, z0 = second ? b.z0 : a.z0;
+    const int64_t first = second ? pa : 0;
+    const int64_t end = second ? hi : min(hi, pa);
+    const int64_t li = (q - first) / nr;
+    const int r_lo = (int)(q - first - li * nr);
+    const int r_hi = piece_end(q, end, r_lo, nr, nr);
+    const int chunk = second ? b.list[li] : a.list[li];
+    ols_item<C>(x, n, fop, ld, H, chunk, z0 + r_lo, z0 + r_hi, zrow, V, P, tw, lds, tid);
     q += r_hi - r_lo;
   }
 }
@@ -479,17 +484,19 @@ hipError_t launch_ols_conv(const float2* x, int64_t n, float* fop, int64_t ld, c
   return hipGetLastError();
 }
 
-hipError_t launch_ols_conv_list(const float2* x, int64_t n, float* fop, int64_t ld, const OlsTables& t, int z0,
-                                int nr, int zrow, int slots, const int* chunk_list, int nlist, hipStream_t s,
-                                const int* d_nlist) {
-  if (nlist <= 0 || nr <= 0) return hipSuccess;
+hipError_t launch_ols_conv_list(const float2* x, int64_t n, float* fop, int64_t ld, const OlsTables& t, ChunkList a,
+                                ChunkList b, int zrow, int slots, hipStream_t s) {
+  for (ChunkList* l : {&a, &b})
+    if (l->n <= 0 || l->nr <= 0) *l = ChunkList{};
+  const int64_t pairs = (int64_t)a.n * a.nr + (int64_t)b.n * b.nr;
+  if (pairs <= 0) return hipSuccess;
   const OlsGeom& g = t.geom;
-  const unsigned grid = (unsigned)std::min<int64_t>((int64_t)nlist * nr, slots);
+  const unsigned grid = (unsigned)std::min<int64_t>(pairs, slots);
   switch (g.C) {
 #define FDAS_OLS_CASE(CC)                                                                                          \
   case CC:                                                                                                         \
     hipLaunchKernelGGL(k_ols_conv_list<CC>, dim3(grid), dim3(Shape<CC>::NT), 0, s, x, n, fop, ld, t.H, t.tw1,      \
-                       t.tw2, z0, nr, chunk_list, nlist, d_nlist, zrow, g.V, g.P);                                 \
+                       t.tw2, a, b, zrow, g.V, g.P);                                                               \
     break;
     FDAS_OLS_CASE(2048)
     FDAS_OLS_CASE(4096)

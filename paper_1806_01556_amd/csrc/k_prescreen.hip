@@ -323,19 +323,26 @@ __device__ __forceinline__ int64_t max64(int64_t a, int64_t b) { return a > b ? 
 
 // exclusive prefix of v over the workgroup; *total receives the sum
 __device__ __forceinline__ int block_exclusive_scan(int v, int* s_scan, int* total) {
-  const int t = threadIdx.x;
-  s_scan[t] = v;
-  __syncthreads();
-  for (int o = 1; o < kSelThreads; o <<= 1) {
-    const int u = t >= o ? s_scan[t - o] : 0;
-    __syncthreads();
-    s_scan[t] += u;
-    __syncthreads();
+  // inclusive sums within a wave, then the 16 waves' sums
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(incl, o);
+    if (lane >= o) incl += u;
   }
-  const int incl = s_scan[t];
-  *total = s_scan[kSelThreads - 1];
+  if (lane == 63) s_scan[w] = incl;
   __syncthreads();
-  return incl - v;
+  int before = 0, all = 0;
+#pragma unroll
+  for (int q = 0; q < kSelThreads / 64; ++q) {
+    const int c = s_scan[q];
+    before += q < w ? c : 0;
+    all += c;
+  }
+  *total = all;
+  __syncthreads();
+  return before + incl - v;
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_ps_search_lists(const float* __restrict__ logits, float thr,
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(kSelThreads) void k_ps_search_lists(const float* __
                                                                  int* __restrict__ lists, int cap_c, int cap_t) {
   __shared__ unsigned char s_search[kMaxSelBlocks];
   __shared__ unsigned char s_src[kMaxSelBlocks];
-  __shared__ int s_scan[kSelThreads];
+  __shared__ int s_scan[kSelThreads / 64];
   __shared__ int s_all;
   const int t = threadIdx.x;
   // Fallback to the plain search: a NaN threshold or any logit that is not
