@@ -166,8 +166,8 @@ __device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t rs, int lane_of
 // the terms m <= z_max / |i|; rows are walked in groups of equal term count MV,
 // R rows at a time, so that a wave always has about 28 loads in flight (half of
 // the rows have the fundamental only).  Planes past MV hold the same sum: it is
-// compared with the smallest of their thresholds.  Measured on 2^22 bins: 0.76 ms
-// for the whole call, 5.2 TB/s of its 2.75 planes of lines; 0.93 ms before.
+// compared with the smallest of their thresholds.  Bound by the lines it moves from
+// beyond L2: 2.75 planes (3.9 GB of 2^22 bins) at 5.4 TB/s without sharing.
 //
 // Row i0 + r of [a, b], clamped to b (a repeated row sets its bit again).
 template <int NH, int MV, int R>
@@ -224,8 +224,103 @@ __device__ __forceinline__ void fund_groups(const float* __restrict__ fop, int64
   if constexpr (MV < NH) fund_groups<NH, MV + 1>(fop, ld, n, z_max, t0, i0, i1, s_ta, rbase, mk);
 }
 
+// All rows of a long spectrum, one row step for the two signs of a node: rows +-i
+// with their MV terms, and with CH = 2 rows +-c0, +-c1 (one term each, equal where
+// only one is wanted: a repeated row sets its bit again).
+template <int MV, int CH>
+__device__ __forceinline__ void fund_node(const float* __restrict__ fop, int64_t ld, int n, int z_max, int64_t t0,
+                                          int i, int c0, int c1, const float* __restrict__ s_ta, RowMask& mk) {
+  const int t = (int)threadIdx.x;
+  float v[2][MV][4], w[2][CH + 1][4];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+#pragma unroll
+    for (int m = 1; m <= MV; ++m) {
+      const int row = z_max + (g ? -m * i : m * i);
+      const __amdgpu_buffer_rsrc_t rs = row_rsrc(fop + (size_t)row * ld + m * t0, (int64_t)n - m * t0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) v[g][m - 1][a] = row_load(rs, 4 * m * t, 4 * m * kStrideFund * a);
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int row = z_max + (g ? -1 : 1) * (c ? c1 : c0);
+      const __amdgpu_buffer_rsrc_t rs = row_rsrc(fop + (size_t)row * ld + t0, (int64_t)n - t0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) w[g][c][a] = row_load(rs, 4 * t, 4 * kStrideFund * a);
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int r = z_max + (g ? -i : i);
+    float hp[4];
+    bool hit = false;
+#pragma unroll
+    for (int m = 1; m <= MV; ++m) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) hp[a] = m == 1 ? v[g][0][a] : hp[a] + v[g][m - 1][a];
+      hit = hit || max4(hp) > s_ta[8 * r + m - 1];
+    }
+    mk.note(hit, r);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int rc = z_max + (g ? -1 : 1) * (c ? c1 : c0);
+      mk.note(max4(w[g][c]) > s_ta[8 * rc], rc);
+    }
+  }
+}
+
+template <int NH, int MV>
+__device__ __forceinline__ void fund_visit(const float* __restrict__ fop, int64_t ld, int n, int z_max, int64_t t0,
+                                           int mv, int i, int c0, int c1, const float* __restrict__ s_ta, RowMask& mk) {
+  if (mv == MV) {
+    if (c0 == 0) {
+      fund_node<MV, 0>(fop, ld, n, z_max, t0, i, 0, 0, s_ta, mk);
+      return;
+    }
+    // c0 > z_max / 2 and i = c0 / 2: more than four terms cannot be here unless z_max < 10
+    fund_node<MV, 2>(fop, ld, n, z_max, t0, i, c0, c1, s_ta, mk);
+    return;
+  }
+  if constexpr (MV < NH) fund_visit<NH, MV + 1>(fop, ld, n, z_max, t0, mv, i, c0, c1, s_ta, mk);
+}
+
+// The row |i| = 2 i' (or 2 i' + 1) follows its half i' at once: rows 1 .. L = z_max / 2
+// (two terms and more) in preorder of the binary tree i -> 2 i, 2 i + 1, each with
+// those of its children that have one term.  The lines that a tile reads as term m
+// of row i are those that the tile at twice the column reads as term m / 2 of row
+// 2 i, and the tile order runs the two together on one XCD, so part of them is
+// still in its L2: 3.1 GB from beyond it for 2^22 bins, 3.75 GB with the rows in
+// groups of equal term count (nothing shared; 1.7 planes, 2.4 GB, if the tiles kept step).
+// Measured, whole call: 2^22 bins 722 -> 678 us, 3,000,001 545 -> 522, 1,500,001
+// 315 -> 301, 4,000,001 with z_max 17 333 -> 299; 1,000,003 242 -> 251, so up to
+// 2^20 bins, where one round of workgroups holds all tiles, the groups stay.
+constexpr int kTreeAboveN = 1 << 20;
+static_assert(kTreeAboveN >= kSplitBins, "a launch above it has one row segment");
 template <int NH>
-__global__ __launch_bounds__(HS_THREADS, 6) void k_detect_fund(const float* __restrict__ fop, int64_t ld, int n,
+__device__ __forceinline__ void fund_tree(const float* __restrict__ fop, int64_t ld, int n, int z_max, int64_t t0,
+                                          const float* __restrict__ s_ta, RowMask& mk) {
+  const int L = z_max / 2;
+  fund_node<NH, 0>(fop, ld, n, z_max, t0, 0, 0, 0, s_ta, mk);
+  int i = 1;
+#pragma unroll 1
+  while (i > 0) {
+    int c0 = 0, c1 = 0;
+    if (2 * i + 1 > L) {
+      c0 = 2 * i > L ? 2 * i : 2 * i + 1;
+      c1 = min(2 * i + 1, z_max);
+    }
+    fund_visit<NH, 2>(fop, ld, n, z_max, t0, min(NH, z_max / i), i, c0, c1, s_ta, mk);
+    if (2 * i <= L) {
+      i = 2 * i;
+    } else {  // the next sibling of the node or of the nearest ancestor that has one
+      while (i > 0 && ((i & 1) || i + 1 > L)) i >>= 1;
+      if (i > 0) i += 1;
+    }
+  }
+}
+
+template <int NH>
+__global__ __launch_bounds__(HS_THREADS, 4) void k_detect_fund(const float* __restrict__ fop, int64_t ld, int n,
                                                                int z_max, int rbase, int rend,
                                                                const int* __restrict__ tile_of_block,
                                                                const float* __restrict__ ta,
@@ -248,7 +343,14 @@ __global__ __launch_bounds__(HS_THREADS, 6) void k_detect_fund(const float* __re
   row_segment(rbase, rend, r0, r1);
   const int64_t t0 = (int64_t)tile * XT;
   RowMask mk;
-  fund_groups<NH, 1>(fop, ld, n, z_max, t0, r0 - z_max, r1 - 1 - z_max, s_ta, rbase, mk);
+  // a segment or a pass holds a contiguous part of the rows, where few doubles meet
+  bool tree = false;
+  if constexpr (NH > 1) tree = n > kTreeAboveN && rend - rbase == rows && z_max >= 2;
+  if (tree) {
+    if constexpr (NH > 1) fund_tree<NH>(fop, ld, n, z_max, t0, s_ta, mk);
+  } else {
+    fund_groups<NH, 1>(fop, ld, n, z_max, t0, r0 - z_max, r1 - 1 - z_max, s_ta, rbase, mk);
+  }
   const int c0 = (int)t0 + (int)threadIdx.x;
   if (c0 >= n) mk = RowMask();
   flush_mask(mk, c0, hitrows, hit_cap, hit_count);
@@ -611,11 +713,6 @@ __device__ __forceinline__ void hs_prologue(HsState<NH>& st, const float* __rest
   if constexpr (R + 1 < R0 + DEPTH) hs_prologue<Z, NH, R0, R1, R + 1>(st, fop, ld, j0, lo);
 }
 
-// Phase 1 over all columns [0, n) in groups of 4 (the last group may be
-// partial).  The 16-byte read of the last group stays inside the row because
-// ld >= n and ld % 4 == 0; a source column j/k + 1 read for k >= 2 is at most
-// (n-1)/2 + 1 <= ld - 1.  Values read beyond column n - 1 only reach columns
-// >= n, which phase 2 never emits.
 // Phase 1 for one thread: rows [R0, R1) of columns j0..j0+3 of a plane with n
 // columns.  Returns the bit mask of rows holding a cell above threshold (3 words).
 template <int Z, int NH, int R0 = 0, int R1 = 2 * Z + 1>
@@ -1154,8 +1251,8 @@ hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_
   // The other maps' kernels reserve LDS they do not use, so that fewer waves share
   // a compute unit than registers allow: the waves' source rows evict each
   // other's lines.  Highest: three workgroups (2^22 bins 2.06 ms; four 2.19-2.24,
-  // two 2.19).  Fundamental: four beside its 4 KB table (1,500,001 bins 0.365 ms;
-  // six or eight 0.415).
+  // two 2.19).  Fundamental: four beside its 4 KB table (1,500,001 bins 0.301 ms;
+  // seven 0.352).
   const size_t reserve = MAP == FDAS_HSUM_HIGHEST ? 50000 : MAP == FDAS_HSUM_FUNDAMENTAL ? 36000 : 0;
   hipLaunchKernelGGL(detect, dim3(blocks, segs), dim3(HS_THREADS), reserve, s, fop, ld, n, z_max, rbase, rend, order, ta,
                      wk.hitrows, wk.hit_cap, wk.hitrow_count);

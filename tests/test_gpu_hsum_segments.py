@@ -46,3 +46,26 @@ def test_segments_passes_and_tiles(index, z_max, n, n_harm, p):
             for f in ("harm", "z", "r"):
                 assert np.array_equal(got[f], ref[f]), (call, f)
             assert np.array_equal(got["power"].view(np.int32), ref["power"].astype(np.float32).view(np.int32)), call
+
+
+# z_max = 2 .. 5: the smallest trees; 19, 21, 41: the last node has one child of one
+# term (2 i + 1) with three, four and four terms; 47: the widest single pass
+@pytest.mark.parametrize("z_max,n_harm", [(2, 8), (3, 2), (4, 3), (5, 8), (19, 3), (21, 8), (41, 4), (47, 2)])
+def test_fundamental_rows_in_tree_order(z_max, n_harm):
+    n, rows = (1 << 20) + 1029, 2 * z_max + 1
+    rng = np.random.default_rng(z_max)
+    plane = rng.exponential(size=(rows, n)).astype(np.float32)
+    buf = np.full((rows, fdas.fop_ld(n)), np.nan, dtype=np.float32)
+    buf[:, :n] = plane
+    ta = oh.threshold_array(n_harm, z_max, 1e-4).astype(np.float32)
+    ta = ta * (1.0 + 0.002 * np.arange(rows, dtype=np.float32)[None, :])
+    ref = oh.candidates(plane, n_harm, ta=ta, index="fundamental")
+    print(f"hsum tree: z_max={z_max} n_harm={n_harm}", flush=True)
+    with fdas.plan_create(z_max=z_max, n_harm=n_harm, n_max=n, hsum_index=fdas.HSUM_FUNDAMENTAL) as plan:
+        fop, ta_t = torch.from_numpy(buf).to("cuda:0"), torch.from_numpy(ta).to("cuda:0")
+        cands, counts = fdas.alloc_cands(plan, "cuda:0")
+        fdas.harmonic_sum(plan, fop, n, cands, counts, ta=ta_t)
+        got, hc = fdas.candidates(plan, cands, counts)
+    assert np.array_equal(hc, oh.plane_counts(ref, n_harm))
+    assert np.array_equal(got["z"], ref["z"]) and np.array_equal(got["r"], ref["r"])
+    assert np.array_equal(got["power"].view(np.uint32), ref["power"].astype(np.float32).view(np.uint32))
