@@ -357,8 +357,7 @@ void stretch_source_rows(int Z, int nh, int* lo, int* hi) {
 // are sorted by the fraction of log2(t) (the bits after the leading one,
 // left-aligned) and then by octave, which puts every chain t, 2t(+1), 4t(+3),
 // 8t(+7) next to each other, so a tile's k = 2, 4, 8 sources were read moments
-// before.  The sorted list is split into 8 contiguous segments, one per XCD
-// (workgroup b runs on XCD b mod 8), so a chain also shares one L2.
+// before.
 static std::vector<int> octave_order(int T) {
   int top = 0;
   while ((1LL << (top + 1)) <= (int64_t)std::max(1, T - 1)) ++top;  // octave of the largest index
@@ -379,6 +378,8 @@ static std::vector<int> octave_order(int T) {
   return order;
 }
 
+// The ordered list is split into 8 contiguous segments, one per XCD (workgroup
+// b runs on XCD b mod 8), so a chain also shares one L2.
 void harmsum_tile_order(int64_t n, std::vector<int>& tile_of_block, int cols) {
   const int T = (int)((n + cols - 1) / cols);
   const std::vector<int> order = octave_order(T);

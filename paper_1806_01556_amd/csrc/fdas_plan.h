@@ -39,7 +39,7 @@ struct fdas_plan {
   int32_t* h_result_counts = nullptr;
   int bits_r = 1;                 // bits of the column index in the sort key
   std::map<std::pair<int64_t, int>, std::pair<int*, int>> tile_orders;  // (n, tile columns) -> (device order, workgroups)
-  int4* d_hitrows = nullptr;      // [ceil(n_max/4)] rows with hits (harmonic sum phase 1)
+  int4* d_hitrows = nullptr;      // [harmsum_hit_entries(n_max)] rows with hits (harmonic sum phase 1)
   int32_t* d_hitrow_count = nullptr;
   fdas_tuning tuning{};           // batch launch parameters (0 = default)
   int* d_lists = nullptr;         // fdas_search_blocks: chunk list then tile list
