@@ -289,10 +289,10 @@ __device__ __forceinline__ void fund_visit(const float* __restrict__ fop, int64_
 // those of its children that have one term.  The lines that a tile reads as term m
 // of row i are those that the tile at twice the column reads as term m / 2 of row
 // 2 i, and the tile order runs the two together on one XCD, so part of them is
-// still in its L2: 3.1 GB from beyond it for 2^22 bins, 3.75 GB with the rows in
-// groups of equal term count (nothing shared; 1.7 planes, 2.4 GB, if the tiles kept step).
-// Measured, whole call: 2^22 bins 722 -> 678 us, 3,000,001 545 -> 522, 1,500,001
-// 315 -> 301, 4,000,001 with z_max 17 333 -> 299; 1,000,003 242 -> 251, so up to
+// still in its L2: 3.4 GB from beyond it for 2^22 bins, 3.75 GB with the rows in
+// groups of equal term count (2.4 GB, 1.7 planes, if the tiles kept step).
+// Measured, whole call: 2^22 bins 720 -> 671 us, 3,000,001 545 -> 514, 1,500,001
+// 315 -> 288, 4,000,001 with z_max 17 333 -> 289; 1,000,003 242 -> 251, so up to
 // 2^20 bins, where one round of workgroups holds all tiles, the groups stay.
 constexpr int kTreeAboveN = 1 << 20;
 static_assert(kTreeAboveN >= kSplitBins, "a launch above it has one row segment");
