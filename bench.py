@@ -822,14 +822,16 @@ def main():
         conv = {"name": "k_ols_conv", "bound": "alu", "peak": FP32_VECTOR_PEAK_TF, "file": "k_ols_conv.hip"}
     elif args.method == "direct":
         taps = sum(2 * (8 + (9 * abs(z) + 1) // 2) for z in range(-42, 43))
-        conv_flop = 8 * taps * n                     # one complex multiply-add per template tap and bin
+        # a quarter of the 8 flop of a complex multiply-add per template tap and
+        # bin: h_-z = conj(h_z) and h_z[-d] = h_z[d] leave that much to multiply
+        conv_flop = 2 * taps * n
         conv = {"name": "k_direct_conv", "bound": "mfma", "peak": FP32_MATRIX_PEAK_TF,
                 "file": "k_direct_conv.hip"}
     else:
-        # split precision: three 16-bit products per FP32 product; the
+        # split precision: three (BF16: four) 16-bit products per FP32 product; the
         # contraction's useful flops counted once, against the 16-bit peak
         taps = sum(2 * (8 + (9 * abs(z) + 1) // 2) for z in range(-42, 43))
-        conv_flop = 8 * taps * n
+        conv_flop = 2 * taps * n
         conv = {"name": "k_direct_conv_split", "bound": "mfma", "peak": FP16_MATRIX_PEAK_TF,
                 "file": "k_direct_conv.hip"}
     kernels = {
@@ -865,15 +867,16 @@ def main():
                         "kernels may share the GPU"}
 
     if args.method in ("direct-fp16", "direct-bf16"):
-        # matrix-core work the split kernel issues: its 11 template tiles
-        # (85 templates by |z|, 8 per tile, each over the union of its
-        # members' supports padded to 8 tap pairs) make 163 groups of 16 taps
-        # per 16 bins, each 3 v_mfma_f32_16x16x32 of 16,384 flop
-        issued = 163 * 3 * 16384 / 16 * n
+        # matrix-core work the split kernel issues: its 6 template tiles (8 |z|
+        # each, over the distances 0 .. L/2 - 1 of the widest, padded to 32)
+        # make 23 steps per 16 bins, each one v_mfma_f32_16x16x32 of 16,384
+        # flop per product for Re X and one for Im X
+        products = 3 if args.method == "direct-fp16" else 4
+        issued = 23 * 2 * products * 16384 / 16 * n
         issued_tf = issued / (conv_ms * 1e-3) / 1e12
         roof["mfma_issued"] = {"achieved": round(issued_tf, 3), "peak": FP16_MATRIX_PEAK_TF, "unit": "TFLOP/s",
                                "frac": round(issued_tf / FP16_MATRIX_PEAK_TF, 4),
-                               "note": "hi*hi + hi*lo + lo*hi products and padded taps included"}
+                               "note": "all products of the halves and padded taps included"}
     out = {
         "metric": METRIC,
         "value": round(args.steps / wall, 3),
