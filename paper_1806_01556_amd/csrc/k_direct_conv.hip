@@ -120,6 +120,87 @@ __device__ __forceinline__ void pair_store(const v4f& a, const v4f& b, int row, 
   }
 }
 
+// Bins that the matrix products must not see: NaN, infinities, and values whose
+// folded sum could overflow.  A tile multiplies every bin within its widest
+// member's support, by zero past a narrower member's own, and 0 x Inf is NaN.
+// Such bins are staged as zero, and the cells whose own support holds one are
+// formed again by repair_cells.  Spectra without them are as fast as before (2^20
+// bins FP32 381 and 381 us, 2^22 bins FP16 760 and 758); one infinity among 2^22
+// bins costs 1.6 ms, NaN throughout 2.6 ms (FP32) and 5.0 ms (split).
+constexpr float kBadBin = 1.7e38f;
+__device__ __forceinline__ bool bad_bin(const float2& v) {
+  return !(fabsf(v.x) < kBadBin && fabsf(v.y) < kBadBin);
+}
+
+// The cells of NB bins from j0 on whose own support holds a bad bin, as the sum
+// over their taps; tap(t, col, d) is the value of column col of tile t at
+// distance d >= 0 (half of it at d = 0).  Called by a whole workgroup of 256
+// after its stores; a thread takes one bin.  Only blocks that met a bad bin come here.
+template <int NB, int TG, typename Tap>
+__device__ __forceinline__ void repair_cells(const float2* __restrict__ x, int64_t n, float* __restrict__ fop,
+                                             int64_t ld, int64_t j0, int reach, const ColumnInfo* cols, Tap tap) {
+  // the stores of this block's cells come first
+  __threadfence();
+  __syncthreads();
+  constexpr int PER = 256 / NB;  // threads to a bin: each takes every PER-th slot
+  // opaque, so that nothing formed from it is kept in registers through the products
+  int tid = (int)threadIdx.x;
+  __asm__ volatile("" : "+v"(tid));
+  const int64_t j = j0 + tid % NB;
+  if (j >= n) return;
+  auto bin = [&](int64_t i) { return i >= 0 && i < n ? x[i] : make_float2(0.0f, 0.0f); };
+  // distance of the nearest bad bin, and of the nearest NaN, before and from j
+  int left = reach + 1, right = reach + 1, nan_left = reach + 1, nan_right = reach + 1;
+  for (int d = reach; d >= 0; --d) {
+    const float2 a = bin(j - d), b = bin(j + d);
+    if (bad_bin(a)) left = d;
+    if (bad_bin(b)) right = d;
+    if (a.x != a.x || a.y != a.y) nan_left = d;
+    if (b.x != b.x || b.y != b.y) nan_right = d;
+  }
+  for (int slot = tid / NB; slot < 8 * TG; slot += PER) {
+    const ColumnInfo re = cols[2 * slot], im = cols[2 * slot + 1];
+    const int P = re.edge;
+    if (re.row < 0 || (left > P && right > P - 1)) continue;
+    float yr[2], yi[2];  // +z, -z
+    if (nan_left <= P || nan_right < P) {
+      // whatever the taps: spectra that are NaN throughout end here
+      yr[0] = yi[0] = yr[1] = yi[1] = __builtin_nanf("");
+    } else {
+      const float2 v = bin(j - P);
+      const float a = re.tap * re.scale, b = im.tap * im.scale;
+      yr[0] = v.x * a - v.y * b;
+      yi[0] = v.x * b + v.y * a;
+      yr[1] = v.x * a + v.y * b;
+      yi[1] = v.y * a - v.x * b;
+      for (int d = 0; d < P; ++d) {
+        const float ta = tap(slot >> 3, 2 * (slot & 7), d) * re.scale;
+        const float tb = tap(slot >> 3, 2 * (slot & 7) + 1, d) * im.scale;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+          const float2 w = bin(side ? j - d : j + d);
+          yr[0] += w.x * ta - w.y * tb;
+          yi[0] += w.x * tb + w.y * ta;
+          yr[1] += w.x * ta + w.y * tb;
+          yi[1] += w.y * ta - w.x * tb;
+        }
+      }
+    }
+    fop[(size_t)re.row * ld + j] = yr[0] * yr[0] + yi[0] * yi[0];
+    if (im.row >= 0) fop[(size_t)im.row * ld + j] = yr[1] * yr[1] + yi[1] * yi[1];
+  }
+}
+
+// Operand entry of step p of tile t in a group (entries are step-major, and a step
+// holds the tiles that still run).
+template <int TG>
+__device__ __forceinline__ int group_entry(const int4* __restrict__ tiles, int t, int p) {
+  int e = t;
+#pragma unroll
+  for (int q = 0; q < TG; ++q) e += min(tiles[q].x, p);
+  return e;
+}
+
 // A group of TG tiles at once: tiles[t] = {folded steps, 0, 0, 0} (steps fall
 // with t), rows[t * 16 + col] = FOP row of column col (-1: none),
 // edge[t * 8 + slot] = L/2 of the slot's template, edge_tap[t * 16 + col] its
@@ -195,8 +276,11 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     const float* __restrict__ edge_tap, int count, int Pm, int blocks) {
   extern __shared__ float4 lds4[];
   __shared__ ColumnInfo cols[16 * TG];
+  __shared__ int s_bad[2];  // 1 + the last block staged in this strip that met a bad bin
   const int tid = threadIdx.x;
   load_columns(cols, 16 * TG, rows, edge, edge_tap, nullptr, tid);
+  if (tid < 2) s_bad[tid] = 0;
+  __syncthreads();
   const int halo = Pm + FOLD_PAD;
   const int strip = BLK_BINS + 2 * halo;  // bins jb - halo + u
   const float* bs = reinterpret_cast<const float*>(lds4);
@@ -213,7 +297,12 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     float2* cur = xs + ((blk - blk0) & 1) * strip;
     for (int u = tid; u < strip; u += DW * 64) {
       const int64_t idx = (int64_t)blk * BLK_BINS - halo + u;
-      cur[u] = (idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
+      float2 v = (idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
+      if (bad_bin(v)) {
+        v = make_float2(0.0f, 0.0f);
+        s_bad[(blk - blk0) & 1] = blk + 1;
+      }
+      cur[u] = v;
     }
     __syncthreads();
     const int64_t jb = (int64_t)blk * BLK_BINS + w * WAVE_BINS;
@@ -251,6 +340,10 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
         for (int s = 0; s < SUB; ++s) pair_store(st.ar[t][s], st.ai[t][s], row, dst + 16 * s, left - 16 * s);
       }
     }
+    if (__builtin_amdgcn_readfirstlane(s_bad[(blk - blk0) & 1]) == blk + 1)
+      repair_cells<BLK_BINS, TG>(x, n, fop, ld, (int64_t)blk * BLK_BINS, Pm, cols, [&](int t, int col, int d) {
+        return bs[64 * group_entry<TG>(tiles, t, d / 4) + 16 * (d & 3) + col];
+      });
   }
 }
 
@@ -427,7 +520,7 @@ template <typename T, int TG>
 __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const uint4* __restrict__ Bsp,
     const int4* __restrict__ tiles, const float* __restrict__ tscale, const int* __restrict__ rows,
-    const int* __restrict__ edge, const float* __restrict__ edge_tap, int count, int halo, int blocks) {
+    const int* __restrict__ edge, const float* __restrict__ edge_tap, int count, int halo, int Pm, int blocks) {
   extern __shared__ uint4 lds_u4[];
   __shared__ ColumnInfo cols[16 * TG];
   __shared__ float s_max[4];
@@ -455,14 +548,26 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
       nx[i] = (u < strip && idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
     }
   };
-  // largest |Re|, |Im| of this wave's share of the fetched strip.  Taken before
+  // largest |Re|, |Im| of this wave's share of the fetched strip, negated when
+  // the share held a bad bin (which becomes zero).  Taken before
   // the block's stores are issued: a wait for the loads then waits for no store.
   auto note_max = [&]() {
-    float mx = 0.0f;
+    auto share_max = [&]() {  // NaN if one is met
+      float m = 0.0f;
 #pragma unroll
-    for (int i = 0; i < SPER; ++i) mx = fmaxf(mx, fmaxf(fabsf(nx[i].x), fabsf(nx[i].y)));
+      for (int i = 0; i < SPER; ++i)
+        m = __builtin_elementwise_maximum(m, __builtin_elementwise_maximum(fabsf(nx[i].x), fabsf(nx[i].y)));
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+      for (int o = 32; o > 0; o >>= 1) m = __builtin_elementwise_maximum(m, __shfl_xor(m, o));
+      return m;
+    };
+    float mx = share_max();
+    if (!(mx < kBadBin)) {  // uniform
+#pragma unroll
+      for (int i = 0; i < SPER; ++i)
+        if (bad_bin(nx[i])) nx[i] = make_float2(0.0f, 0.0f);
+      mx = -share_max();
+    }
     if (lane == 0) s_max[w] = mx;
   };
   fetch(blk0);
@@ -470,9 +575,11 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
   for (int blk = blk0; blk < blk1; ++blk) {
     const int64_t j0 = (int64_t)blk * SBLK_BINS;
     __syncthreads();  // every wave is done with the previous strip
-    const float mx = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    const float mx = fmaxf(fmaxf(fabsf(s_max[0]), fabsf(s_max[1])), fmaxf(fabsf(s_max[2]), fabsf(s_max[3])));
+    const int bad = __builtin_amdgcn_readfirstlane(__float_as_int(s_max[0]) | __float_as_int(s_max[1]) |
+                                                   __float_as_int(s_max[2]) | __float_as_int(s_max[3]));  // sign
     int ex = 0;
-    if (mx > 0.0f && mx < 3.0e38f) ex = 13 - ilogbf(mx);  // 2^13 <= max * 2^ex < 2^14
+    if (mx > 0.0f) ex = 13 - ilogbf(mx);  // 2^13 <= max * 2^ex < 2^14
 #pragma unroll
     for (int i = 0; i < SPER; ++i) {
       const int u = tid + 256 * i;
@@ -531,6 +638,13 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
           pair_store(a, c, row, dst + 32 * s, left - 32 * s);
       }
     }
+    if (bad < 0)
+      repair_cells<SBLK_BINS, TG>(x, n, fop, ld, j0, Pm, cols, [&](int t, int col, int d) {
+        // lane 16 ((d / 8) % 4) + col, value d % 8: hi, and lo 64 lanes on
+        const T* e = reinterpret_cast<const T*>(lds_u4 + 128 * group_entry<TG>(tiles, t, d / 32));
+        const int at = (16 * ((d >> 3) & 3) + col) * 8 + (d & 7);
+        return (float)e[at] + (float)e[at + 512];
+      });
   }
 }
 
@@ -547,7 +661,7 @@ hipError_t launch_split_group(const float2* x, int64_t n, float* fop, int64_t ld
   }
   hipLaunchKernelGGL((k_direct_conv_split<T, TG>), dim3(grid), dim3(256), lds, s, x, n, fop, ld,
                      t.Bsp + (size_t)128 * gr.offset, t.tiles + gr.first, t.tscale + gr.first, t.rows + 16 * gr.first,
-                     t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, halo, blocks);
+                     t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, halo, t.P_max, blocks);
   return hipGetLastError();
 }
 
