@@ -355,9 +355,11 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
 // the rounding of the halves and kept (2-norm error 5.1e-6 without it, 4.0e-6
 // with, 2^22 bins 0.77 and 0.85 ms).  One instruction takes 16 bins x 32
 // distances x 16 real filters (8 |z|).  FP16 has a narrow exponent range, so the
-// block's strip of X is scaled by 2^ex (largest |Re|, |Im| brought to about 2^13,
-// a folded value below 2^15) and each template tile by a plan-chosen 2^eh; both
-// scalings are exact and undone on the accumulator.
+// block's strip of X is scaled by 2^ex (largest |Re|, |Im| brought to 2^14 .. 32752,
+// so that a folded value stays within 65504) and each template tile by a
+// plan-chosen 2^eh; both scalings are exact and undone on the accumulator.  What is
+// left of a bin 2^18 and more under the strip's largest is a multiple of 2^-24
+// scaled: with the strip at 2^13 the error of such bins beside a line was twice this.
 
 constexpr int SSUB = 2;                      // 16-bin sub-tiles per wave, 32 bins apart
 constexpr int SBLK_BINS = 128;               // 4 waves: wave w takes bins 64 (w / 2) + 16 (w % 2) + 32 s
@@ -458,8 +460,8 @@ __device__ __forceinline__ void strip_down(const float2* __restrict__ p, float2 
 // A group of TG tiles at once, as in the FP32 kernel, with steps of 32
 // distances: lane group kg holds distances 32 q + 8 kg + e.  Bsp holds 2 KiB
 // per (step, tile): 64 lanes x 8 hi values, then 64 x 8 lo values; tscale[t] =
-// 2^-eh.  The strip of X stays FP32 (scaled so that a folded value is below
-// 2^15) and every folded value is split when it is used: the sum of two 16-bit
+// 2^-eh.  The strip of X stays FP32 (scaled so that a folded value is at most
+// 65504) and every folded value is split when it is used: the sum of two 16-bit
 // halves is no 16-bit value.  A wave's two sub-tiles lie 32 bins, one step,
 // apart, so sub-tile 0 of the next step reads upwards what sub-tile 1 reads
 // now, and sub-tile 1 downwards what sub-tile 0 reads now: one upward and one
@@ -579,7 +581,11 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     const int bad = __builtin_amdgcn_readfirstlane(__float_as_int(s_max[0]) | __float_as_int(s_max[1]) |
                                                    __float_as_int(s_max[2]) | __float_as_int(s_max[3]));  // sign
     int ex = 0;
-    if (mx > 0.0f) ex = 13 - ilogbf(mx);  // 2^13 <= max * 2^ex < 2^14
+    if (mx > 0.0f) {
+      // 2^14 <= max * 2^ex, and the sum of two bins at most 65504, FP16's largest
+      ex = 14 - ilogbf(mx);
+      if (ldexpf(mx, ex) > 32752.0f) --ex;
+    }
 #pragma unroll
     for (int i = 0; i < SPER; ++i) {
       const int u = tid + 256 * i;
