@@ -350,6 +350,7 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
   bool overflow = false;
   // record i of trial t lands at pre[t] + i of one trial-major array
   std::vector<int64_t> pre(count + 1, 0);
+  bool shares = false;  // a row may hold more records than one workgroup orders
   for (int i = 0; i < count; ++i) {
     int64_t tot = 0;
     for (int k = 0; k < nh; ++k) {
@@ -357,6 +358,7 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
       if (c < 0) return fail(FDAS_ERR_DEVICE, "negative candidate count");
       if (c > cap) overflow = true;
       tot += std::min(c, cap);
+      shares = shares || bucket_shares_possible(std::min(c, cap));
     }
     pre[i + 1] = pre[i] + tot;
   }
@@ -413,8 +415,10 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
         p->bbucket_cap = count;
       }
       sorted = p->d_bsort_b;
-      e = launch_bucket_sort(nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, M, M,
-                             p->d_bsort_a, p->d_bbucket, sorted, nullptr, 0, nullptr, s);
+      const BucketSort q{nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, p->d_bbucket,
+                         p->d_bsort_a, sorted, M, nullptr, 0, nullptr, nullptr};
+      e = launch_bucket_sort(q, s);
+      if (e == hipSuccess && shares) e = launch_bucket_shares(q, s);
     } else {
       e = launch_sort_batch(p->d_rb_tab, count, cap, nh, (int)M, p->rows, p->desc.z_max, p->bits_r, p->d_bsort_a,
                             p->d_bsort_b, p->d_bsort_hist, p->d_bsort_totals, &sorted, s);

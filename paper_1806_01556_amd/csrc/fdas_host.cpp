@@ -170,17 +170,19 @@ constexpr int kEarlyRecords = 8192;
 
 // Queue the ordering of one candidate list.  Bucket-sorted lists go to `out` when
 // it is given, or to `early` when they are at most kEarlyRecords (with the counts to
-// counts_out); *sorted is where the others land.
+// counts_out, and to shares_out whether launch_bucket_shares(*q) has to follow);
+// *sorted is where the others land.
 hipError_t order_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_t* d_counts, fdas_cand* out,
-                            fdas_cand* early, int32_t* counts_out, fdas_cand** sorted, hipStream_t s) {
+                            fdas_cand* early, int32_t* counts_out, int32_t* shares_out, BucketSort* q,
+                            fdas_cand** sorted, hipStream_t s) {
   const int nh = p->desc.n_harm, cap = p->desc.cand_capacity;
   if (!sort_buckets(cap))
     return launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r, p->d_sort_a,
                                   p->d_sort_b, p->d_sort_hist, p->d_sort_totals, sorted, s);
   *sorted = out ? out : p->d_sort_b;
-  return launch_bucket_sort(d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r,
-                            (int64_t)nh * cap, (int64_t)nh * cap, p->d_sort_a, p->d_bucket, *sorted, early,
-                            kEarlyRecords, counts_out, s);
+  *q = BucketSort{d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r, p->d_bucket, p->d_sort_a,
+                  *sorted, (int64_t)nh * cap, early, kEarlyRecords, counts_out, shares_out};
+  return launch_bucket_sort(*q, s);
 }
 
 hipError_t tile_order_for(fdas_plan* p, int64_t n, const int** d_order, int* blocks, int cols) {
@@ -375,7 +377,7 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
         (e = hipMalloc(&p->d_bucket, fdas::bucket_work_ints(1) * sizeof(int))) != hipSuccess ||
         (e = hipMemset(p->d_bucket, 0, fdas::bucket_work_ints(1) * sizeof(int))) != hipSuccess ||
         (e = hipDeviceSynchronize()) != hipSuccess ||
-        (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 8 * sizeof(int32_t), 0)) != hipSuccess ||
+        (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 9 * sizeof(int32_t), 0)) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_early), fdas::kEarlyRecords * sizeof(fdas_cand), 0)) !=
             hipSuccess ||
         (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max) * sizeof(int4))) != hipSuccess ||
@@ -507,12 +509,19 @@ fdas_status fdas_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
   fdas_cand* early = static_cast<fdas_cand*>(d_early);
   int32_t* hc = static_cast<int32_t*>(d_hc);
   fdas_cand* sorted = nullptr;
-  e = fdas::order_candidates(p, d_cands, d_counts, nullptr, top_k > 0 ? nullptr : early, hc, &sorted, s);
+  fdas::BucketSort bq{};
+  e = fdas::order_candidates(p, d_cands, d_counts, nullptr, top_k > 0 ? nullptr : early, hc, hc + 8, &bq, &sorted, s);
   if (e == hipSuccess && early_top) e = fdas::launch_topk(sorted, cap, nh, d_counts, top_k, early, nullptr, s);
   if (e != hipSuccess) return hip_fail(e, "ordering candidates");
   int32_t* counts = p->h_counts;
   if (!buckets) e = hipMemcpyAsync(counts, d_counts, nh * sizeof(int32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess && buckets && counts[8] > 0) {
+    // rows of thousands of records are left: order them, and what was made of the list again
+    e = fdas::launch_bucket_shares(bq, s);
+    if (e == hipSuccess && early_top) e = fdas::launch_topk(sorted, cap, nh, d_counts, top_k, early, nullptr, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  }
   if (e != hipSuccess) return hip_fail(e, "reading candidate counts");
   if (h_counts) std::copy(counts, counts + nh, h_counts);
   bool overflow = false;
@@ -573,7 +582,7 @@ fdas_status fdas_candidates_mapped(fdas_plan* p, const fdas_cand* d_cands, const
     return hip_fail(e, "allocating the page-locked result buffer");
   }
   if (!p->h_result_counts &&
-      (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_result_counts), 8 * sizeof(int32_t), 0)) != hipSuccess) {
+      (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_result_counts), 9 * sizeof(int32_t), 0)) != hipSuccess) {
     p->h_result_counts = nullptr;
     return hip_fail(e, "allocating the page-locked result counts");
   }
@@ -588,13 +597,20 @@ fdas_status fdas_candidates_mapped(fdas_plan* p, const fdas_cand* d_cands, const
   int32_t* rc = static_cast<int32_t*>(d_rc);
   // the last kernel writes the result buffer: the top-k selection (paper mode),
   // the bucket sort, or a copy of the radix-sorted records
-  e = fdas::order_candidates(p, d_cands, d_counts, keep > 0 ? nullptr : res, nullptr, keep > 0 ? nullptr : rc, &sorted,
-                             s);
+  fdas::BucketSort bq{};
+  e = fdas::order_candidates(p, d_cands, d_counts, keep > 0 ? nullptr : res, nullptr, keep > 0 ? nullptr : rc, rc + 8, &bq,
+                             &sorted, s);
   if (e == hipSuccess && keep > 0)
     e = fdas::launch_topk(sorted, cap, nh, d_counts, keep, res, rc, s);
   else if (e == hipSuccess && sorted != res)
     e = fdas::launch_copy_out(sorted, cap, nh, d_counts, nh * cap, res, rc, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess && fdas::sort_buckets(cap) && p->h_result_counts[8] > 0) {
+    // rows of thousands of records are left: order them, and what was made of the list again
+    e = fdas::launch_bucket_shares(bq, s);
+    if (e == hipSuccess && keep > 0) e = fdas::launch_topk(sorted, cap, nh, d_counts, keep, res, rc, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  }
   if (e != hipSuccess) return hip_fail(e, "ordering and reading candidates");
   const int32_t* counts = p->h_result_counts;
   if (h_counts) std::copy(counts, counts + nh, h_counts);

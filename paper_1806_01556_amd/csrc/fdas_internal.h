@@ -240,19 +240,31 @@ struct RbTrial {
   int64_t pad;
 };
 
-// Ordering by buckets, for lists of up to 65,536 records per plane
-// (sort_buckets): one list (planes, counts; trials = 1, tab NULL) or the trials of
-// a batch (tab).  `most` is at least the number of records in all, `scratch`
-// holds `most` records; work holds bucket_work_ints(trials) ints that were zero
-// before the first call.  The ordered records go to out (up to out_cap), or to
-// `early` (NULL: never) when they are at most early_cap; out, early and counts_out
-// (one list's counts; NULL skips them) may be page-locked host memory.
+// Ordering by buckets, for lists of up to 65,536 records per plane (sort_buckets):
+// one list (planes, counts; trials = 1, tab NULL) or the trials of a batch (tab).
+// out, early, counts_out and shares_out may be page-locked host memory.
+struct BucketSort {
+  const fdas_cand* planes;
+  const int32_t* counts;
+  const RbTrial* tab;
+  int trials, cap, nh, rows, z_max, bits_r;
+  int* work;           // bucket_work_ints(trials) ints, zero before the first call
+  fdas_cand* scratch;  // as many records as the lists hold
+  fdas_cand* out;      // the ordered records, up to out_cap
+  int64_t out_cap;
+  fdas_cand* early;    // where they go when they are at most early_cap (NULL: never)
+  int early_cap;
+  int32_t* counts_out;  // one list's counts (NULL skips them)
+  int32_t* shares_out;  // not 0: buckets are left to launch_bucket_shares (NULL skips it)
+};
 bool sort_buckets(int cap);
 size_t bucket_work_ints(int trials);
-hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
-                              int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
-                              int* work, fdas_cand* out, fdas_cand* early, int early_cap, int32_t* counts_out,
-                              hipStream_t s);
+hipError_t launch_bucket_sort(const BucketSort& q, hipStream_t s);
+// The buckets that launch_bucket_sort left, with the same arguments and nothing
+// changed in work and scratch between.  None is left of a list whose planes hold
+// no more records than bucket_shares_possible allows.
+bool bucket_shares_possible(int32_t plane_records);
+hipError_t launch_bucket_shares(const BucketSort& q, hipStream_t s);
 
 int sort_passes_batch(int count, int rows, int bits_r);
 

@@ -34,9 +34,9 @@ struct fdas_plan {
   int* d_sort_totals = nullptr;   // [256 * passes] digit totals per pass
   fdas_cand* h_early = nullptr; // page-locked records of short readbacks (kEarlyRecords)
   int* d_bucket = nullptr;      // bucket counters of the single-list readback (zero between calls)
-  int32_t* h_counts = nullptr;    // pinned host copy of the device counts
+  int32_t* h_counts = nullptr;    // pinned host copy of the device counts, and the shares left to order
   fdas_cand* h_result = nullptr;  // page-locked result records of fdas_candidates_mapped
-  int32_t* h_result_counts = nullptr;
+  int32_t* h_result_counts = nullptr;  // as h_counts
   int bits_r = 1;                 // bits of the column index in the sort key
   std::map<std::pair<int64_t, int>, std::pair<int*, int>> tile_orders;  // (n, tile columns) -> (device order, workgroups)
   int4* d_hitrows = nullptr;      // [harmsum_hit_entries(n_max)] rows with hits (harmonic sum phase 1)

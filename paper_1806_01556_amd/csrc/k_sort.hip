@@ -9,14 +9,17 @@
 //   k_bucket_count    records per bucket
 //   k_bucket_scatter  (r, power) pairs to their bucket's range, in any order
 //   k_bucket_sort     a workgroup orders one bucket by r and writes the records
+//                     (k_bucket_sort_small: a wave, in a batch)
+//   k_bucket_shares   only for lists with a bucket of more than 4096 records
 // The list sizes are read from the device counts, so nothing waits for the host.
 // A readback is bound by launches and their dependent latencies, not by its
 // few megabytes: 229 k records took 73 us in the 13 launches of the radix sort
 // below and take 32 us here, 7 k records 35 and 17 us.  A bucket holds the cells of
-// one row, some hundreds; the one workgroup that orders it keeps up to 4096 in
-// LDS and passes over memory for more.  That does not scale to a row of millions
-// of candidates, so longer lists are packed into one array and sorted by the
-// whole key with an LSD radix sort (8-bit digits, stable passes):
+// one row, mostly some hundreds; a workgroup orders up to 4096 in LDS, and a larger
+// bucket is divided among workgroups by rank, each of which reads all of it.  That
+// does not scale to a row of millions of candidates, so longer lists are packed
+// into one array and sorted by the whole key with an LSD radix sort (8-bit digits,
+// stable passes):
 //   k_sort_pack    packs the per-plane lists (sizes read from the device
 //                  counts, so nothing waits for the host) and clears the
 //                  per-pass digit totals
@@ -375,12 +378,27 @@ constexpr int kBucketCap = 65536;
 // --- bucket sort ----------------------------------------------------------------
 // Bucket (k - 1) * rows + row; blockIdx.y is the trial.  Work arrays per trial:
 // totals[kMaxBuckets] and cursor[kMaxBuckets], zero between calls (the plan
-// clears them once, k_bucket_sort after use), and starts[kMaxBuckets + 1].
+// clears them once, k_bucket_sort after use), starts[kMaxBuckets + 1], and the
+// shares of the large buckets: their number, then {bucket, share << 16} each.
 
 constexpr int kMaxBuckets = 8 * 129;
-constexpr int kBucketInts = 3 * kMaxBuckets + 8;  // per trial
 constexpr int kBucketLds = 4096;                  // records a workgroup orders in LDS
 constexpr int kBucketSmall = 512;                 // ... and a wave
+constexpr int SHARE_T = 1024;                     // threads of k_bucket_shares
+constexpr int kShareCount = 3 * kMaxBuckets + 1;  // index of the number of shares
+constexpr int kMaxShares = 8 * kBucketCap / 960 * 5 / 4;  // ceil(c / 960) <= 5/4 c / 960 for c > 4096
+constexpr int kBucketInts = kShareCount + 1 + kMaxShares;      // per trial
+static_assert(kMaxBuckets < (1 << 16) && kBucketCap <= (1 << 16), "share and position fields");
+
+// Shares of a bucket of c > kBucketLds records in a list of m: small ones take a
+// workgroup the least time, but each reads the whole bucket.  Whole readback of one
+// row and of eight rows of 65,536 records: 107 and 275 us in shares of 960, 112 and
+// 271 of 1920, 128 and 286 of 3584; eight rows without their way to the host (copying
+// readback) 356, 331 and 296 us.
+__device__ __forceinline__ int bucket_shares(int c, int m) {
+  const int share = m <= 2 * kBucketCap ? 960 : 3584;
+  return (c + share - 1) / share;
+}
 
 struct BucketList {
   const int4* planes;     // one list
@@ -446,6 +464,7 @@ __global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __r
   __shared__ int start[kMaxBuckets + 1];
   __shared__ int h[kMaxBuckets];
   __shared__ int s_wave[ST / 64];
+  __shared__ int s_shares;
   int64_t base;
   const BucketList bl = trial_list(all, base);
   int off[9], lo, hi;
@@ -472,6 +491,7 @@ __global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __r
     if ((t & 63) >= o) incl += u;
   }
   if ((t & 63) == 63) s_wave[t >> 6] = incl;
+  if (t == 0) s_shares = 0;
   __syncthreads();
   int at = incl - sum;
   for (int q = 0; q < (t >> 6); ++q) at += s_wave[q];
@@ -481,12 +501,21 @@ __global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __r
     if (b < nb) {
       start[b] = at;
       h[b] = 0;
-      if (blockIdx.x == 0) starts[b] = at;
+      if (blockIdx.x == 0) {
+        starts[b] = at;
+        if (own[q] > kBucketLds) {
+          const int W = bucket_shares(own[q], m);
+          const int first = atomicAdd(&s_shares, W);
+          for (int w = 0; w < W; ++w)
+            if (first + w < kMaxShares) bl.work[kShareCount + 1 + first + w] = b | (w << 16);
+        }
+      }
       at += own[q];
     }
   }
   if (blockIdx.x == 0 && t == 0) starts[nb] = m;
   __syncthreads();
+  if (blockIdx.x == 0 && t == 0) bl.work[kShareCount] = min(s_shares, kMaxShares);
   for (int i = lo + t; i < hi; i += ST) {
     int b;
     bucket_record(bl, off, i, b);
@@ -503,69 +532,6 @@ __global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __r
     const int4 rec = bucket_record(bl, off, i, b);
     pairs[base + start[b] + atomicAdd(&h[b], 1)] = make_int2(rec.z, rec.w);
   }
-}
-
-// Stable LSD radix sort by r of c pairs in memory by one workgroup; returns the
-// buffer that holds the result.
-__device__ int2* bucket_radix(int2* a, int2* tmp, int c, int passes, int* hist, int (*wcnt)[256]) {
-  const int t = threadIdx.x, w = t >> 6;
-  __shared__ int s_wave[ST / 64];
-  int2 *src = a, *dst = tmp;
-  for (int p = 0; p < passes; ++p) {
-    const int shift = 8 * p;
-    hist[t] = 0;
-#pragma unroll
-    for (int q = 0; q < ST / 64; ++q) wcnt[q][t] = 0;
-    __syncthreads();
-    for (int i = t; i < c; i += ST) atomicAdd(&hist[((unsigned)src[i].x >> shift) & 255u], 1);
-    __syncthreads();
-    const int own = hist[t];
-    int incl = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(incl, o);
-      if ((t & 63) >= o) incl += u;
-    }
-    if ((t & 63) == 63) s_wave[w] = incl;
-    __syncthreads();
-    for (int q = 0; q < w; ++q) incl += s_wave[q];
-    hist[t] = incl - own;
-    __syncthreads();
-    for (int i0 = 0; i0 < c; i0 += ST) {
-      const int i = i0 + t;
-      const bool valid = i < c;
-      const int2 v = valid ? src[i] : make_int2(0, 0);
-      const int d = valid ? (int)(((unsigned)v.x >> shift) & 255u) : 0;
-      unsigned long long peers = __ballot(valid);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const unsigned long long m1 = __ballot((d >> b) & 1);
-        peers &= ((d >> b) & 1) ? m1 : ~m1;
-      }
-      const int rank =
-          __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
-      if (valid && rank == 0) wcnt[w][d] = __popcll(peers);
-      __syncthreads();
-      if (valid) {
-        int pos = hist[d] + rank;
-        for (int q = 0; q < w; ++q) pos += wcnt[q][d];
-        dst[pos] = v;
-      }
-      __syncthreads();
-      int add = 0;
-#pragma unroll
-      for (int q = 0; q < ST / 64; ++q) {
-        add += wcnt[q][t];
-        wcnt[q][t] = 0;
-      }
-      hist[t] += add;
-      __syncthreads();
-    }
-    int2* x = src;
-    src = dst;
-    dst = x;
-  }
-  return src;
 }
 
 // Ascending bitonic sort of N keys (a power of two, at least 64) by TH threads, t
@@ -629,14 +595,181 @@ __global__ __launch_bounds__(ST) void k_bucket_sort_small(BucketList all, const 
     if (i < room) out[base + s0 + i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
 }
 
-// Orders bucket blockIdx.x if it holds more than `above` records and writes them;
-// records past out_cap are dropped.  When all the list's records fit in early_cap,
-// they go to `early` (page-locked memory) instead of out; with counts_out the
-// counts go out too.
-__global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __restrict__ pairs, int2* __restrict__ tmp,
-                                                    int passes, int above, int64_t out_cap, int4* __restrict__ out,
-                                                    int4* __restrict__ early, int early_cap,
-                                                    int32_t* __restrict__ counts_out) {
+// Gathers records of a bucket of c, those with ranks [p0, p1) among them, as
+// keys (r << 32 | position) in any order: at most kBucketLds, all those of ranks
+// [p0 - *skip, p0 - *skip + the count returned) in the order of these keys.  A
+// radix select of 12 bits a round over (r, position), distinct whatever the records
+// hold, narrows the two ends until what lies between them fits: one round unless a
+// digit at an end holds more records than there is room for.  A
+// whole workgroup reads the bucket once per round, and once more for the keys;
+// `keys` is the histograms' memory until then.  What bounds it is latency: U loads at a
+// time without a branch between them, the next ones under way, one LDS reservation
+// for all that a wave finds in them.
+__device__ __forceinline__ int bucket_share_keys(const int2* __restrict__ mine, int c, int p0, int p1, int bits_r,
+                                                 unsigned long long* keys, int* skip) {
+  constexpr int DIG = 12, U = 8;
+  __shared__ int s_wave[2][SHARE_T / 64];
+  __shared__ int s_bin[2], s_need[2], s_size[2], s_n;
+  static_assert(2 * sizeof(int) << DIG <= sizeof(unsigned long long) * kBucketLds, "two histograms");
+  int(*hist)[1 << DIG] = reinterpret_cast<int(*)[1 << DIG]>(keys);
+  const int t = threadIdx.x, lane = t & 63;
+  const unsigned top = bits_r < 32 ? (1u << bits_r) - 1u : ~0u;
+  // batch(r, i0): r of the records i0 + u SHARE_T, u < U (past the end: the last one's)
+  auto each = [&](auto batch) {
+    unsigned next[U];
+    auto load = [&](int i0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) next[u] = (unsigned)mine[min(i0 + u * SHARE_T, c - 1)].x;
+    };
+    load(t);
+    for (int i0 = t; i0 - t < c; i0 += U * SHARE_T) {
+      unsigned r[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) r[u] = min(next[u], top);
+      load(i0 + U * SHARE_T);  // in flight while this batch is worked on
+      batch(r, i0);
+    }
+  };
+  // the ends: keys below prefix[0] << left rank before p0 - need[0]; those up to
+  // prefix[1] << left and its digit's rest rank before p1 - 1 - need[1] + size[1]
+  unsigned long long prefix[2] = {0ull, 0ull};
+  int need[2] = {p0, p1 - 1}, size[2] = {c, c};
+  int left = bits_r + 16;
+  auto between = [&]() { return p1 - 1 - need[1] + size[1] - (p0 - need[0]); };
+  while (between() > kBucketLds) {  // uniform
+    // a digit lies within r or within the position; at no bits left every digit is one record
+    const int width = min(DIG, left > 16 ? left - 16 : left), shift = left - width;
+    const unsigned mask = (1u << width) - 1u;
+    const bool one = prefix[0] == prefix[1];  // the same records count for both ends
+    for (int e = t; e < 2 << DIG; e += SHARE_T) (&hist[0][0])[e] = 0;
+    __syncthreads();
+    if (left == bits_r + 16) {
+      const int sh = shift - 16;  // bits_r > 0
+      each([&](const unsigned (&r)[U], int i0) {
+        const bool whole = i0 - t + U * SHARE_T <= c;  // uniform
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const unsigned d = r[u] >> sh;
+          // neighbours in the list are often neighbours in r: one addition for a wave of one digit
+          const unsigned first = (unsigned)__builtin_amdgcn_readfirstlane((int)d);
+          if (whole && __ballot(d != first) == 0ull) {
+            if (lane == 0) atomicAdd(&hist[0][first], 64);
+          } else if (i0 + u * SHARE_T < c) {
+            atomicAdd(&hist[0][d], 1);
+          }
+        }
+      });
+    } else {
+      each([&](const unsigned (&r)[U], int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * SHARE_T;
+          const unsigned long long v = (((unsigned long long)r[u] << 16) | (unsigned)i) >> shift, up = v >> width;
+          if (i < c && up == prefix[0]) atomicAdd(&hist[0][(unsigned)v & mask], 1);
+          if (i < c && !one && up == prefix[1]) atomicAdd(&hist[1][(unsigned)v & mask], 1);
+        }
+      });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int* h = hist[one ? 0 : j];
+      constexpr int PER = (1 << DIG) / SHARE_T;
+      int sum = 0;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) sum += h[t * PER + q];
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+      }
+      if (lane == 63) s_wave[j][t >> 6] = incl;
+      __syncthreads();
+      for (int q = 0; q < (t >> 6); ++q) incl += s_wave[j][q];
+      int below = incl - sum;
+      if (need[j] >= below && need[j] < incl) {  // one thread
+        for (int q = 0; q < PER; ++q) {
+          const int v = h[t * PER + q];
+          if (need[j] >= below && need[j] < below + v) {
+            s_bin[j] = t * PER + q;
+            s_need[j] = need[j] - below;
+            s_size[j] = v;
+          }
+          below += v;
+        }
+      }
+      __syncthreads();
+      prefix[j] = (prefix[j] << width) | (unsigned)s_bin[j];
+      need[j] = s_need[j];
+      size[j] = s_size[j];
+    }
+    left = shift;
+  }
+  *skip = need[0];
+  if (t == 0) s_n = 0;
+  __syncthreads();
+  each([&](const unsigned (&r)[U], int i0) {
+    unsigned found = 0u;  // bit u
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * SHARE_T;
+      const unsigned long long k = (((unsigned long long)r[u] << 16) | (unsigned)i) >> left;
+      found |= i < c && k >= prefix[0] && k <= prefix[1] ? 1u << u : 0u;
+    }
+    if (__ballot(found != 0u) == 0ull) return;  // uniform
+    const int cnt = __popc(found);
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    int at = 0;
+    if (lane == 63) at = atomicAdd(&s_n, incl);
+    at = __builtin_amdgcn_readlane(at, 63) + incl - cnt;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if ((found >> u) & 1u) {
+        if (at < kBucketLds) keys[at] = ((unsigned long long)r[u] << 32) | (unsigned)(i0 + u * SHARE_T);
+        ++at;
+      }
+  });
+  return between();
+}
+
+// Keys [0, got) put in order by TH threads, and cnt of them from `skip` on written
+// from out[first] on as records of bucket b: (r, power), or (r, position) of the
+// bucket's records in `from`.  Records past out_cap are dropped.
+template <int TH>
+__device__ __forceinline__ void order_and_write(const BucketList& bl, unsigned long long* keys, int got, int b, int skip,
+                                                int cnt, const int2* __restrict__ from, int4* __restrict__ out,
+                                                int64_t first, int64_t out_cap) {
+  const int t = threadIdx.x;
+  int N = 64;
+  while (N < got) N <<= 1;
+  for (int i = got + t; i < N; i += TH) keys[i] = ~0ull;  // orders last: r >= 0
+  __syncthreads();
+  bitonic<TH>(keys, N, t);
+  __syncthreads();
+  const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
+  const int64_t room = out_cap - first;
+  for (int i = t; i < cnt; i += TH)
+    if (i < room) {
+      const unsigned long long k = keys[skip + i];
+      const int2 v = from ? from[(unsigned)k] : make_int2((int)(k >> 32), (int)(unsigned)k);
+      out[first + i] = make_int4(harm, z, v.x, v.y);
+    }
+}
+
+// Orders bucket blockIdx.x if it holds more than `above` records and at most
+// kBucketLds, and writes them.  When all the list's records fit in early_cap, they
+// go to `early` (page-locked memory) instead of out; with counts_out the counts go
+// out too, with shares_out the number of shares left to k_bucket_shares.
+__global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, const int2* __restrict__ pairs, int above,
+                                                    int64_t out_cap, int4* __restrict__ out, int4* __restrict__ early,
+                                                    int early_cap, int32_t* __restrict__ counts_out,
+                                                    int32_t* __restrict__ shares_out) {
   __shared__ unsigned long long keys[kBucketLds];
   int64_t base;
   const BucketList bl = trial_list(all, base);
@@ -644,32 +777,45 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, int2* __rest
   const int* starts = bl.work + 2 * kMaxBuckets;
   const int s0 = starts[b], c = starts[b + 1] - s0;
   if (counts_out && b == 0 && t < bl.nh) counts_out[t] = bl.counts[t];
+  if (shares_out && b == 0 && t == 0) *shares_out = bl.work[kShareCount];
   // an empty bucket's total and cursor are zero already
   if (c <= above) return;  // uniform
   if (t == 0) {
     bl.work[b] = 0;
     bl.work[kMaxBuckets + b] = 0;
   }
+  if (c > kBucketLds) return;  // uniform
   if (early && starts[bl.nh * bl.rows] <= early_cap) out = early;
-  const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
-  int2* mine = pairs + base + s0;
-  int4* dst = out + base + s0;
-  const int64_t room = out_cap - (base + s0);
-  if (c > kBucketLds) {
-    int* h = reinterpret_cast<int*>(keys);
-    const int2* r = bucket_radix(mine, tmp + base + s0, c, passes, h, reinterpret_cast<int(*)[256]>(h + 256));
-    for (int i = t; i < c; i += ST)
-      if (i < room) dst[i] = make_int4(harm, z, r[i].x, r[i].y);
-    return;
+  for (int i = t; i < c; i += ST) keys[i] = bucket_key(pairs + base + s0, i, c);
+  order_and_write<ST>(bl, keys, c, b, 0, c, nullptr, out, base + s0, out_cap);
+}
+
+// The buckets of more than kBucketLds records, in shares dealt to the workgroups.
+// Interference that fills a row, or a plan of few rows, brings up to 65,536 records
+// to a bucket.  The host launches this only for a list that has such a bucket: it
+// learns so with the counts it waits for (a single list) or sees that a plane holds
+// enough records (a batch), so the usual readback pays nothing for it.  Whole readback
+// of 65,536 records of one row: 106 us; 100 us in the radix sort of the whole
+// key, 686 us with one workgroup that passed over them in memory.
+__global__ __launch_bounds__(SHARE_T) void k_bucket_shares(BucketList all, const int2* __restrict__ pairs, int bits_r,
+                                                           int64_t out_cap, int4* __restrict__ out,
+                                                           int4* __restrict__ early, int early_cap) {
+  __shared__ unsigned long long keys[kBucketLds];
+  int64_t base;
+  const BucketList bl = trial_list(all, base);
+  const int* starts = bl.work + 2 * kMaxBuckets;
+  const int shares = bl.work[kShareCount];
+  if (early && starts[bl.nh * bl.rows] <= early_cap) out = early;
+  for (int e = blockIdx.x; e < shares; e += gridDim.x) {  // uniform
+    const int v = bl.work[kShareCount + 1 + e], b = v & 0xffff, w = v >> 16;
+    const int s0 = starts[b], c = starts[b + 1] - s0, W = bucket_shares(c, starts[bl.nh * bl.rows]);
+    const int2* mine = pairs + base + s0;
+    const int p0 = (int)((int64_t)c * w / W), cnt = (int)((int64_t)c * (w + 1) / W) - p0;
+    int skip;
+    const int got = bucket_share_keys(mine, c, p0, p0 + cnt, bits_r, keys, &skip);
+    order_and_write<SHARE_T>(bl, keys, got, b, skip, cnt, mine, out, base + s0 + p0, out_cap);
+    __syncthreads();  // the keys are read
   }
-  int N = 64;
-  while (N < c) N <<= 1;
-  for (int i = t; i < N; i += ST) keys[i] = bucket_key(mine, i, c);
-  __syncthreads();
-  bitonic<ST>(keys, N, t);
-  __syncthreads();
-  for (int i = t; i < c; i += ST)
-    if (i < room) dst[i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
 }
 
 // The ordered records and the counts written straight into page-locked host
@@ -720,30 +866,43 @@ bool sort_buckets(int cap) { return cap <= kBucketCap; }
 
 size_t bucket_work_ints(int trials) { return (size_t)trials * kBucketInts; }
 
-hipError_t launch_bucket_sort(const fdas_cand* planes, const int32_t* counts, const RbTrial* tab, int trials, int cap,
-                              int nh, int rows, int z_max, int bits_r, int64_t most, int64_t out_cap, fdas_cand* scratch,
-                              int* work, fdas_cand* out, fdas_cand* early, int early_cap, int32_t* counts_out,
-                              hipStream_t s) {
-  if (nh < 1 || rows < 1 || nh * rows > kMaxBuckets || trials < 1 || !work) return hipErrorInvalidValue;
-  const BucketList bl{reinterpret_cast<const int4*>(planes), counts, tab, cap, nh, rows, z_max, work};
-  // the scratch records hold the scattered pairs and, after them, the radix passes' other buffer
-  int2* pairs = reinterpret_cast<int2*>(scratch);
-  int2* tmp = pairs + most;
-  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)nh * cap + ST - 1) / ST));
-  const dim3 buckets((unsigned)(nh * rows), trials);
-  const int passes = (bits_r + 7) / 8;
-  int4* dst = reinterpret_cast<int4*>(out);
-  int4* fast = reinterpret_cast<int4*>(early);
+namespace {
+bool bucket_list(const BucketSort& q, BucketList& bl) {
+  if (q.nh < 1 || q.rows < 1 || q.nh * q.rows > kMaxBuckets || !sort_buckets(q.cap) || q.trials < 1 || !q.work)
+    return false;
+  bl = BucketList{reinterpret_cast<const int4*>(q.planes), q.counts, q.tab, q.cap, q.nh, q.rows, q.z_max, q.work};
+  return true;
+}
+}  // namespace
+
+hipError_t launch_bucket_sort(const BucketSort& q, hipStream_t s) {
+  BucketList bl;
+  if (!bucket_list(q, bl)) return hipErrorInvalidValue;
+  int2* pairs = reinterpret_cast<int2*>(q.scratch);
+  int4 *out = reinterpret_cast<int4*>(q.out), *early = reinterpret_cast<int4*>(q.early);
+  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)q.nh * q.cap + ST - 1) / ST));
+  const unsigned buckets = (unsigned)(q.nh * q.rows), trials = (unsigned)q.trials;
   hipLaunchKernelGGL(k_bucket_count, dim3(wgs, trials), dim3(ST), 0, s, bl);
   hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, pairs);
   int above = 0;
   if (trials > 1) {
-    hipLaunchKernelGGL(k_bucket_sort_small, dim3((unsigned)(nh * rows + ST / 64 - 1) / (ST / 64), trials), dim3(ST), 0, s,
-                       bl, pairs, out_cap, dst);
+    hipLaunchKernelGGL(k_bucket_sort_small, dim3((buckets + ST / 64 - 1) / (ST / 64), trials), dim3(ST), 0, s, bl, pairs,
+                       q.out_cap, out);
     above = kBucketSmall;
   }
-  hipLaunchKernelGGL(k_bucket_sort, buckets, dim3(ST), 0, s, bl, pairs, tmp, passes, above, out_cap, dst,
-                     fast, early_cap, counts_out);
+  hipLaunchKernelGGL(k_bucket_sort, dim3(buckets, trials), dim3(ST), 0, s, bl, pairs, above, q.out_cap, out, early,
+                     q.early_cap, q.counts_out, q.shares_out);
+  return hipGetLastError();
+}
+
+bool bucket_shares_possible(int32_t plane_records) { return plane_records > kBucketLds; }
+
+hipError_t launch_bucket_shares(const BucketSort& q, hipStream_t s) {
+  BucketList bl;
+  if (!bucket_list(q, bl)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_bucket_shares, dim3(q.trials > 1 ? 96 : 512, (unsigned)q.trials), dim3(SHARE_T), 0, s, bl,
+                     reinterpret_cast<const int2*>(q.scratch), q.bits_r, q.out_cap, reinterpret_cast<int4*>(q.out),
+                     reinterpret_cast<int4*>(q.early), q.early_cap);
   return hipGetLastError();
 }
 
