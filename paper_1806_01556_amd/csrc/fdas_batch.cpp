@@ -350,7 +350,8 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
   bool overflow = false;
   // record i of trial t lands at pre[t] + i of one trial-major array
   std::vector<int64_t> pre(count + 1, 0);
-  bool shares = false;  // a row may hold more records than one workgroup orders
+  int64_t most = 0;     // records of the longest trial
+  bool shares = false;  // a row may hold more records than a wave orders
   for (int i = 0; i < count; ++i) {
     int64_t tot = 0;
     for (int k = 0; k < nh; ++k) {
@@ -358,9 +359,10 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
       if (c < 0) return fail(FDAS_ERR_DEVICE, "negative candidate count");
       if (c > cap) overflow = true;
       tot += std::min(c, cap);
-      shares = shares || bucket_shares_possible(std::min(c, cap));
+      shares = shares || batch_shares_possible(std::min(c, cap));
     }
     pre[i + 1] = pre[i] + tot;
+    most = std::max(most, tot);
   }
   const int64_t M = pre[count];
   if (M > INT32_MAX / 2) return fail(FDAS_ERR_CAPACITY, "%lld candidates in one batch readback", (long long)M);
@@ -415,8 +417,8 @@ fdas_status fdas_candidates_batch(fdas_plan* p, const fdas_trial* h_trials, int3
         p->bbucket_cap = count;
       }
       sorted = p->d_bsort_b;
-      const BucketSort q{nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, p->d_bbucket,
-                         p->d_bsort_a, sorted, M, nullptr, 0, nullptr, nullptr};
+      const BucketSort q{nullptr, nullptr, p->d_rb_tab, count, cap, nh, p->rows, p->desc.z_max, p->bits_r, most,
+                         p->d_bbucket, p->d_bsort_a, sorted, M, nullptr, 0, nullptr, nullptr};
       e = launch_bucket_sort(q, s);
       if (e == hipSuccess && shares) e = launch_bucket_shares(q, s);
     } else {

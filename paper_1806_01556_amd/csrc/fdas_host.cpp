@@ -180,8 +180,9 @@ hipError_t order_candidates(fdas_plan* p, const fdas_cand* d_cands, const int32_
     return launch_sort_candidates(d_cands, cap, nh, d_counts, p->rows, p->desc.z_max, p->bits_r, p->d_sort_a,
                                   p->d_sort_b, p->d_sort_hist, p->d_sort_totals, sorted, s);
   *sorted = out ? out : p->d_sort_b;
-  *q = BucketSort{d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r, p->d_bucket, p->d_sort_a,
-                  *sorted, (int64_t)nh * cap, early, kEarlyRecords, counts_out, shares_out};
+  const int64_t most = (int64_t)nh * cap;
+  *q = BucketSort{d_cands, d_counts, nullptr, 1, cap, nh, p->rows, p->desc.z_max, p->bits_r, most, p->d_bucket,
+                  p->d_sort_a, *sorted, most, early, kEarlyRecords, counts_out, shares_out};
   return launch_bucket_sort(*q, s);
 }
 

@@ -248,6 +248,7 @@ struct BucketSort {
   const int32_t* counts;
   const RbTrial* tab;
   int trials, cap, nh, rows, z_max, bits_r;
+  int64_t most;        // records of the longest list, at most
   int* work;           // bucket_work_ints(trials) ints, zero before the first call
   fdas_cand* scratch;  // as many records as the lists hold
   fdas_cand* out;      // the ordered records, up to out_cap
@@ -255,15 +256,15 @@ struct BucketSort {
   fdas_cand* early;    // where they go when they are at most early_cap (NULL: never)
   int early_cap;
   int32_t* counts_out;  // one list's counts (NULL skips them)
-  int32_t* shares_out;  // not 0: buckets are left to launch_bucket_shares (NULL skips it)
+  int32_t* shares_out;  // set to 0 if none of one list's buckets is left to launch_bucket_shares
 };
 bool sort_buckets(int cap);
 size_t bucket_work_ints(int trials);
 hipError_t launch_bucket_sort(const BucketSort& q, hipStream_t s);
 // The buckets that launch_bucket_sort left, with the same arguments and nothing
-// changed in work and scratch between.  None is left of a list whose planes hold
-// no more records than bucket_shares_possible allows.
-bool bucket_shares_possible(int32_t plane_records);
+// changed in work and scratch between; of a batch, none is left unless
+// batch_shares_possible for a plane.
+bool batch_shares_possible(int32_t plane_records);
 hipError_t launch_bucket_shares(const BucketSort& q, hipStream_t s);
 
 int sort_passes_batch(int count, int rows, int bits_r);

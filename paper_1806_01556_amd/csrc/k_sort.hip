@@ -9,7 +9,6 @@
 //   k_bucket_count    records per bucket
 //   k_bucket_scatter  (r, power) pairs to their bucket's range, in any order
 //   k_bucket_sort     a workgroup orders one bucket by r and writes the records
-//                     (k_bucket_sort_small: a wave, in a batch)
 //   k_bucket_shares   only for lists with a bucket of more than 4096 records
 // The list sizes are read from the device counts, so nothing waits for the host.
 // A readback is bound by launches and their dependent latencies, not by its
@@ -34,7 +33,8 @@
 // records); tiles past the actual count return at once.
 //
 // A batch of trials is ordered into one trial-major array: every trial has its
-// own buckets, or, in the radix sort (k_sort_pack_batch), records carry their
+// own buckets, which k_bucket_sort_small (a wave to a bucket) and k_bucket_shares
+// order, launched for as many records as the longest trial holds; or, in the radix sort (k_sort_pack_batch), records carry their
 // trial number in bits 8 and up of the harmonic field and the key puts the trial
 // above the plane slot; the last scatter pass clears the tag.  The batch record
 // count is known to the host, so those launches are sized exactly.
@@ -378,25 +378,26 @@ constexpr int kBucketCap = 65536;
 // --- bucket sort ----------------------------------------------------------------
 // Bucket (k - 1) * rows + row; blockIdx.y is the trial.  Work arrays per trial:
 // totals[kMaxBuckets] and cursor[kMaxBuckets], zero between calls (the plan
-// clears them once, k_bucket_sort after use), starts[kMaxBuckets + 1], and the
-// shares of the large buckets: their number, then {bucket, share << 16} each.
+// clears them once, k_bucket_sort or k_bucket_sort_small after use),
+// starts[kMaxBuckets + 1], and the shares of the buckets that those kernels leave
+// (more than 4096 and 512 records): their number, then {bucket, share << 16} each.
 
 constexpr int kMaxBuckets = 8 * 129;
 constexpr int kBucketLds = 4096;                  // records a workgroup orders in LDS
 constexpr int kBucketSmall = 512;                 // ... and a wave
 constexpr int SHARE_T = 1024;                     // threads of k_bucket_shares
 constexpr int kShareCount = 3 * kMaxBuckets + 1;  // index of the number of shares
-constexpr int kMaxShares = 8 * kBucketCap / 960 * 5 / 4;  // ceil(c / 960) <= 5/4 c / 960 for c > 4096
+constexpr int kMaxShares = 8 * kBucketCap / kBucketSmall;  // no share has fewer than 512 records
 constexpr int kBucketInts = kShareCount + 1 + kMaxShares;      // per trial
 static_assert(kMaxBuckets < (1 << 16) && kBucketCap <= (1 << 16), "share and position fields");
 
-// Shares of a bucket of c > kBucketLds records in a list of m: small ones take a
-// workgroup the least time, but each reads the whole bucket.  Whole readback of one
+// Shares of a bucket of c records in a list of m, one up to kBucketLds.  Small ones take
+// a workgroup the least time, but each reads the whole bucket.  Whole readback of one
 // row and of eight rows of 65,536 records: 107 and 275 us in shares of 960, 112 and
 // 271 of 1920, 128 and 286 of 3584; eight rows without their way to the host (copying
 // readback) 356, 331 and 296 us.
 __device__ __forceinline__ int bucket_shares(int c, int m) {
-  const int share = m <= 2 * kBucketCap ? 960 : 3584;
+  const int share = c <= kBucketLds ? kBucketLds : m <= 2 * kBucketCap ? 960 : 3584;
   return (c + share - 1) / share;
 }
 
@@ -460,7 +461,8 @@ __global__ __launch_bounds__(ST) void k_bucket_count(BucketList all) {
     if (h[b]) atomicAdd(&bl.work[b], h[b]);
 }
 
-__global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __restrict__ pairs) {
+// Buckets of more than `above` records become shares.
+__global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int above, int2* __restrict__ pairs) {
   __shared__ int start[kMaxBuckets + 1];
   __shared__ int h[kMaxBuckets];
   __shared__ int s_wave[ST / 64];
@@ -503,7 +505,7 @@ __global__ __launch_bounds__(ST) void k_bucket_scatter(BucketList all, int2* __r
       h[b] = 0;
       if (blockIdx.x == 0) {
         starts[b] = at;
-        if (own[q] > kBucketLds) {
+        if (own[q] > above) {
           const int W = bucket_shares(own[q], m);
           const int first = atomicAdd(&s_shares, W);
           for (int w = 0; w < W; ++w)
@@ -564,35 +566,44 @@ __device__ __forceinline__ unsigned long long bucket_key(const int2* mine, int i
   return ((unsigned long long)(unsigned)v.x << 32) | (unsigned)v.y;
 }
 
-// Orders the buckets of up to kBucketSmall records, a wave each; larger ones are
-// left to k_bucket_sort.  The trials of a batch have thousands of buckets, most
-// with a few records: 16 trials 46 us with a workgroup and 32 KB of LDS for every
-// bucket, 35 with 4 KB for the small ones, 21 for both launches with a wave each.
-__global__ __launch_bounds__(ST) void k_bucket_sort_small(BucketList all, const int2* __restrict__ pairs,
+// Orders the buckets of up to kBucketSmall records, a wave to `span` (at most 64)
+// of them; larger ones are left to k_bucket_shares.  The trials of a batch have
+// thousands of buckets, most with a few records or none: 16 trials of 7 k records
+// 46 us with a workgroup and 32 KB of LDS for every bucket, 35 with 4 KB for the
+// small ones, 21 with a wave each.
+__global__ __launch_bounds__(ST) void k_bucket_sort_small(BucketList all, const int2* __restrict__ pairs, int span,
                                                           int64_t out_cap, int4* __restrict__ out) {
   __shared__ unsigned long long s_keys[ST / 64][kBucketSmall];
   int64_t base;
   const BucketList bl = trial_list(all, base);
-  const int b = (int)blockIdx.x * (ST / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (b >= bl.nh * bl.rows) return;  // uniform per wave; no barrier follows
+  const int nb = bl.nh * bl.rows, lane = threadIdx.x & 63;
+  const int b0 = ((int)blockIdx.x * (ST / 64) + (threadIdx.x >> 6)) * span;  // no barrier follows
   const int* starts = bl.work + 2 * kMaxBuckets;
-  const int s0 = starts[b], c = starts[b + 1] - s0;
-  if (c <= 0 || c > kBucketSmall) return;
-  if (lane == 0) {
-    bl.work[b] = 0;
-    bl.work[kMaxBuckets + b] = 0;
+  // lane l looks at bucket b0 + l
+  const bool in = lane < span && b0 + lane < nb;
+  const int at = in ? starts[b0 + lane] : 0;
+  const int held = in ? starts[b0 + lane + 1] - at : 0;
+  if (held > 0) {
+    bl.work[b0 + lane] = 0;
+    bl.work[kMaxBuckets + b0 + lane] = 0;
   }
   unsigned long long* keys = s_keys[threadIdx.x >> 6];
-  int N = 64;
-  while (N < c) N <<= 1;
-  for (int i = lane; i < N; i += 64) keys[i] = bucket_key(pairs + base + s0, i, c);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  bitonic<64>(keys, N, lane);
-  const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
-  const int64_t room = out_cap - (base + s0);
-  for (int i = lane; i < c; i += 64)
-    if (i < room) out[base + s0 + i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
+  for (unsigned long long todo = __ballot(held > 0 && held <= kBucketSmall); todo != 0ull; todo &= todo - 1ull) {
+    const int l = (int)__builtin_ctzll(todo), b = b0 + l;
+    const int s0 = __builtin_amdgcn_readlane(at, l), c = __builtin_amdgcn_readlane(held, l);
+    int N = 64;
+    while (N < c) N <<= 1;
+    for (int i = lane; i < N; i += 64) keys[i] = bucket_key(pairs + base + s0, i, c);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    bitonic<64>(keys, N, lane);
+    const int harm = b / bl.rows + 1, z = b % bl.rows - bl.z_max;
+    const int64_t room = out_cap - (base + s0);
+    for (int i = lane; i < c; i += 64)
+      if (i < room) out[base + s0 + i] = make_int4(harm, z, (int)(keys[i] >> 32), (int)(unsigned)keys[i]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // Gathers records of a bucket of c, those with ranks [p0, p1) among them, as
@@ -762,12 +773,11 @@ __device__ __forceinline__ void order_and_write(const BucketList& bl, unsigned l
     }
 }
 
-// Orders bucket blockIdx.x if it holds more than `above` records and at most
-// kBucketLds, and writes them.  When all the list's records fit in early_cap, they
+// Orders bucket blockIdx.x of a list, if it holds at most kBucketLds records, and
+// writes them.  When all the list's records fit in early_cap, they
 // go to `early` (page-locked memory) instead of out; with counts_out the counts go
 // out too, with shares_out the number of shares left to k_bucket_shares.
-__global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, const int2* __restrict__ pairs, int above,
-                                                    int64_t out_cap, int4* __restrict__ out, int4* __restrict__ early,
+__global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, const int2* __restrict__ pairs, int64_t out_cap, int4* __restrict__ out, int4* __restrict__ early,
                                                     int early_cap, int32_t* __restrict__ counts_out,
                                                     int32_t* __restrict__ shares_out) {
   __shared__ unsigned long long keys[kBucketLds];
@@ -779,7 +789,7 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, const int2* 
   if (counts_out && b == 0 && t < bl.nh) counts_out[t] = bl.counts[t];
   if (shares_out && b == 0 && t == 0) *shares_out = bl.work[kShareCount];
   // an empty bucket's total and cursor are zero already
-  if (c <= above) return;  // uniform
+  if (c <= 0) return;  // uniform
   if (t == 0) {
     bl.work[b] = 0;
     bl.work[kMaxBuckets + b] = 0;
@@ -790,11 +800,11 @@ __global__ __launch_bounds__(ST) void k_bucket_sort(BucketList all, const int2* 
   order_and_write<ST>(bl, keys, c, b, 0, c, nullptr, out, base + s0, out_cap);
 }
 
-// The buckets of more than kBucketLds records, in shares dealt to the workgroups.
+// The buckets that the other kernels leave, in shares dealt to the workgroups.
 // Interference that fills a row, or a plan of few rows, brings up to 65,536 records
-// to a bucket.  The host launches this only for a list that has such a bucket: it
-// learns so with the counts it waits for (a single list) or sees that a plane holds
-// enough records (a batch), so the usual readback pays nothing for it.  Whole readback
+// to a bucket.  For a single list the host launches this only if there is a share,
+// which it learns with the counts that it waits for, so the usual readback pays
+// nothing for it; for a batch, if a plane holds enough records.  Whole readback
 // of 65,536 records of one row: 106 us; 100 us in the radix sort of the whole
 // key, 686 us with one workgroup that passed over them in memory.
 __global__ __launch_bounds__(SHARE_T) void k_bucket_shares(BucketList all, const int2* __restrict__ pairs, int bits_r,
@@ -812,7 +822,7 @@ __global__ __launch_bounds__(SHARE_T) void k_bucket_shares(BucketList all, const
     const int2* mine = pairs + base + s0;
     const int p0 = (int)((int64_t)c * w / W), cnt = (int)((int64_t)c * (w + 1) / W) - p0;
     int skip;
-    const int got = bucket_share_keys(mine, c, p0, p0 + cnt, bits_r, keys, &skip);
+    const int got = bucket_share_keys(mine, c, p0, p0 + cnt, bits_r, keys, &skip);  // all of them if c <= kBucketLds
     order_and_write<SHARE_T>(bl, keys, got, b, skip, cnt, mine, out, base + s0 + p0, out_cap);
     __syncthreads();  // the keys are read
   }
@@ -880,27 +890,35 @@ hipError_t launch_bucket_sort(const BucketSort& q, hipStream_t s) {
   if (!bucket_list(q, bl)) return hipErrorInvalidValue;
   int2* pairs = reinterpret_cast<int2*>(q.scratch);
   int4 *out = reinterpret_cast<int4*>(q.out), *early = reinterpret_cast<int4*>(q.early);
-  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, ((int64_t)q.nh * q.cap + ST - 1) / ST));
+  // Workgroups for the records that a list can hold.  Sized for the capacity, 1024
+  // trials of 10 records took 847 us, the readback with the radix sort 372; sized
+  // for their records 250.
+  const unsigned wgs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (q.most + ST - 1) / ST));
   const unsigned buckets = (unsigned)(q.nh * q.rows), trials = (unsigned)q.trials;
   hipLaunchKernelGGL(k_bucket_count, dim3(wgs, trials), dim3(ST), 0, s, bl);
-  hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, pairs);
-  int above = 0;
-  if (trials > 1) {
-    hipLaunchKernelGGL(k_bucket_sort_small, dim3((buckets + ST / 64 - 1) / (ST / 64), trials), dim3(ST), 0, s, bl, pairs,
-                       q.out_cap, out);
-    above = kBucketSmall;
+  hipLaunchKernelGGL(k_bucket_scatter, dim3(wgs, trials), dim3(ST), 0, s, bl, q.tab ? kBucketSmall : kBucketLds, pairs);
+  if (q.tab) {
+    // a wave to some two buckets with records, or to more where 16,384 waves, two
+    // rounds of the chip, have them all
+    const int64_t want = std::max<int64_t>(2 * (int64_t)buckets / std::max<int64_t>(1, q.most),
+                                           (int64_t)buckets * trials / 16384);
+    const int span = (int)std::max<int64_t>(1, std::min<int64_t>(64, want));
+    const unsigned waves = (buckets + span - 1) / span;
+    hipLaunchKernelGGL(k_bucket_sort_small, dim3((waves + ST / 64 - 1) / (ST / 64), trials), dim3(ST), 0, s, bl, pairs,
+                       span, q.out_cap, out);
+  } else {
+    hipLaunchKernelGGL(k_bucket_sort, dim3(buckets), dim3(ST), 0, s, bl, pairs, q.out_cap, out, early, q.early_cap,
+                       q.counts_out, q.shares_out);
   }
-  hipLaunchKernelGGL(k_bucket_sort, dim3(buckets, trials), dim3(ST), 0, s, bl, pairs, above, q.out_cap, out, early,
-                     q.early_cap, q.counts_out, q.shares_out);
   return hipGetLastError();
 }
 
-bool bucket_shares_possible(int32_t plane_records) { return plane_records > kBucketLds; }
+bool batch_shares_possible(int32_t plane_records) { return plane_records > kBucketSmall; }
 
 hipError_t launch_bucket_shares(const BucketSort& q, hipStream_t s) {
   BucketList bl;
   if (!bucket_list(q, bl)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_bucket_shares, dim3(q.trials > 1 ? 96 : 512, (unsigned)q.trials), dim3(SHARE_T), 0, s, bl,
+  hipLaunchKernelGGL(k_bucket_shares, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(q.tab ? 96 : 512, q.most / kBucketSmall)), (unsigned)q.trials), dim3(SHARE_T), 0, s, bl,
                      reinterpret_cast<const int2*>(q.scratch), q.bits_r, q.out_cap, reinterpret_cast<int4*>(q.out),
                      reinterpret_cast<int4*>(q.early), q.early_cap);
   return hipGetLastError();
