@@ -44,8 +44,8 @@ constexpr int XT = 4 * HS_THREADS;
 constexpr int kRowsPerPass = 96;
 constexpr int kSplitBins = 786432;
 constexpr int kMaxSegs = 8;
-// entries past ceil(n / 4): the last tile's or block's threads hold fewer than four columns each
-constexpr int kHitSlack = kMaxSegs * 1024;
+// entries past those of ceil(n / 4) threads: the last tile's and block's hold fewer than four columns each
+constexpr int kHitSlack = kMaxSegs * (kStrideHigh + HS_THREADS);
 
 // Columns of a thread's group: c0 + STRIDE a, a = 0..3.
 constexpr int kStrideFund = HS_THREADS;  // a wave's load covers 64 columns at stride m
@@ -760,7 +760,8 @@ __device__ __forceinline__ void hs_flush_entries(const int4* __restrict__ s_ent,
 // rows one memory latency after another (8 rows ahead), so a spectrum too short
 // to fill the chip takes the time of 85 rows whatever its length: up to 2^18
 // bins (1024 waves) the rows go to four workgroups.  Measured phase 1: 16,384
-// bins 18.8 -> 8.0 us, 200,003 bins 20.4 -> 18.8 us.
+// bins 18.8 -> 8.0 us, 200,003 bins 20.4 -> 18.8 us; both phases at 2^18 bins 28.7 ->
+// 27.9 us.
 constexpr int kSegRows = 4;
 constexpr int kSegMaxN = 1 << 18;
 template <int Z, int NH, int TH = HS_THREADS, int SEGS = 1>
@@ -1262,7 +1263,10 @@ hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_
 }
 
 int64_t harmsum_hit_entries(int64_t n_max) {
-  return std::max<int64_t>((n_max + 3) / 4, kSplitBins / 4) + kHitSlack;
+  // segments x groups of the longest spectrum, and of the one with the most of either split
+  const int64_t maps = std::min<int64_t>(kMaxSegs * ((n_max + 3) / 4), kSplitBins / 4);
+  const int64_t rows85 = kSegRows * ((std::min<int64_t>(n_max, kSegMaxN) + 3) / 4);
+  return std::max({(n_max + 3) / 4, maps, rows85}) + kHitSlack;
 }
 
 hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, int n_harm, const float* ta,
