@@ -42,7 +42,7 @@ void free_plan(fdas_plan* p) {
   if (p->d_Bpk) (void)hipFree(p->d_Bpk);
   if (p->d_Bsp) (void)hipFree(p->d_Bsp);
   if (p->d_tscale) (void)hipFree(p->d_tscale);
-  if (p->d_dtiles) (void)hipFree(p->d_dtiles);
+  if (p->d_dsteps) (void)hipFree(p->d_dsteps);
   if (p->d_drows) (void)hipFree(p->d_drows);
   if (p->d_dedge) (void)hipFree(p->d_dedge);
   if (p->d_dedge_tap) (void)hipFree(p->d_dedge_tap);
@@ -346,7 +346,7 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
     if ((split ? (e = upload(&p->d_Bsp, pk.Bsp.data(), pk.Bsp.size() * sizeof(uint16_t))) != hipSuccess ||
                      (e = upload(&p->d_tscale, pk.tscale.data(), pk.tscale.size() * sizeof(float))) != hipSuccess
                : (e = upload(&p->d_Bpk, pk.Bpk.data(), pk.Bpk.size() * sizeof(float))) != hipSuccess) ||
-        (e = upload(&p->d_dtiles, pk.tiles.data(), pk.tiles.size() * sizeof(int))) != hipSuccess ||
+        (e = upload(&p->d_dsteps, pk.steps.data(), pk.steps.size() * sizeof(int))) != hipSuccess ||
         (e = upload(&p->d_drows, pk.rows.data(), pk.rows.size() * sizeof(int))) != hipSuccess ||
         (e = upload(&p->d_dedge, pk.edge.data(), pk.edge.size() * sizeof(int))) != hipSuccess ||
         (e = upload(&p->d_dedge_tap, pk.edge_tap.data(), pk.edge_tap.size() * sizeof(float))) != hipSuccess) {
@@ -411,7 +411,7 @@ fdas_status fdas_convolve(fdas_plan* p, const void* d_spectrum, int64_t n, float
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   hipError_t e;
   if (p->direct) {
-    const fdas::DirectTables t{p->d_Bpk,   p->d_Bsp,       p->d_tscale,       p->d_dtiles,           p->d_drows,
+    const fdas::DirectTables t{p->d_Bpk,   p->d_Bsp,       p->d_tscale,       p->d_dsteps,           p->d_drows,
                                p->d_dedge, p->d_dedge_tap, p->dgroups.data(), (int)p->dgroups.size(), p->dP_max};
     if (p->desc.precision == FDAS_PREC_FP32)
       e = fdas::launch_direct_conv(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t, p->cus,

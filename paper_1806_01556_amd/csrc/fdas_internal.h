@@ -39,7 +39,7 @@ struct DirectPack {
   std::vector<float> Bpk;
   std::vector<uint16_t> Bsp;
   std::vector<float> tscale;    // [tiles] 2^-eh (split)
-  std::vector<int> tiles;       // [tiles][4] {steps, 0, 0, 0}
+  std::vector<int> steps;       // [tiles], falling
   std::vector<int> rows;        // [tiles][16] FOP row of a column (even: +z, odd: -z, -1: none)
   std::vector<int> edge;        // [tiles][8] L/2 of a slot
   std::vector<float> edge_tap;  // [tiles][16] the unpaired tap at d = -L/2 of a column (x 2^eh)
@@ -117,7 +117,7 @@ struct DirectTables {
   const float* Bpk;
   const uint4* Bsp;
   const float* tscale;
-  const int4* tiles;
+  const int* steps;
   const int* rows;
   const int* edge;
   const float* edge_tap;

@@ -173,17 +173,16 @@ namespace {
 
 // Tile table of the direct correlations: slots of |z| = z_max .. 0 in tiles of
 // 8, `per_step` distances to a step; groups of consecutive tiles, the fewest
-// equal ones of at most 6 tiles and 64 KiB (`entry_bytes` per entry, `extra`
-// entries per tile beside its steps).
-void tile_table(int z_max, int per_step, int extra, int entry_bytes, DirectPack& pk) {
+// equal ones of at most 6 tiles and 64 KiB (`entry_bytes` per entry).
+void tile_table(int z_max, int per_step, int entry_bytes, DirectPack& pk) {
   const int T = (z_max + 8) / 8;
-  pk.tiles.assign((size_t)T * 4, 0);
+  pk.steps.assign(T, 0);
   pk.rows.assign((size_t)T * 16, -1);
   pk.edge.assign((size_t)T * 8, 0);
   pk.P_max = tap_count(z_max) / 2;
   for (int g = 0; g < T; ++g) {
     // distances 0 .. P - 1 of the widest member
-    pk.tiles[4 * g] = (tap_count(z_max - 8 * g) / 2 + per_step - 1) / per_step;
+    pk.steps[g] = (tap_count(z_max - 8 * g) / 2 + per_step - 1) / per_step;
     for (int t = 0; t < 8 && z_max - 8 * g - t >= 0; ++t) {
       const int az = z_max - 8 * g - t;
       pk.rows[16 * g + 2 * t] = z_max + az;
@@ -196,7 +195,7 @@ void tile_table(int z_max, int per_step, int extra, int entry_bytes, DirectPack&
     int most = 0;
     for (int q = 0, offset = 0; q < ng; ++q) {
       DirectGroup gr{q * T / ng, (q + 1) * T / ng - q * T / ng, offset, 0};
-      for (int g = gr.first; g < gr.first + gr.tiles; ++g) gr.count += pk.tiles[4 * g] + extra;
+      for (int g = gr.first; g < gr.first + gr.tiles; ++g) gr.count += pk.steps[g];
       offset += gr.count;
       most = std::max(most, gr.count);
       pk.groups.push_back(gr);
@@ -221,14 +220,14 @@ double slot_tap(const std::vector<std::vector<cd>>& bank, int z_max, int g, int 
 }  // namespace
 
 void direct_pack(const std::vector<std::vector<cd>>& bank, int z_max, DirectPack& pk) {
-  tile_table(z_max, 4, 0, 256, pk);
+  tile_table(z_max, 4, 256, pk);
   auto entry = [&](int g, int step) {
     for (int lane = 0; lane < 64; ++lane)
       pk.Bpk.push_back((float)slot_tap(bank, z_max, g, lane & 15, 4 * step + (lane >> 4)));
   };
   for (const DirectGroup& gr : pk.groups)
-    for (int p = 0; p < pk.tiles[4 * gr.first]; ++p)
-      for (int g = gr.first; g < gr.first + gr.tiles && pk.tiles[4 * g] > p; ++g) entry(g, p);
+    for (int p = 0; p < pk.steps[gr.first]; ++p)
+      for (int g = gr.first; g < gr.first + gr.tiles && pk.steps[g] > p; ++g) entry(g, p);
   for (int c = 0; c < (int)pk.rows.size(); ++c)
     pk.edge_tap.push_back((float)slot_tap(bank, z_max, c / 16, c % 16, -1));
 }
@@ -249,13 +248,13 @@ float from_bf16_bits(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b 
 }  // namespace
 
 void direct_pack_split(const std::vector<std::vector<cd>>& bank, int z_max, bool bf16, DirectPack& pk) {
-  tile_table(z_max, 32, 0, 2048, pk);
-  const int T = (int)pk.tiles.size() / 4;
+  tile_table(z_max, 32, 2048, pk);
+  const int T = (int)pk.steps.size();
   std::vector<int> eh(T, 0);
   for (int g = 0; g < T; ++g) {
     float mx = 0.0f;
     for (int col = 0; col < 16; ++col)
-      for (int d = -1; d < 32 * pk.tiles[4 * g]; ++d) mx = std::max(mx, std::fabs((float)slot_tap(bank, z_max, g, col, d)));
+      for (int d = -1; d < 32 * pk.steps[g]; ++d) mx = std::max(mx, std::fabs((float)slot_tap(bank, z_max, g, col, d)));
     eh[g] = mx > 0.0f ? 14 - std::ilogb(mx) : 0;
     pk.tscale.push_back(std::ldexp(1.0f, -eh[g]));
   }
@@ -272,8 +271,8 @@ void direct_pack_split(const std::vector<std::vector<cd>>& bank, int z_max, bool
     pk.Bsp.insert(pk.Bsp.end(), lo, lo + 64 * 8);
   };
   for (const DirectGroup& gr : pk.groups)
-    for (int p = 0; p < pk.tiles[4 * gr.first]; ++p)
-      for (int g = gr.first; g < gr.first + gr.tiles && pk.tiles[4 * g] > p; ++g) entry(g, p);
+    for (int p = 0; p < pk.steps[gr.first]; ++p)
+      for (int g = gr.first; g < gr.first + gr.tiles && pk.steps[g] > p; ++g) entry(g, p);
   for (int c = 0; c < (int)pk.rows.size(); ++c)
     pk.edge_tap.push_back(std::ldexp((float)slot_tap(bank, z_max, c / 16, c % 16, -1), eh[c / 16]));
 }

@@ -20,7 +20,7 @@ struct fdas_plan {
   float* d_Bpk = nullptr;       // direct, FP32: packed template operand
   uint4* d_Bsp = nullptr;       // direct, split precisions: hi/lo 16-bit operand
   float* d_tscale = nullptr;    // direct, split precisions: per-tile 2^-eh
-  int4* d_dtiles = nullptr;     // direct: tile table
+  int* d_dsteps = nullptr;      // direct: steps of the tiles
   int* d_drows = nullptr;       // direct: FOP rows of the tiles' columns
   int* d_dedge = nullptr;       // direct: L/2 of every slot
   float* d_dedge_tap = nullptr; // direct: unpaired tap of every column

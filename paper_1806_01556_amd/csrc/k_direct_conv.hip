@@ -16,11 +16,11 @@
 //   - with h_z = a + ib, the real-filter correlations A = X * a and B = X * b
 //     serve both signs: Y_z = A + iB, Y_-z = A - iB;
 //   - each filter runs over distances d >= 0 with X[j + d] + X[j - d] as
-//     the operand (FP32 kernel), d = 0 with half the tap, and the unpaired tap
-//     in a step of its own.
+//     the operand, d = 0 with half the tap; the unpaired tap is added on the
+//     vector units at the end.
 //
 // MFMA mapping of the FP32 kernel (v_mfma_f32_16x16x4f32, one 16 x 16 FP32
-// output block, K = 4 distances):
+// output block, K = 4 distances; the split kernel below has K = 32):
 //   rows    = 16 consecutive output bins;
 //   columns = 8 |z| x {Re h, Im h};
 //   one instruction for Re X and one for Im X, in accumulators of their own.
@@ -31,8 +31,8 @@
 // only runs over its widest member's support, so short templates do not pay
 // for the 394-tap ones.
 //
-// Work split: a workgroup = 4 waves covers 256 consecutive bins (FP32), a wave 4
-// sub-tiles of 16 bins.
+// Work split: a workgroup = 4 waves covers 256 consecutive bins (FP32; split 128), a
+// wave 4 sub-tiles of 16 bins (split 2).
 
 #include <algorithm>
 
@@ -40,15 +40,6 @@
 
 namespace fdas {
 namespace {
-
-// Two adjacent FOP values stored non-temporally: the plane is written once and
-// read back only after the whole convolution, so it should not stay in the
-// caches (the same policy as the overlap-save kernel's stores).
-__device__ __forceinline__ void store2_nt(float* dst, float a, float b) {
-  typedef float f2v __attribute__((ext_vector_type(2)));
-  const f2v v = {a, b};
-  __builtin_nontemporal_store(v, reinterpret_cast<f2v*>(dst));
-}
 
 constexpr int DW = 4;                 // waves per workgroup
 constexpr int SUB = 4;                // 16-bin sub-tiles per wave
@@ -194,19 +185,18 @@ __device__ __forceinline__ void repair_cells(const float2* __restrict__ x, int64
 // Operand entry of step p of tile t in a group (entries are step-major, and a step
 // holds the tiles that still run).
 template <int TG>
-__device__ __forceinline__ int group_entry(const int4* __restrict__ tiles, int t, int p) {
+__device__ __forceinline__ int group_entry(const int* __restrict__ steps, int t, int p) {
   int e = t;
 #pragma unroll
-  for (int q = 0; q < TG; ++q) e += min(tiles[q].x, p);
+  for (int q = 0; q < TG; ++q) e += min(steps[q], p);
   return e;
 }
 
-// A group of TG tiles at once: tiles[t] = {folded steps, 0, 0, 0} (steps fall
-// with t), rows[t * 16 + col] = FOP row of column col (-1: none),
+// A group of TG tiles at once: steps[t] of tile t's folded steps (falling with
+// t), rows[t * 16 + col] = FOP row of column col (-1: none),
 // edge[t * 8 + slot] = L/2 of the slot's template, edge_tap[t * 16 + col] its
-// unpaired tap.  The operand holds 64
-// floats per (step, tile) in lane order: step p (lane group kk: distance
-// d = 4 p + kk) of every tile with more than p steps.  Dynamic LDS: the operand
+// unpaired tap.  The operand holds 64 floats per (step, tile) in lane order: step p
+// (lane group kk: distance d = 4 p + kk) of every tile with more than p steps.  Dynamic LDS: the operand
 // (`count` entries, and as much again as one step holds, read ahead) and two
 // strips of X (Pm + 8 bins on either side of the workgroup's bins).  The
 // unpaired taps are added on the vector units (8 multiply-adds per tile and
@@ -234,9 +224,9 @@ struct FoldState {
 };
 
 template <int TG, int T>
-__device__ __forceinline__ void fold_steps(FoldState<TG>& st, const int4* __restrict__ tiles, int p) {
+__device__ __forceinline__ void fold_steps(FoldState<TG>& st, const int* __restrict__ steps, int p) {
   // tiles 0 .. T-1 still run: to the end of tile T-1
-  const int end = tiles[T - 1].x;
+  const int end = steps[T - 1];
   for (; p < end; ++p) {
     float fr[SUB], fi[SUB], bv[T];
 #pragma unroll
@@ -266,13 +256,13 @@ __device__ __forceinline__ void fold_steps(FoldState<TG>& st, const int4* __rest
         st.ai[t][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(fi[s], bv[t], st.ai[t][s], 0, 0, 0);
       }
   }
-  if constexpr (T > 1) fold_steps<TG, T - 1>(st, tiles, p);
+  if constexpr (T > 1) fold_steps<TG, T - 1>(st, steps, p);
 }
 
 template <int TG>
 __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const float4* __restrict__ Bpk,
-    const int4* __restrict__ tiles, const int* __restrict__ rows, const int* __restrict__ edge,
+    const int* __restrict__ steps, const int* __restrict__ rows, const int* __restrict__ edge,
     const float* __restrict__ edge_tap, int count, int Pm, int blocks) {
   extern __shared__ float4 lds4[];
   __shared__ ColumnInfo cols[16 * TG];
@@ -322,7 +312,7 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     }
 #pragma unroll
     for (int t = 0; t < TG; ++t) st.b[t] = st.bp[64 * t];
-    fold_steps<TG, TG>(st, tiles, 0);
+    fold_steps<TG, TG>(st, steps, 0);
     const int64_t left = n - (jb + 4 * kk);  // bins from this lane's first to the end
     const bool whole = jb + WAVE_BINS <= n;  // uniform
     const float2* __restrict__ here = cur + w * WAVE_BINS + 4 * kk + halo;  // this lane's first output bin
@@ -342,7 +332,7 @@ __global__ __launch_bounds__(DW * 64, 2) void k_direct_conv(
     }
     if (__builtin_amdgcn_readfirstlane(s_bad[(blk - blk0) & 1]) == blk + 1)
       repair_cells<BLK_BINS, TG>(x, n, fop, ld, (int64_t)blk * BLK_BINS, Pm, cols, [&](int t, int col, int d) {
-        return bs[64 * group_entry<TG>(tiles, t, d / 4) + 16 * (d & 3) + col];
+        return bs[64 * group_entry<TG>(steps, t, d / 4) + 16 * (d & 3) + col];
       });
   }
 }
@@ -521,7 +511,7 @@ __device__ __forceinline__ void split_step(v4f (&ar)[TG][SSUB], v4f (&ai)[TG][SS
 template <typename T, int TG>
 __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const uint4* __restrict__ Bsp,
-    const int4* __restrict__ tiles, const float* __restrict__ tscale, const int* __restrict__ rows,
+    const int* __restrict__ steps, const float* __restrict__ tscale, const int* __restrict__ rows,
     const int* __restrict__ edge, const float* __restrict__ edge_tap, int count, int halo, int Pm, int blocks) {
   extern __shared__ uint4 lds_u4[];
   __shared__ ColumnInfo cols[16 * TG];
@@ -536,9 +526,9 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
   const int m = lane & 15;
   const int kg = lane >> 4;
   const int w0 = 64 * (w >> 1) + 16 * (w & 1);  // first bin of this wave's sub-tile 0
-  int steps[TG];
+  int run[TG];
 #pragma unroll
-  for (int t = 0; t < TG; ++t) steps[t] = tiles[t].x;
+  for (int t = 0; t < TG; ++t) run[t] = steps[t];
   const int blk0 = (int)((int64_t)blocks * blockIdx.x / gridDim.x);
   const int blk1 = (int)((int64_t)blocks * (blockIdx.x + 1) / gridDim.x);
   float2 nx[SPER];  // the next block's strip, loaded while this one is worked on
@@ -608,12 +598,12 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     strip_down(dn + 32, d[1]);
     up += 64;
     dn -= 32;
-    for (int q = 0; q < steps[0]; q += 2) {
+    for (int q = 0; q < run[0]; q += 2) {
       int active = 0, next = 0;
 #pragma unroll
       for (int t = 0; t < TG; ++t) {
-        active += q < steps[t] ? 1 : 0;
-        next += q + 1 < steps[t] ? 1 : 0;
+        active += q < run[t] ? 1 : 0;
+        next += q + 1 < run[t] ? 1 : 0;
       }
       split_step<T, TG, 0>(ar, ai, u, d, up, dn, b, active);
       b += 128 * active;
@@ -647,7 +637,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     if (bad < 0)
       repair_cells<SBLK_BINS, TG>(x, n, fop, ld, j0, Pm, cols, [&](int t, int col, int d) {
         // lane 16 ((d / 8) % 4) + col, value d % 8: hi, and lo 64 lanes on
-        const T* e = reinterpret_cast<const T*>(lds_u4 + 128 * group_entry<TG>(tiles, t, d / 32));
+        const T* e = reinterpret_cast<const T*>(lds_u4 + 128 * group_entry<TG>(steps, t, d / 32));
         const int at = (16 * ((d >> 3) & 3) + col) * 8 + (d & 7);
         return (float)e[at] + (float)e[at + 512];
       });
@@ -666,7 +656,7 @@ hipError_t launch_split_group(const float2* x, int64_t n, float* fop, int64_t ld
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_direct_conv_split<T, TG>), dim3(grid), dim3(256), lds, s, x, n, fop, ld,
-                     t.Bsp + (size_t)128 * gr.offset, t.tiles + gr.first, t.tscale + gr.first, t.rows + 16 * gr.first,
+                     t.Bsp + (size_t)128 * gr.offset, t.steps + gr.first, t.tscale + gr.first, t.rows + 16 * gr.first,
                      t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, halo, t.P_max, blocks);
   return hipGetLastError();
 }
@@ -721,7 +711,7 @@ hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld
       if (e != hipSuccess) return e;                                                                                \
     }                                                                                                               \
     hipLaunchKernelGGL(k_direct_conv<TG>, dim3(grid), dim3(DW * 64), lds, s, x, n, fop, ld,                         \
-                       reinterpret_cast<const float4*>(t.Bpk) + (size_t)16 * gr.offset, t.tiles + gr.first,         \
+                       reinterpret_cast<const float4*>(t.Bpk) + (size_t)16 * gr.offset, t.steps + gr.first,         \
                        t.rows + 16 * gr.first, t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, t.P_max, \
                        (int)blocks);                                                                                \
     break;                                                                                                          \
