@@ -125,6 +125,12 @@ void fdas_plan_desc_default(fdas_plan_desc* desc);
  *   d in [-L/2, L/2 - 1],  L(z) = 2*(8 + ceil(4.5*|z|))  (<= 400 taps, Section 1),
  * their overlap-save spectra, the default thresholds TA(k, i) = Q^{-1}(k, p_fa)
  * (inverse regularised upper incomplete gamma), and uploads them.
+ * Device memory held: the template tables (2.8 MB at z_max 42), 32 bytes per record
+ * of the n_harm * cand_capacity that a readback orders, and 16 bytes per entry of
+ * the harmonic sum's hit list: 8768 and the largest of n_max / 4, min(2 n_max, 196608)
+ * and min(n_max, 2^18) entries (0.7 MB for 2^14 bins, 17 MB for 2^22); batch calls add
+ * theirs on first use.  Page-locked host memory: 128 KB, and 16 * n_harm * cand_capacity
+ * bytes from the first fdas_candidates_mapped on.
  * Returns FDAS_ERR_NO_DEVICE when no GPU is present; *out is NULL on error. */
 fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out);
 
@@ -272,7 +278,8 @@ fdas_status fdas_candidates_mapped(fdas_plan* plan, const fdas_cand* d_cands, co
 typedef struct fdas_prescreen fdas_prescreen;
 
 int32_t fdas_prescreen_param_count(void);
-/* Workspace for batches of up to max_batch blocks on `device`; parameters start at 0. */
+/* Workspace for batches of up to max_batch blocks on `device` (0.39 MB each, and 23 MB
+ * of partial weight gradients); parameters start at 0. */
 fdas_status fdas_prescreen_create(int32_t device, int32_t max_batch, fdas_prescreen** out);
 fdas_status fdas_prescreen_destroy(fdas_prescreen* ps);             /* NULL is a no-op */
 /* FP32 parameters from / to host memory (set also clears the Adam state).  Synchronise. */
