@@ -61,6 +61,18 @@ __device__ __forceinline__ void row_segment(int rbase, int rend, int& r0, int& r
   r1 = rbase + (int)((int64_t)len * (blockIdx.y + 1) / gridDim.y);
 }
 
+// First of the rows (of `len`, in `segs` segments) that an entry's segment holds.
+// An entry's bits lie within one segment, so the lowest one tells which.
+// With low its row + 1 the segment is (low * segs - 1) / len; a quotient of whole
+// numbers below 1000 whose dividend is moved by half is no whole number, so the
+// reciprocals (1 / len, 1 / segs) give its whole part exactly.
+__device__ __forceinline__ int entry_first_row(const int4& ent, int len, int segs, float per_row, float per_seg) {
+  if (segs == 1) return 0;  // uniform
+  const int low = ent.y ? __ffs(ent.y) : ent.z ? 32 + __ffs(ent.z) : 64 + __ffs(ent.w);
+  const int seg = (int)(((float)(low * segs) - 0.5f) * per_row);
+  return (int)(((float)(seg * len) + 0.5f) * per_seg);
+}
+
 struct RowMask {
   unsigned w[3] = {0u, 0u, 0u};
   // bit is uniform: the branches are scalar
@@ -974,29 +986,51 @@ __device__ __forceinline__ void hs_emit_wave(const float* __restrict__ fop, int6
   hs_append_wave<NH, 1>(hk, n, 2 * Z + 1, j0, i, r, act, ta, cands, cap, counts, lane);
 }
 
-// Phase 2 of the kernels for any row count and of the other index maps: work
-// item w = entry * 96 + row bit of the pass that starts at row rbase.
+// Phase 2 of the kernels for any row count and of the other index maps.  Work item
+// w = entry * 96 + row of the pass while the grid has a thread for every one of
+// them (the row is then known before the entry is read: 0.4 us); for longer lists
+// entry * W + row within the entry's segment, W rows to the longest segment.  With
+// 96 items to an entry whatever its segment, planes with most rows above threshold
+// took up to 3.1 x the time in eight segments.
 template <int MAP, int NH>
 __global__ __launch_bounds__(HS_THREADS) void k_emit_map(const float* __restrict__ fop, int64_t ld, int n, int z_max,
-                                                         int rbase, const int4* __restrict__ hitrows, int hit_cap,
+                                                         int rbase, int rend, int segs, float per_row, float per_seg,
+                                                         const int4* __restrict__ hitrows, int hit_cap,
                                                          const int32_t* __restrict__ hit_count,
                                                          const float* __restrict__ ta, fdas_cand* __restrict__ cands,
                                                          int cap, int32_t* __restrict__ counts) {
   constexpr int STRIDE =
       MAP == FDAS_HSUM_HIGHEST ? kStrideHigh : MAP == FDAS_HSUM_FUNDAMENTAL ? kStrideFund : 1;
-  const int64_t items = (int64_t)min(*hit_count, hit_cap) * kRowsPerPass;
+  const int len = rend - rbase;
+  const int64_t entries = min(*hit_count, hit_cap);
   const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)gridDim.x * HS_THREADS;
-  for (int64_t w0 = (int64_t)blockIdx.x * HS_THREADS + (threadIdx.x & ~63); w0 < items; w0 += stride) {
-    const int64_t w = w0 + lane;
-    bool act = w < items;
+  const unsigned stride = gridDim.x * HS_THREADS;  // at most 2^22
+  const unsigned start = blockIdx.x * HS_THREADS + (threadIdx.x & ~63);
+  const bool once = entries * kRowsPerPass <= stride;  // uniform
+  int W = kRowsPerPass, e = (int)((start + lane) / kRowsPerPass), o = (int)((start + lane) % kRowsPerPass);
+  int step_e = 0, step_o = 0;
+  if (!once) {
+    // item w0 + lane is row o of entry e: stepped on without a division
+    W = (len + segs - 1) / segs;
+    e = (int)((start + lane) / (unsigned)W);
+    o = (int)((start + lane) % (unsigned)W);
+    step_e = (int)(stride / (unsigned)W);
+    step_o = (int)(stride % (unsigned)W);
+  }
+  const int64_t items = entries * W;
+  for (int64_t w0 = start; w0 < items; w0 += stride, e += step_e, o += step_o) {
+    if (o >= W) {
+      o -= W;
+      ++e;
+    }
+    bool act = w0 + lane < items;
     int4 ent = make_int4(0, 0, 0, 0);
     int b = 0;
     if (act) {
-      ent = hitrows[w / kRowsPerPass];
-      b = (int)(w % kRowsPerPass);
+      ent = hitrows[e];
+      b = once ? o : entry_first_row(ent, len, segs, per_row, per_seg) + o;
       const unsigned word = (unsigned)(b < 32 ? ent.y : (b < 64 ? ent.z : ent.w));
-      act = ((word >> (b % 32)) & 1u) != 0;
+      act = b < len && ((word >> (b % 32)) & 1u) != 0;
     }
     if (__ballot(act) == 0ull) continue;  // uniform
     const int r = rbase + b, i = r - z_max;
@@ -1007,8 +1041,11 @@ __global__ __launch_bounds__(HS_THREADS) void k_emit_map(const float* __restrict
 }
 
 // Phase 2: work item w = entry * ROWS + row, grid-stride over all items in
-// wave-uniform steps so the whole wave reaches the compaction together.
-template <int Z, int NH>
+// wave-uniform steps so the whole wave reaches the compaction together; with four
+// segments and more items than threads entry * W + row within the entry's segment.
+// 2^18 bins with most rows above threshold took 3.77 ms with all rows to an entry, take
+// 1.07 this way and 1.04 in one segment.
+template <int Z, int NH, int SEGS = 1>
 __global__ __launch_bounds__(HS_THREADS) void k_harmsum_emit(const float* __restrict__ fop, int64_t ld, int n,
                                                              const int4* __restrict__ hitrows,
                                                              const int32_t* __restrict__ hitrow_count,
@@ -1016,19 +1053,27 @@ __global__ __launch_bounds__(HS_THREADS) void k_harmsum_emit(const float* __rest
                                                              fdas_cand* __restrict__ cands, int cap,
                                                              int32_t* __restrict__ counts) {
   constexpr int ROWS = 2 * Z + 1;
-  const int64_t items = (int64_t)(*hitrow_count) * ROWS;
+  const int64_t entries = *hitrow_count;
   const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * HS_THREADS;
+  const bool once = SEGS == 1 || entries * ROWS <= stride;  // uniform
+  constexpr int WS = (ROWS + SEGS - 1) / SEGS;
+  const int64_t items = entries * (once ? ROWS : WS);
   for (int64_t w0 = (int64_t)blockIdx.x * HS_THREADS + (threadIdx.x & ~63); w0 < items; w0 += stride) {
     const int64_t w = w0 + lane;
     bool act = w < items;
     int4 ent = make_int4(0, 0, 0, 0);
     int r = 0;
     if (act) {
-      ent = hitrows[w / ROWS];
-      r = (int)(w % ROWS);
+      if (once) {
+        ent = hitrows[w / ROWS];
+        r = (int)(w % ROWS);
+      } else {
+        ent = hitrows[w / WS];
+        r = (int)(w % WS) + entry_first_row(ent, ROWS, SEGS, 1.0f / ROWS, 1.0f / SEGS);
+      }
       const unsigned word = (unsigned)(r < 32 ? ent.y : (r < 64 ? ent.z : ent.w));
-      act = ((word >> (r % 32)) & 1u) != 0;
+      act = (SEGS == 1 || r < ROWS) && ((word >> (r % 32)) & 1u) != 0;
     }
     if (__ballot(act) == 0ull) continue;  // uniform
     hs_emit_wave<Z, NH>(fop, ld, n, ent.x, r, act, ta, cands, cap, counts, lane);
@@ -1257,8 +1302,8 @@ hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_
   const size_t reserve = MAP == FDAS_HSUM_HIGHEST ? 50000 : MAP == FDAS_HSUM_FUNDAMENTAL ? 36000 : 0;
   hipLaunchKernelGGL(detect, dim3(blocks, segs), dim3(HS_THREADS), reserve, s, fop, ld, n, z_max, rbase, rend, order, ta,
                      wk.hitrows, wk.hit_cap, wk.hitrow_count);
-  hipLaunchKernelGGL((k_emit_map<MAP, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, n, z_max, rbase,
-                     wk.hitrows, wk.hit_cap, wk.hitrow_count, ta, cands, cap, counts);
+  hipLaunchKernelGGL((k_emit_map<MAP, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, n, z_max, rbase, rend,
+                     (int)segs, 1.0f / (rend - rbase), 1.0f / segs, wk.hitrows, wk.hit_cap, wk.hitrow_count, ta, cands, cap, counts);
   return hipGetLastError();
 }
 
@@ -1286,14 +1331,17 @@ hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, in
     switch (n_harm) {
 #define FDAS_HSZ_CASE(NH)                                                                                          \
   case NH:                                                                                                         \
-    if (segs)                                                                                                      \
+    if (segs) {                                                                                                    \
       hipLaunchKernelGGL((k_harmsum_z<42, NH, HS_THREADS, kSegRows>), dim3(blocks, kSegRows), dim3(HS_THREADS), 0, \
                          s, fop, ld, nn, wk.tile_of_block, ta, wk.hitrows, wk.hitrow_count);                       \
-    else                                                                                                           \
+      hipLaunchKernelGGL((k_harmsum_emit<42, NH, kSegRows>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, nn,   \
+                         wk.hitrows, wk.hitrow_count, ta, cands, cap, counts);                                     \
+    } else {                                                                                                       \
       hipLaunchKernelGGL((k_harmsum_z<42, NH>), dim3(blocks), dim3(HS_THREADS), 0, s, fop, ld, nn,                 \
                          wk.tile_of_block, ta, wk.hitrows, wk.hitrow_count);                                       \
-    hipLaunchKernelGGL((k_harmsum_emit<42, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, nn, wk.hitrows,   \
-                       wk.hitrow_count, ta, cands, cap, counts);                                                   \
+      hipLaunchKernelGGL((k_harmsum_emit<42, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, nn, wk.hitrows, \
+                         wk.hitrow_count, ta, cands, cap, counts);                                                 \
+    }                                                                                                              \
     break;
       FDAS_HSZ_CASE(1)
       FDAS_HSZ_CASE(2)
