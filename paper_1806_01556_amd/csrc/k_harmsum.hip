@@ -61,18 +61,6 @@ __device__ __forceinline__ void row_segment(int rbase, int rend, int& r0, int& r
   r1 = rbase + (int)((int64_t)len * (blockIdx.y + 1) / gridDim.y);
 }
 
-// First of the rows (of `len`, in `segs` segments) that an entry's segment holds.
-// An entry's bits lie within one segment, so the lowest one tells which.
-// With low its row + 1 the segment is (low * segs - 1) / len; a quotient of whole
-// numbers below 1000 whose dividend is moved by half is no whole number, so the
-// reciprocals (1 / len, 1 / segs) give its whole part exactly.
-__device__ __forceinline__ int entry_first_row(const int4& ent, int len, int segs, float per_row, float per_seg) {
-  if (segs == 1) return 0;  // uniform
-  const int low = ent.y ? __ffs(ent.y) : ent.z ? 32 + __ffs(ent.z) : 64 + __ffs(ent.w);
-  const int seg = (int)(((float)(low * segs) - 0.5f) * per_row);
-  return (int)(((float)(seg * len) + 0.5f) * per_seg);
-}
-
 struct RowMask {
   unsigned w[3] = {0u, 0u, 0u};
   // bit is uniform: the branches are scalar
@@ -986,65 +974,115 @@ __device__ __forceinline__ void hs_emit_wave(const float* __restrict__ fop, int6
   hs_append_wave<NH, 1>(hk, n, 2 * Z + 1, j0, i, r, act, ta, cands, cap, counts, lane);
 }
 
-// Phase 2 of the kernels for any row count and of the other index maps.  Work item
-// w = entry * 96 + row of the pass while the grid has a thread for every one of
-// them (the row is then known before the entry is read: 0.4 us); for longer lists
-// entry * W + row within the entry's segment, W rows to the longest segment.  With
-// 96 items to an entry whatever its segment, planes with most rows above threshold
-// took up to 3.1 x the time in eight segments.
+// Position of the k-th (from 0) of the set bits of the 96-bit mask {y, z, w}, which
+// has more than k.
+__device__ __forceinline__ int set_bit(int k, int y, int z, int w) {
+  const int c0 = __popc(y), c1 = __popc(z);
+  int pos = 0;
+  unsigned word = (unsigned)y;
+  if (k >= c0) {
+    k -= c0;
+    pos = 32;
+    word = (unsigned)z;
+    if (k >= c1) {
+      k -= c1;
+      pos = 64;
+      word = (unsigned)w;
+    }
+  }
+#pragma unroll
+  for (int s = 16; s > 0; s >>= 1) {
+    const int c = __popc(word & ((1u << s) - 1u));
+    if (k >= c) {
+      k -= c;
+      pos += s;
+      word >>= s;
+    }
+  }
+  return pos;
+}
+
+// The noted rows of a hit-row list (ROWS to an entry) dealt to the lanes of the
+// grid's waves: work(c0, bit, act) of every set bit, a whole wave at a time (act:
+// this lane has one).  While the grid has a thread for every row of every entry,
+// item = entry * ROWS + row: the row is known before the entry is read and nothing
+// is passed between lanes, 0.5-1.3 us less for the usual short list.  For longer ones
+// a wave takes up to 32 entries at once and its lanes their set bits: as many rounds
+// as 64 rows of hits, where a lane for every row, set or not, spent most of a round on
+// rows without (and in segments on rows of other segments).
+constexpr int kDealEntries = 32;
+template <int ROWS, typename Work>
+__device__ __forceinline__ void deal_rows(const int4* __restrict__ hitrows, int entries, Work work) {
+  const int lane = threadIdx.x & 63;
+  const int wave = blockIdx.x * (HS_THREADS / 64) + (threadIdx.x >> 6), waves = gridDim.x * (HS_THREADS / 64);
+  const bool once = (int64_t)entries * ROWS <= (int64_t)waves * 64;  // uniform
+  const int G = once ? 1 : min(kDealEntries, (entries + waves - 1) / waves);
+  const int w = wave * 64 + lane, row = w % ROWS;  // of a short list
+  // one call of work, as its code is long
+  for (int64_t e0 = once ? wave * 64 / ROWS : (int64_t)wave * G; e0 < entries; e0 += (int64_t)waves * G) {
+    int4 ent = make_int4(0, 0, 0, 0);
+    const int64_t e = once ? w / ROWS : e0 + lane;
+    if (e < entries && (once || lane < G)) ent = hitrows[e];
+    const int cnt = __popc(ent.y) + __popc(ent.z) + __popc(ent.w);
+    int upto = cnt;  // bits of the entries up to this lane's, of lanes under kDealEntries
+    int bits = 64;
+    if (!once) {
+#pragma unroll
+      for (int o = 1; o < kDealEntries; o <<= 1) {
+        const int u = __shfl_up(upto, o);
+        if (lane >= o) upto += u;
+      }
+      bits = __builtin_amdgcn_readlane(upto, kDealEntries - 1);
+    }
+    for (int t0 = 0; t0 < bits; t0 += 64) {
+      int c0 = ent.x, bit = row;
+      bool act;
+      if (once) {
+        const unsigned word = (unsigned)(row < 32 ? ent.y : (row < 64 ? ent.z : ent.w));
+        act = ((word >> (row % 32)) & 1u) != 0;
+        if (__ballot(act) == 0ull) return;  // uniform
+      } else {
+        const int t = t0 + lane;
+        int src = 0;  // the entry that holds bit t
+#pragma unroll
+        for (int o = kDealEntries / 2; o > 0; o >>= 1) src += t >= __shfl(upto, src + o - 1) ? o : 0;
+        const int first = __shfl(upto - cnt, src);
+        bit = set_bit(t - first, __shfl(ent.y, src), __shfl(ent.z, src), __shfl(ent.w, src));
+        c0 = __shfl(ent.x, src);
+        act = t < bits;
+      }
+      work(c0, bit, act);
+    }
+    if (once) return;
+  }
+}
+
+// Phase 2 of the kernels for any row count and of the other index maps.  Measured,
+// both phases, 2^22 bins and 85 rows at a false-alarm probability of 1e-4 (some
+// 36,000 candidates to a plane): fundamental map 1162 -> 675 us, highest 4556 -> 2122, of
+// which phase 1 takes 627 and 1842.
 template <int MAP, int NH>
 __global__ __launch_bounds__(HS_THREADS) void k_emit_map(const float* __restrict__ fop, int64_t ld, int n, int z_max,
-                                                         int rbase, int rend, int segs, float per_row, float per_seg,
-                                                         const int4* __restrict__ hitrows, int hit_cap,
+                                                         int rbase, const int4* __restrict__ hitrows, int hit_cap,
                                                          const int32_t* __restrict__ hit_count,
                                                          const float* __restrict__ ta, fdas_cand* __restrict__ cands,
                                                          int cap, int32_t* __restrict__ counts) {
   constexpr int STRIDE =
       MAP == FDAS_HSUM_HIGHEST ? kStrideHigh : MAP == FDAS_HSUM_FUNDAMENTAL ? kStrideFund : 1;
-  const int len = rend - rbase;
-  const int64_t entries = min(*hit_count, hit_cap);
-  const int lane = threadIdx.x & 63;
-  const unsigned stride = gridDim.x * HS_THREADS;  // at most 2^22
-  const unsigned start = blockIdx.x * HS_THREADS + (threadIdx.x & ~63);
-  const bool once = entries * kRowsPerPass <= stride;  // uniform
-  int W = kRowsPerPass, e = (int)((start + lane) / kRowsPerPass), o = (int)((start + lane) % kRowsPerPass);
-  int step_e = 0, step_o = 0;
-  if (!once) {
-    // item w0 + lane is row o of entry e: stepped on without a division
-    W = (len + segs - 1) / segs;
-    e = (int)((start + lane) / (unsigned)W);
-    o = (int)((start + lane) % (unsigned)W);
-    step_e = (int)(stride / (unsigned)W);
-    step_o = (int)(stride % (unsigned)W);
-  }
-  const int64_t items = entries * W;
-  for (int64_t w0 = start; w0 < items; w0 += stride, e += step_e, o += step_o) {
-    if (o >= W) {
-      o -= W;
-      ++e;
-    }
-    bool act = w0 + lane < items;
-    int4 ent = make_int4(0, 0, 0, 0);
-    int b = 0;
-    if (act) {
-      ent = hitrows[e];
-      b = once ? o : entry_first_row(ent, len, segs, per_row, per_seg) + o;
-      const unsigned word = (unsigned)(b < 32 ? ent.y : (b < 64 ? ent.z : ent.w));
-      act = b < len && ((word >> (b % 32)) & 1u) != 0;
-    }
-    if (__ballot(act) == 0ull) continue;  // uniform
-    const int r = rbase + b, i = r - z_max;
+  deal_rows<kRowsPerPass>(hitrows, min(*hit_count, hit_cap), [&](int c0, int bit, bool act) {
+    const int r = rbase + bit, i = r - z_max;
     float hk[NH + 1][4];
-    if (act) map_sums<MAP, NH>(hk, fop, ld, n, z_max, i, ent.x);
-    hs_append_wave<NH, STRIDE>(hk, n, 2 * z_max + 1, ent.x, i, r, act, ta, cands, cap, counts, lane);
-  }
+    if (act) map_sums<MAP, NH>(hk, fop, ld, n, z_max, i, c0);
+    hs_append_wave<NH, STRIDE>(hk, n, 2 * z_max + 1, c0, i, r, act, ta, cands, cap, counts, threadIdx.x & 63);
+  });
 }
 
-// Phase 2: work item w = entry * ROWS + row, grid-stride over all items in
-// wave-uniform steps so the whole wave reaches the compaction together; with four
-// segments and more items than threads entry * W + row within the entry's segment.
-// 2^18 bins with most rows above threshold took 3.77 ms with all rows to an entry, take
-// 1.07 this way and 1.04 in one segment.
+// Phase 2 of the 85-row kernel: work item w = entry * ROWS + row, grid-stride over
+// all items in wave-uniform steps so the whole wave reaches the compaction together
+// (hits crowd into rows near pulsars, and single waves would have dozens of rounds
+// if the set rows were dealt); with row segments, which have few rows each, as
+// deal_rows does: 2^18 bins with most rows above threshold took 3.77 ms with all
+// rows to an entry, take 0.46 this way.
 template <int Z, int NH, int SEGS = 1>
 __global__ __launch_bounds__(HS_THREADS) void k_harmsum_emit(const float* __restrict__ fop, int64_t ld, int n,
                                                              const int4* __restrict__ hitrows,
@@ -1052,28 +1090,26 @@ __global__ __launch_bounds__(HS_THREADS) void k_harmsum_emit(const float* __rest
                                                              const float* __restrict__ ta,
                                                              fdas_cand* __restrict__ cands, int cap,
                                                              int32_t* __restrict__ counts) {
-  constexpr int ROWS = 2 * Z + 1;
-  const int64_t entries = *hitrow_count;
   const int lane = threadIdx.x & 63;
+  if constexpr (SEGS > 1) {
+    deal_rows<2 * Z + 1>(hitrows, *hitrow_count, [&](int c0, int bit, bool act) {
+      hs_emit_wave<Z, NH>(fop, ld, n, c0, bit, act, ta, cands, cap, counts, lane);
+    });
+    return;
+  }
+  constexpr int ROWS = 2 * Z + 1;
+  const int64_t items = (int64_t)(*hitrow_count) * ROWS;
   const int64_t stride = (int64_t)gridDim.x * HS_THREADS;
-  const bool once = SEGS == 1 || entries * ROWS <= stride;  // uniform
-  constexpr int WS = (ROWS + SEGS - 1) / SEGS;
-  const int64_t items = entries * (once ? ROWS : WS);
   for (int64_t w0 = (int64_t)blockIdx.x * HS_THREADS + (threadIdx.x & ~63); w0 < items; w0 += stride) {
     const int64_t w = w0 + lane;
     bool act = w < items;
     int4 ent = make_int4(0, 0, 0, 0);
     int r = 0;
     if (act) {
-      if (once) {
-        ent = hitrows[w / ROWS];
-        r = (int)(w % ROWS);
-      } else {
-        ent = hitrows[w / WS];
-        r = (int)(w % WS) + entry_first_row(ent, ROWS, SEGS, 1.0f / ROWS, 1.0f / SEGS);
-      }
+      ent = hitrows[w / ROWS];
+      r = (int)(w % ROWS);
       const unsigned word = (unsigned)(r < 32 ? ent.y : (r < 64 ? ent.z : ent.w));
-      act = (SEGS == 1 || r < ROWS) && ((word >> (r % 32)) & 1u) != 0;
+      act = ((word >> (r % 32)) & 1u) != 0;
     }
     if (__ballot(act) == 0ull) continue;  // uniform
     hs_emit_wave<Z, NH>(fop, ld, n, ent.x, r, act, ta, cands, cap, counts, lane);
@@ -1302,8 +1338,8 @@ hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_
   const size_t reserve = MAP == FDAS_HSUM_HIGHEST ? 50000 : MAP == FDAS_HSUM_FUNDAMENTAL ? 36000 : 0;
   hipLaunchKernelGGL(detect, dim3(blocks, segs), dim3(HS_THREADS), reserve, s, fop, ld, n, z_max, rbase, rend, order, ta,
                      wk.hitrows, wk.hit_cap, wk.hitrow_count);
-  hipLaunchKernelGGL((k_emit_map<MAP, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, n, z_max, rbase, rend,
-                     (int)segs, 1.0f / (rend - rbase), 1.0f / segs, wk.hitrows, wk.hit_cap, wk.hitrow_count, ta, cands, cap, counts);
+  hipLaunchKernelGGL((k_emit_map<MAP, NH>), dim3(eblocks), dim3(HS_THREADS), 0, s, fop, ld, n, z_max, rbase,
+                     wk.hitrows, wk.hit_cap, wk.hitrow_count, ta, cands, cap, counts);
   return hipGetLastError();
 }
 

@@ -3,8 +3,10 @@
 Spectra short enough for row segments list every segment's rows by themselves;
 the emission must not visit all rows for each.  A spectrum four bins longer than
 the longest with segments does the same work in one: the shorter one may not
-take longer (1.3 x for the segments' own launch shape and the box).  Lists, counts and
-order are checked where rows are full in one segment and empty in another.
+take longer (1.3 x for the segments' own launch shape and the box).  Nor may a false-alarm
+probability of 1e-4, whose candidates fit in the default lists, take 1.5 x the time of
+the default 1e-6 on a long spectrum.  Lists, counts and order are checked where rows
+are full in one segment and empty in another.
 """
 
 import numpy as np
@@ -20,11 +22,11 @@ from paper_1806_01556_amd import fdas  # noqa: E402
 MAPS = {"stretch": fdas.HSUM_STRETCH, "fundamental": fdas.HSUM_FUNDAMENTAL, "highest": fdas.HSUM_HIGHEST}
 
 
-def _time(n, z_max, index):
+def _time(n, z_max, index, p_fa=0.05):
     with fdas.plan_create(n_max=1 << 21, z_max=z_max, hsum_index=MAPS[index]) as plan:
         g = torch.Generator(device="cuda:0").manual_seed(3)
         fop = torch.empty((plan.rows, fdas.fop_ld(n)), device="cuda:0").exponential_(generator=g)
-        thr = fdas.thresholds(8, 0.05).astype(np.float32)
+        thr = fdas.thresholds(8, p_fa).astype(np.float32)
         ta = torch.from_numpy(np.repeat(thr[:, None], plan.rows, 1).copy()).to("cuda:0")
         cands, counts = fdas.alloc_cands(plan, "cuda:0")
         best = 1e9
@@ -45,6 +47,14 @@ def test_dense_planes_take_no_longer_in_segments(index, z_max, n):
     with_segments, without = _time(n, z_max, index), _time(n + 4, z_max, index)
     print(f"dense planes: {index} z_max={z_max} n={n}: {1e3 * with_segments:.0f} us, n + 4: {1e3 * without:.0f}", flush=True)
     assert with_segments <= 1.3 * without
+
+
+@pytest.mark.parametrize("index", ["fundamental", "highest"])
+def test_isolated_hits_take_little_of_the_time(index):
+    n, z_max = 1 << 21, 42
+    many, few = _time(n, z_max, index, 1e-4), _time(n, z_max, index, 1e-6)
+    print(f"isolated hits: {index}: {1e3 * many:.0f} us at 1e-4, {1e3 * few:.0f} at 1e-6", flush=True)
+    assert many <= 1.5 * few
 
 
 @pytest.mark.parametrize("index", sorted(MAPS))
