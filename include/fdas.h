@@ -128,8 +128,8 @@ void fdas_plan_desc_default(fdas_plan_desc* desc);
  * Device memory held: the template tables (2.8 MB at z_max 42), 32 bytes per record
  * of the n_harm * cand_capacity that a readback orders, and 16 bytes per entry of
  * the harmonic sum's hit list: 8768 and the largest of n_max / 4, min(2 n_max, 196608)
- * and min(n_max, 2^18) entries (0.7 MB for 2^14 bins, 17 MB for 2^22); batch calls add
- * theirs on first use.  Page-locked host memory: 128 KB, and 16 * n_harm * cand_capacity
+ * and min(n_max, 2^18) (highest-anchored map: 2^20) entries (0.7 MB for 2^14 bins, 17 MB
+ * for 2^22); batch calls add theirs on first use.  Page-locked host memory: 128 KB, and 16 * n_harm * cand_capacity
  * bytes from the first fdas_candidates_mapped on.
  * Returns FDAS_ERR_NO_DEVICE when no GPU is present; *out is NULL on error. */
 fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out);

@@ -381,7 +381,7 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), 9 * sizeof(int32_t), 0)) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void**>(&p->h_early), fdas::kEarlyRecords * sizeof(fdas_cand), 0)) !=
             hipSuccess ||
-        (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max) * sizeof(int4))) != hipSuccess ||
+        (e = hipMalloc(&p->d_hitrows, (size_t)fdas::harmsum_hit_entries(desc->n_max, desc->hsum_index) * sizeof(int4))) != hipSuccess ||
         (e = hipMalloc(&p->d_hitrow_count, sizeof(int32_t))) != hipSuccess) {
       free_plan(p);
       return hip_fail(e, "allocating the candidate sort workspace");
@@ -452,7 +452,7 @@ fdas_status fdas_harmonic_sum(fdas_plan* p, const float* d_fop, int64_t n, int64
   }
   hipError_t e;
   fdas::HsWork wk{d_order, order_blocks, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups,
-                  (int)fdas::harmsum_hit_entries(p->desc.n_max)};
+                  (int)fdas::harmsum_hit_entries(p->desc.n_max, p->desc.hsum_index)};
   e = fdas::launch_harmsum(d_fop, n, ld, p->desc.z_max, p->desc.n_harm, d_ta ? d_ta : p->d_ta, d_cands,
                            p->desc.cand_capacity, d_counts, wk, p->desc.hsum_index, s);
   if (e != hipSuccess) return hip_fail(e, "launching the harmonic sum");

@@ -158,9 +158,9 @@ struct HsWork {
   int emit_blocks;           // workgroups of phase 2 (0: default)
   int hit_cap;               // entries the list holds, at least harmsum_hit_entries of the plan's n_max
 };
-// Hit-row entries a plan for spectra of up to n_max bins needs: one per thread
-// of phase 1, row segments of short spectra included.
-int64_t harmsum_hit_entries(int64_t n_max);
+// Hit-row entries a plan for spectra of up to n_max bins and an index map needs: one
+// per thread of phase 1, row segments of short spectra included.
+int64_t harmsum_hit_entries(int64_t n_max, int index);
 
 // One spectrum of a batch for the harmonic sum (device table entry).
 struct HsTrial {

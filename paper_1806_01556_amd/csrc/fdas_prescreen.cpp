@@ -382,7 +382,7 @@ fdas_status fdas_search_blocks(fdas_plan* p, const void* d_spectrum, int64_t n, 
                              p->desc.z_max, slots, s);
   if (e == hipSuccess && !tiles.empty()) {
     HsWork wk{p->d_lists + chunks.size() + src_chunks.size(), (int)tiles.size(), p->d_hitrows, p->d_hitrow_count,
-              p->tuning.emit_workgroups, (int)harmsum_hit_entries(p->desc.n_max)};
+              p->tuning.emit_workgroups, (int)harmsum_hit_entries(p->desc.n_max, p->desc.hsum_index)};
     e = launch_harmsum(d_fop, n, ld, p->desc.z_max, nh, p->d_ta, d_cands, p->desc.cand_capacity, d_counts, wk,
                        FDAS_HSUM_STRETCH, s);
   }
@@ -455,7 +455,7 @@ fdas_status fdas_search_flagged(fdas_plan* p, const void* d_spectrum, int64_t n,
   if (e == hipSuccess) {
     // every tile slot gets a workgroup; slots past the selection hold -1 and exit
     HsWork wk{lists + cap_c, cap_t, p->d_hitrows, p->d_hitrow_count, p->tuning.emit_workgroups,
-              (int)harmsum_hit_entries(p->desc.n_max)};
+              (int)harmsum_hit_entries(p->desc.n_max, p->desc.hsum_index)};
     e = launch_harmsum(d_fop, n, ld, p->desc.z_max, nh, p->d_ta, d_cands, p->desc.cand_capacity, d_counts, wk,
                        FDAS_HSUM_STRETCH, s);
   }

@@ -38,12 +38,18 @@ constexpr int HS_THREADS = 256;
 //
 // The row segments (blockIdx.y) fill the chip where the columns alone do not:
 // 256 columns make a wave, so n below about 3072 waves x 256 = 786,432 bins is
-// split, up to 8 ways.  A launch covers at most 96 rows (the bits of an entry).
+// split, up to 8 ways.  The highest-anchored map, whose rows take longest, is split
+// four ways from 2^18 to 2^20 bins: 512 to 1024 workgroups of whole columns are two or
+// three to a compute unit, and the time is that of the units with one more (2^19 bins
+// 272 -> 212 us, 235 before there were segments; 400,000 224 -> 173, 2^20 465 ->
+// 388).  A launch covers at most 96 rows (the bits of an entry).
 
 constexpr int XT = 4 * HS_THREADS;
 constexpr int kRowsPerPass = 96;
 constexpr int kSplitBins = 786432;
 constexpr int kMaxSegs = 8;
+constexpr int kHighSegs = 4;
+constexpr int kHighSplitLo = 1 << 18, kHighSplitHi = 1 << 20;
 // entries past those of ceil(n / 4) threads: the last tile's and block's hold fewer than four columns each
 constexpr int kHitSlack = kMaxSegs * (kStrideHigh + HS_THREADS);
 
@@ -1343,11 +1349,14 @@ hipError_t launch_map(Detect detect, const float* fop, int n, int64_t ld, int z_
   return hipGetLastError();
 }
 
-int64_t harmsum_hit_entries(int64_t n_max) {
+int64_t harmsum_hit_entries(int64_t n_max, int index) {
   // segments x groups of the longest spectrum, and of the one with the most of either split
   const int64_t maps = std::min<int64_t>(kMaxSegs * ((n_max + 3) / 4), kSplitBins / 4);
   const int64_t rows85 = kSegRows * ((std::min<int64_t>(n_max, kSegMaxN) + 3) / 4);
-  return std::max({(n_max + 3) / 4, maps, rows85}) + kHitSlack;
+  const int64_t high = index == FDAS_HSUM_HIGHEST && n_max > kHighSplitLo
+                           ? kHighSegs * ((std::min<int64_t>(n_max, kHighSplitHi) + 3) / 4)
+                           : 0;
+  return std::max({(n_max + 3) / 4, maps, rows85, high}) + kHitSlack;
 }
 
 hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, int n_harm, const float* ta,
@@ -1411,7 +1420,8 @@ hipError_t launch_harmsum(const float* fop, int64_t n, int64_t ld, int z_max, in
   }
   if (groups > wk.hit_cap) return hipErrorInvalidValue;
   // row segments: enough waves to fill the chip, if the list can hold every thread's entry
-  const int64_t want = std::min<int64_t>(kMaxSegs, kSplitBins / n);
+  int64_t want = std::min<int64_t>(kMaxSegs, kSplitBins / n);
+  if (index == FDAS_HSUM_HIGHEST && n > kHighSplitLo && n <= kHighSplitHi) want = kHighSegs;
   const unsigned segs = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, wk.hit_cap / groups));
   const int rows = 2 * z_max + 1;
   for (int rbase = 0; rbase < rows; rbase += kRowsPerPass) {
