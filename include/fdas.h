@@ -68,7 +68,8 @@ typedef enum {
  * lo = round16(v - hi) and each product as hi*hi + hi*lo + lo*hi (BF16: and
  * lo*lo) on the 16-bit
  * matrix cores with FP32 accumulation (FP16 operands are scaled by exact
- * powers of two per workgroup strip and per template tile). */
+ * powers of two per workgroup strip and per template tile).  Banks of z_max <= 7
+ * run in FP32 in any case: it is faster there, and at least as accurate. */
 typedef enum {
   FDAS_PREC_FP32 = 0,
   FDAS_PREC_SPLIT_FP16 = 1,

@@ -326,7 +326,8 @@ fdas_status fdas_plan_create(const fdas_plan_desc* desc, fdas_plan** out) {
   std::vector<std::vector<std::complex<double>>> bank;
   fdas::template_bank(desc->z_max, bank);
   p->direct = desc->method == FDAS_CONV_DIRECT_MFMA;
-  const bool split = desc->precision != FDAS_PREC_FP32;
+  const bool split = desc->precision != FDAS_PREC_FP32 && desc->z_max > fdas::kSplitAboveZ;
+  p->dsplit = split;
   fdas::DirectPack pk;
   if (p->direct) {
     if (split)
@@ -413,7 +414,7 @@ fdas_status fdas_convolve(fdas_plan* p, const void* d_spectrum, int64_t n, float
   if (p->direct) {
     const fdas::DirectTables t{p->d_Bpk,   p->d_Bsp,       p->d_tscale,       p->d_dsteps,           p->d_drows,
                                p->d_dedge, p->d_dedge_tap, p->dgroups.data(), (int)p->dgroups.size(), p->dP_max};
-    if (p->desc.precision == FDAS_PREC_FP32)
+    if (!p->dsplit)
       e = fdas::launch_direct_conv(static_cast<const float2*>(d_spectrum), n, d_fop, ld, t, p->cus,
                                    static_cast<hipStream_t>(stream));
     else

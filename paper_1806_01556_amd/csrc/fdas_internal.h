@@ -46,6 +46,11 @@ struct DirectPack {
   std::vector<DirectGroup> groups;
   int P_max = 0;                // widest template, L/2
 };
+// Templates up to |z| = kSplitAboveZ run in FP32 whatever precision a plan asks for:
+// a bank of one tile has too few products for the 16-bit matrix cores to make up for
+// the split of its operands (2^22 bins, z_max 0, 3, 7: FP32 43, 79, 120 us; split
+// FP16 124, 124, 159).
+constexpr int kSplitAboveZ = 7;
 void direct_pack(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, DirectPack& pk);
 void direct_pack_split(const std::vector<std::vector<std::complex<double>>>& bank, int z_max, bool bf16,
                        DirectPack& pk);

@@ -26,6 +26,7 @@ struct fdas_plan {
   float* d_dedge_tap = nullptr; // direct: unpaired tap of every column
   std::vector<fdas::DirectGroup> dgroups;  // direct: tiles of every launch
   int dP_max = 0;
+  bool dsplit = false;          // direct: split operands (else FP32)
   float* d_ta = nullptr;    // [n_harm][rows] default thresholds
   std::vector<float> h_ta;
   fdas_cand* d_sort_a = nullptr;  // [n_harm * cand_capacity] packed candidates

@@ -508,7 +508,10 @@ __device__ __forceinline__ void split_step(v4f (&ar)[TG][SSUB], v4f (&ai)[TG][SS
   }
 }
 
-template <typename T, int TG>
+// NB parts of 128 bins to a block, one after another on one staged strip: narrow
+// banks have so few steps that staging, with its halo of three steps and the wait
+// for its loads, is most of the time.
+template <typename T, int TG, int NB>
 __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     const float2* __restrict__ x, int64_t n, float* __restrict__ fop, int64_t ld, const uint4* __restrict__ Bsp,
     const int* __restrict__ steps, const float* __restrict__ tscale, const int* __restrict__ rows,
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
   __shared__ float s_max[4];
   const int tid = threadIdx.x;
   load_columns(cols, 16 * TG, rows, edge, edge_tap, tscale, tid);
-  const int strip = SBLK_BINS + 2 * halo;  // bins jb - halo + u
+  const int strip = NB * SBLK_BINS + 2 * halo;  // bins jb - halo + u
   float2* xs = reinterpret_cast<float2*>(lds_u4 + 128 * (count + 1));
   for (int i = tid; i < count * 128; i += 256) lds_u4[i] = Bsp[i];
   const int lane = tid & 63;
@@ -536,7 +539,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
 #pragma unroll
     for (int i = 0; i < SPER; ++i) {
       const int u = tid + 256 * i;
-      const int64_t idx = (int64_t)blk * SBLK_BINS - halo + u;
+      const int64_t idx = (int64_t)blk * (NB * SBLK_BINS) - halo + u;
       nx[i] = (u < strip && idx >= 0 && idx < n) ? x[idx] : make_float2(0.0f, 0.0f);
     }
   };
@@ -565,7 +568,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
   fetch(blk0);
   note_max();
   for (int blk = blk0; blk < blk1; ++blk) {
-    const int64_t j0 = (int64_t)blk * SBLK_BINS;
+    const int64_t j0 = (int64_t)blk * (NB * SBLK_BINS);
     __syncthreads();  // every wave is done with the previous strip
     const float mx = fmaxf(fmaxf(fabsf(s_max[0]), fabsf(s_max[1])), fmaxf(fabsf(s_max[2]), fabsf(s_max[3])));
     const int bad = __builtin_amdgcn_readfirstlane(__float_as_int(s_max[0]) | __float_as_int(s_max[1]) |
@@ -583,79 +586,86 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_split(
     }
     __syncthreads();
     if (blk + 1 < blk1) fetch(blk + 1);
-    v4f ar[TG][SSUB], ai[TG][SSUB];
+    for (int nb = 0; nb < NB; ++nb) {
+      if (NB > 1 && nb > 0 && j0 + nb * SBLK_BINS >= n) break;  // uniform
+      const float2* part = xs + halo + nb * SBLK_BINS;
+      v4f ar[TG][SSUB], ai[TG][SSUB];
 #pragma unroll
-    for (int t = 0; t < TG; ++t)
+      for (int t = 0; t < TG; ++t)
 #pragma unroll
-      for (int s = 0; s < SSUB; ++s) ar[t][s] = ai[t][s] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    const float2* up = xs + halo + w0 + m + 8 * kg;
-    const float2* dn = xs + halo + w0 + m - 8 * kg;
-    const uint4* b = lds_u4 + lane;
-    float2 u[2][8], d[2][8];
-    strip_up(up, u[0]);
-    strip_up(up + 32, u[1]);
-    strip_down(dn, d[0]);
-    strip_down(dn + 32, d[1]);
-    up += 64;
-    dn -= 32;
-    for (int q = 0; q < run[0]; q += 2) {
-      int active = 0, next = 0;
+        for (int s = 0; s < SSUB; ++s) ar[t][s] = ai[t][s] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+      const float2* up = part + w0 + m + 8 * kg;
+      const float2* dn = part + w0 + m - 8 * kg;
+      const uint4* b = lds_u4 + lane;
+      float2 u[2][8], d[2][8];
+      strip_up(up, u[0]);
+      strip_up(up + 32, u[1]);
+      strip_down(dn, d[0]);
+      strip_down(dn + 32, d[1]);
+      up += 64;
+      dn -= 32;
+      for (int q = 0; q < run[0]; q += 2) {
+        int active = 0, next = 0;
+#pragma unroll
+        for (int t = 0; t < TG; ++t) {
+          active += q < run[t] ? 1 : 0;
+          next += q + 1 < run[t] ? 1 : 0;
+        }
+        split_step<T, TG, 0>(ar, ai, u, d, up, dn, b, active);
+        b += 128 * active;
+        if (next == 0) break;  // uniform: an odd number of steps
+        split_step<T, TG, 1>(ar, ai, u, d, up + 32, dn - 32, b, next);
+        b += 128 * next;
+        up += 64;
+        dn -= 64;
+      }
+      if (nb == 0 && blk + 1 < blk1) note_max();
+      const int64_t jb = j0 + nb * SBLK_BINS + w0;
+      const int64_t left = n - (jb + 4 * kg);
+      const bool whole = j0 + (nb + 1) * SBLK_BINS <= n;  // uniform
+      const float2* __restrict__ here = part + w0 + 4 * kg;
 #pragma unroll
       for (int t = 0; t < TG; ++t) {
-        active += q < run[t] ? 1 : 0;
-        next += q + 1 < run[t] ? 1 : 0;
-      }
-      split_step<T, TG, 0>(ar, ai, u, d, up, dn, b, active);
-      b += 128 * active;
-      if (next == 0) break;  // uniform: an odd number of steps
-      split_step<T, TG, 1>(ar, ai, u, d, up + 32, dn - 32, b, next);
-      b += 128 * next;
-      up += 64;
-      dn -= 64;
-    }
-    if (blk + 1 < blk1) note_max();
-    const int64_t jb = j0 + w0;
-    const int64_t left = n - (jb + 4 * kg);
-    const bool whole = j0 + SBLK_BINS <= n;  // uniform
-    const float2* __restrict__ here = xs + halo + w0 + 4 * kg;
+        const ColumnInfo ci = cols[t * 16 + m];
+        edge_add<32>(here, ci.edge, ci.tap, ar[t], ai[t]);
+        const float unscale = ldexpf(ci.scale, -ex);
+        const int row = ci.row;
+        float* dst = fop + (size_t)(row < 0 ? 0 : row) * ld + jb + 4 * kg;
 #pragma unroll
-    for (int t = 0; t < TG; ++t) {
-      const ColumnInfo ci = cols[t * 16 + m];
-      edge_add<32>(here, ci.edge, ci.tap, ar[t], ai[t]);
-      const float unscale = ldexpf(ci.scale, -ex);
-      const int row = ci.row;
-      float* dst = fop + (size_t)(row < 0 ? 0 : row) * ld + jb + 4 * kg;
-#pragma unroll
-      for (int s = 0; s < SSUB; ++s) {
-        const v4f a = ar[t][s] * unscale, c = ai[t][s] * unscale;
-        if (whole)
-          pair_store(a, c, row, dst + 32 * s, 4);
-        else
-          pair_store(a, c, row, dst + 32 * s, left - 32 * s);
+        for (int s = 0; s < SSUB; ++s) {
+          const v4f a = ar[t][s] * unscale, c = ai[t][s] * unscale;
+          if (whole)
+            pair_store(a, c, row, dst + 32 * s, 4);
+          else
+            pair_store(a, c, row, dst + 32 * s, left - 32 * s);
+        }
       }
     }
-    if (bad < 0)
-      repair_cells<SBLK_BINS, TG>(x, n, fop, ld, j0, Pm, cols, [&](int t, int col, int d) {
+    if (bad < 0) {
+      auto tap = [&](int t, int col, int d) {
         // lane 16 ((d / 8) % 4) + col, value d % 8: hi, and lo 64 lanes on
         const T* e = reinterpret_cast<const T*>(lds_u4 + 128 * group_entry<TG>(steps, t, d / 32));
         const int at = (16 * ((d >> 3) & 3) + col) * 8 + (d & 7);
         return (float)e[at] + (float)e[at + 512];
-      });
+      };
+      constexpr int RB = NB * SBLK_BINS < 256 ? NB * SBLK_BINS : 256;
+      for (int q = 0; q < NB * SBLK_BINS; q += RB) repair_cells<RB, TG>(x, n, fop, ld, j0 + q, Pm, cols, tap);
+    }
   }
 }
 
 }  // namespace
 
-template <typename T, int TG>
+template <typename T, int TG, int NB>
 hipError_t launch_split_group(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
                               const DirectGroup& gr, int halo, int blocks, unsigned grid, hipStream_t s) {
-  const size_t lds = (size_t)2048 * (gr.count + 1) + sizeof(float2) * (size_t)(SBLK_BINS + 2 * halo);
+  const size_t lds = (size_t)2048 * (gr.count + 1) + sizeof(float2) * (size_t)(NB * SBLK_BINS + 2 * halo);
   if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_direct_conv_split<T, TG>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_direct_conv_split<T, TG, NB>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_direct_conv_split<T, TG>), dim3(grid), dim3(256), lds, s, x, n, fop, ld,
+  hipLaunchKernelGGL((k_direct_conv_split<T, TG, NB>), dim3(grid), dim3(256), lds, s, x, n, fop, ld,
                      t.Bsp + (size_t)128 * gr.offset, t.steps + gr.first, t.tscale + gr.first, t.rows + 16 * gr.first,
                      t.edge + 8 * gr.first, t.edge_tap + 16 * gr.first, gr.count, halo, t.P_max, blocks);
   return hipGetLastError();
@@ -664,25 +674,33 @@ hipError_t launch_split_group(const float2* x, int64_t n, float* fop, int64_t ld
 hipError_t launch_direct_conv_split(const float2* x, int64_t n, float* fop, int64_t ld, const DirectTables& t,
                                     int cus, bool bf16, hipStream_t s) {
   if (t.P_max > MAX_P || t.ngroups < 1 || n < 1 || !t.Bsp || !t.tscale || !t.groups) return hipErrorInvalidValue;
-  const int64_t blocks = (n + SBLK_BINS - 1) / SBLK_BINS;
-  const unsigned grid = (unsigned)std::min<int64_t>(blocks, 2 * cus);
   // steps of 32 distances, run in pairs and read one step ahead
   const int halo = 32 * ((t.P_max + 31) / 32 + 3);
+  // Banks of two tiles (z_max 8 .. 15; narrower ones run in FP32): four parts to a
+  // strip where every workgroup has that many.  2^22 bins in FP16, z_max 8 and 15:
+  // 196 and 263 us in blocks of 128 bins, 170 and 250 in 512.
+  const bool narrow = t.ngroups == 1 && t.groups[0].tiles == 2 && n >= (int64_t)4 * SBLK_BINS * 2 * cus;
+  const int bins = (narrow ? 4 : 1) * SBLK_BINS;
+  if (bins + 2 * halo > 256 * SPER) return hipErrorInvalidValue;
+  const int64_t blocks = (n + bins - 1) / bins;
+  const unsigned grid = (unsigned)std::min<int64_t>(blocks, 2 * cus);
   for (int g = 0; g < t.ngroups; ++g) {
     const DirectGroup& gr = t.groups[g];
     hipError_t e = hipErrorInvalidValue;
     switch (gr.tiles) {
-#define FDAS_SPLIT_CASE(TG)                                                                                \
-  case TG:                                                                                                 \
-    e = bf16 ? launch_split_group<__bf16, TG>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s)            \
-             : launch_split_group<_Float16, TG>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s);         \
-    break;
-      FDAS_SPLIT_CASE(1)
-      FDAS_SPLIT_CASE(2)
-      FDAS_SPLIT_CASE(3)
-      FDAS_SPLIT_CASE(4)
-      FDAS_SPLIT_CASE(5)
-      FDAS_SPLIT_CASE(6)
+#define FDAS_SPLIT_CASE(TG, NB)                                                                            \
+  e = bf16 ? launch_split_group<__bf16, TG, NB>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s)          \
+           : launch_split_group<_Float16, TG, NB>(x, n, fop, ld, t, gr, halo, (int)blocks, grid, s);       \
+  break;
+      case 2:
+        if (narrow) {
+          FDAS_SPLIT_CASE(2, 4)
+        }
+        FDAS_SPLIT_CASE(2, 1)
+      case 3: FDAS_SPLIT_CASE(3, 1)
+      case 4: FDAS_SPLIT_CASE(4, 1)
+      case 5: FDAS_SPLIT_CASE(5, 1)
+      case 6: FDAS_SPLIT_CASE(6, 1)
 #undef FDAS_SPLIT_CASE
       default:
         break;
@@ -696,8 +714,12 @@ hipError_t launch_direct_conv(const float2* x, int64_t n, float* fop, int64_t ld
                               hipStream_t s) {
   if (t.P_max > MAX_P || t.ngroups < 1 || n < 1 || !t.Bpk || !t.groups) return hipErrorInvalidValue;
   const int64_t blocks = (n + BLK_BINS - 1) / BLK_BINS;
-  // a workgroup stages its operand once for a contiguous range of blocks
-  const unsigned grid = (unsigned)std::min<int64_t>(blocks, 2 * cus);
+  // A workgroup stages its operand once for a contiguous range of blocks.  Two to a
+  // compute unit are all that the registers of large groups allow; one tile takes 80,
+  // and six hide each other's staging (z_max 0, 2^22 bins: 63 -> 43 us, z_max 7: 142 ->
+  // 123).
+  const bool one = t.ngroups == 1 && t.groups[0].tiles == 1;
+  const unsigned grid = (unsigned)std::min<int64_t>(blocks, (one ? 6 : 2) * cus);
   for (int g = 0; g < t.ngroups; ++g) {
     const DirectGroup& gr = t.groups[g];
     const size_t lds = sizeof(float) * 64 * (size_t)(gr.count + gr.tiles) +
