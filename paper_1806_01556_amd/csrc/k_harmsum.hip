@@ -1020,35 +1020,40 @@ constexpr int kDealEntries = 32;
 template <int ROWS, typename Work>
 __device__ __forceinline__ void deal_rows(const int4* __restrict__ hitrows, int entries, Work work) {
   const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * (HS_THREADS / 64) + (threadIdx.x >> 6), waves = gridDim.x * (HS_THREADS / 64);
-  const bool once = (int64_t)entries * ROWS <= (int64_t)waves * 64;  // uniform
-  const int G = once ? 1 : min(kDealEntries, (entries + waves - 1) / waves);
-  const int w = wave * 64 + lane, row = w % ROWS;  // of a short list
+  const int wave = blockIdx.x * (HS_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int waves = gridDim.x * (HS_THREADS / 64);
+  const bool once = __builtin_expect((int64_t)entries * ROWS <= (int64_t)waves * 64, 1);  // uniform
+  int G = 1;
+  if (!once) G = min(kDealEntries, (int)((unsigned)(entries + waves - 1) / (unsigned)waves));
+  const unsigned w = wave * 64u + lane;  // of a short list
   // one call of work, as its code is long
-  for (int64_t e0 = once ? wave * 64 / ROWS : (int64_t)wave * G; e0 < entries; e0 += (int64_t)waves * G) {
+  // (entries and e0 + waves * G stay far below 2^31)
+  for (int e0 = once ? (int)(wave * 64u / ROWS) : wave * G; e0 < entries; e0 += waves * G) {
     int4 ent = make_int4(0, 0, 0, 0);
-    const int64_t e = once ? w / ROWS : e0 + lane;
-    if (e < entries && (once || lane < G)) ent = hitrows[e];
-    const int cnt = __popc(ent.y) + __popc(ent.z) + __popc(ent.w);
-    int upto = cnt;  // bits of the entries up to this lane's, of lanes under kDealEntries
-    int bits = 64;
+    int e = (int)(w / ROWS);
+    if (!once) e = lane < G ? e0 + lane : entries;
+    if (e < entries) ent = hitrows[e];
+    int cnt = 0, upto = 0;  // bits of this lane's entry and of those up to it, for lanes under kDealEntries
+    int bits = 64, at = lane;
     if (!once) {
+      asm volatile("" : "+v"(at));  // what follows from it stays out of the short list's instructions
+      cnt = upto = __popc(ent.y) + __popc(ent.z) + __popc(ent.w);
 #pragma unroll
       for (int o = 1; o < kDealEntries; o <<= 1) {
-        const int u = __shfl_up(upto, o);
-        if (lane >= o) upto += u;
+        const int u = __builtin_amdgcn_ds_bpermute((at - o) * 4, upto);
+        if (at >= o) upto += u;
       }
       bits = __builtin_amdgcn_readlane(upto, kDealEntries - 1);
     }
     for (int t0 = 0; t0 < bits; t0 += 64) {
-      int c0 = ent.x, bit = row;
+      int c0 = ent.x, bit = (int)(w % ROWS);
       bool act;
       if (once) {
-        const unsigned word = (unsigned)(row < 32 ? ent.y : (row < 64 ? ent.z : ent.w));
-        act = ((word >> (row % 32)) & 1u) != 0;
+        const unsigned word = (unsigned)(bit < 32 ? ent.y : (bit < 64 ? ent.z : ent.w));
+        act = ((word >> (bit % 32)) & 1u) != 0;
         if (__ballot(act) == 0ull) return;  // uniform
       } else {
-        const int t = t0 + lane;
+        const int t = t0 + at;
         int src = 0;  // the entry that holds bit t
 #pragma unroll
         for (int o = kDealEntries / 2; o > 0; o >>= 1) src += t >= __shfl(upto, src + o - 1) ? o : 0;
